@@ -998,50 +998,90 @@ __device__ __forceinline__ void wave_plan(const uint32_t* cls, uint32_t* wb) {
     }
 }
 
-// An island of two (root a) whose members touch at the start of the step,
-// or would close their gap within the step at their present speeds: such a
-// pair is likely to be in contact for most of the step, and so to take
-// every sub-step.  These pairs are ranked apart (rank | TOUCH_BIT) and
-// packed into the first waves of the class, so that they fill few waves;
-// the pairs that can jump fill the rest.  (Only the packing depends on this
-// test: an island's result does not depend on its wave.)
+// Touching islands: an island of two whose members touch at the start of the
+// step, or would close their gap within it at their present speeds, and an
+// island of one in the same position to a wall.  Such an island is likely to
+// be in contact for most of the step and so to take every sub-step, one
+// after the other.  They are ranked apart (rank | TOUCH_BIT) and laid out
+// thinly, ahead of the packed waves (touch_plan).  Only the layout depends on
+// this test: an island's result does not depend on its wave.
 constexpr uint32_t TOUCH_BIT = 0x80000000u;
+constexpr uint32_t CLS_PAIR = WAVE + 2, CLS_WALL = WAVE + 3;     // rank classes of the touching islands
 template <int D>
-__device__ __forceinline__ bool pair_touching(uint32_t a, const PState& A, const uint32_t* __restrict__ alist,
-                                              const uint32_t* __restrict__ ccount,
-                                              const unsigned long long* __restrict__ prefix,
-                                              const uint32_t* __restrict__ cand) {
+__device__ __forceinline__ bool island_touching(uint32_t a, uint32_t size, const PState& A, const PCfg& c,
+                                                const uint32_t* __restrict__ alist,
+                                                const uint32_t* __restrict__ ccount,
+                                                const unsigned long long* __restrict__ prefix,
+                                                const uint32_t* __restrict__ cand) {
+    // (the Hertz-Mindlin loop, whose waves wait for memory, is faster packed:
+    // 64^3 with 40 touching pairs 24.4 against 26.3 ms for 6 steps)
+    if (c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) return false;
     const uint32_t s = alist[a];
+    float us = 0.f;
+#pragma unroll
+    for (int ax = 0; ax < D; ax++) us += A.u[ax][s] * A.u[ax][s];
+    us = sqrtf(us);
+    if (size == 1) {
+        bool near = false;
+#pragma unroll
+        for (int ax = 0; ax < D; ax++) {
+            const float x = A.xh[ax][s] + A.xl[ax][s];
+            near = near || fminf(x, (float)c.n[ax] - x) - 0.5f * A.d[s] < us;
+        }
+        return near;
+    }
     if (ccount[s] == 0) return false;
     const uint32_t t = cand[(uint32_t)(prefix[s] & 0xffffffffULL)];
-    float r2 = 0.f, us = 0.f, ut = 0.f;
+    float r2 = 0.f, ut = 0.f;
 #pragma unroll
     for (int ax = 0; ax < D; ax++) {
         const float e = (A.xh[ax][s] - A.xh[ax][t]) + (A.xl[ax][s] - A.xl[ax][t]);
         r2 += e * e;
-        us += A.u[ax][s] * A.u[ax][s];
         ut += A.u[ax][t] * A.u[ax][t];
     }
-    const float reach = 0.5f * (A.d[s] + A.d[t]) + sqrtf(us) + sqrtf(ut);
+    const float reach = 0.5f * (A.d[s] + A.d[t]) + us + sqrtf(ut);
     return r2 < reach * reach;
+}
+
+// Layout of the touching islands: `per` of them to a workgroup of the
+// sub-step kernel, in `groups` workgroups.  The sub-steps of one such island
+// are a serial chain that a wave runs no faster for holding fewer islands,
+// but several islands that bounce hold each other up (their checks and jumps
+// fall on different trips), and two busy waves slow each other on one compute
+// unit: so as thin as one workgroup per compute unit allows.  100 touching
+// pairs in 203 x 187 x 211 (3109 sub-steps): the sub-step kernel takes 0.55-0.7
+// ms a step, against 1.0-1.7 ms with eight pairs to a workgroup.
+struct TouchPlan {
+    uint32_t per, groups;
+};
+__device__ __forceinline__ TouchPlan touch_plan(uint32_t islands, uint32_t size) {
+    TouchPlan p;
+    p.per = min(max((islands + NUM_CU - 1) / NUM_CU, 1u), 16u / size);
+    p.groups = (islands + p.per - 1) / p.per;
+    return p;
+}
+// lanemember holds the touching pairs (two entries each), the touching
+// islands of one, then, from this offset, the packed waves of 64.
+__device__ __forceinline__ uint32_t touch_lanes(uint32_t pairs, uint32_t walls) {
+    return (2 * pairs + walls + WAVE - 1) / WAVE * WAVE;
 }
 
 // islands by size class: 1..64 packed into waves, 65 = larger than a wave
 // (ranks within a class are counted in LDS per chunk of 256 and reserved
 // with one global atomic per class and chunk: no contended counter)
 template <int D>
-__global__ __launch_bounds__(256) void k_island_class(PState A, const uint32_t* __restrict__ alist,
+__global__ __launch_bounds__(256) void k_island_class(PState A, PCfg c, const uint32_t* __restrict__ alist,
                                                       const uint32_t* __restrict__ ccount,
                                                       const unsigned long long* __restrict__ prefix,
                                                       const uint32_t* __restrict__ cand,
                                                       const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ isize, uint32_t* __restrict__ irank,
                                                       uint32_t* __restrict__ bigroot, uint32_t* counters) {
-    __shared__ uint32_t lc[WAVE + 3], gbase[WAVE + 3];     // [WAVE + 2]: touching pairs
+    __shared__ uint32_t lc[WAVE + 4], gbase[WAVE + 4];     // the last two: touching pairs, touching a wall
     const uint32_t t = threadIdx.x;
     const uint32_t na = counters[CNT_ACTIVE];
     for (uint32_t c0 = blockIdx.x * 256; c0 < na; c0 += gridDim.x * 256) {
-        if (t < WAVE + 3) lc[t] = 0;
+        if (t < WAVE + 4) lc[t] = 0;
         __syncthreads();
         const uint32_t a = c0 + t;
         uint32_t cls = 0, lr = 0;
@@ -1049,23 +1089,23 @@ __global__ __launch_bounds__(256) void k_island_class(PState A, const uint32_t* 
         if (root) {
             const uint32_t sz = isize[a];
             cls = sz <= WAVE ? sz : WAVE + 1;
-            if (cls == 2 && pair_touching<D>(a, A, alist, ccount, prefix, cand)) cls = WAVE + 2;
+            if (cls <= 2 && island_touching<D>(a, cls, A, c, alist, ccount, prefix, cand))
+                cls = cls == 2 ? CLS_PAIR : CLS_WALL;
             lr = atomicAdd(&lc[cls], 1u);
         }
         __syncthreads();
         if (t < WAVE + 2 && lc[t] > 0) gbase[t] = atomicAdd(&counters[CNT_CLASS + t], lc[t]);
-        if (t == WAVE + 2 && lc[t] > 0) gbase[t] = atomicAdd(&counters[CNT_PAIRC], lc[t]);
+        if (t >= CLS_PAIR && t <= CLS_WALL && lc[t] > 0)
+            gbase[t] = atomicAdd(&counters[t == CLS_PAIR ? CNT_PAIRC : CNT_WALLC], lc[t]);
         __syncthreads();
         if (root) {
             const uint32_t r = gbase[cls] + lr;
-            irank[a] = cls == WAVE + 2 ? (r | TOUCH_BIT) : r;
+            irank[a] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
             if (cls == WAVE + 1) bigroot[r] = a;
         }
         __syncthreads();
     }
 }
-
-
 
 // Lane (small islands, packed by size into waves) or slot (large islands)
 // of active particle a; wavebase[s] = first wave of size class s.
@@ -1075,18 +1115,20 @@ __device__ __forceinline__ void island_place_one(uint32_t a, const uint32_t* __r
                                                  int* __restrict__ lanemember, uint32_t* __restrict__ loc,
                                                  const uint32_t* __restrict__ bigoff,
                                                  uint32_t* __restrict__ bigmember, const uint32_t* wavebase,
-                                                 uint32_t ntouch) {
+                                                 uint32_t pairs, uint32_t walls) {
     uint32_t r = parent[a];
     uint32_t pos = atomicAdd(&fill[r], 1u);
     uint32_t sz = isize[r];
-    if (sz <= WAVE) {
-        // islands of two: the ntouch touching pairs first
+    if (sz <= WAVE && (irank[r] & TOUCH_BIT)) {
+        const uint32_t ir = irank[r] & ~TOUCH_BIT;
+        lanemember[sz == 2 ? 2 * ir + pos : 2 * pairs + ir] = (int)a;
+        loc[a] = (ir % touch_plan(sz == 2 ? pairs : walls, sz).per) * sz + pos;
+    } else if (sz <= WAVE) {
         uint32_t ir = irank[r];
-        if (sz == 2) ir = (ir & TOUCH_BIT) ? (ir & ~TOUCH_BIT) : ir + ntouch;
         uint32_t per = WAVE / sz;
         uint32_t w = wavebase[sz] + ir / per;
         uint32_t lane = (ir % per) * sz + pos;
-        lanemember[(long long)w * WAVE + lane] = (int)a;
+        lanemember[touch_lanes(pairs, walls) + (long long)w * WAVE + lane] = (int)a;
         loc[a] = lane;
     } else {
         bigmember[bigoff[irank[r]] + pos] = a;
@@ -1108,8 +1150,8 @@ __global__ __launch_bounds__(256) void k_island_place(const uint32_t* __restrict
     __shared__ uint32_t wb[WAVE + 1];
     __shared__ uint32_t scan4[4];
     __shared__ uint32_t cls[WAVE + 1];
-    const uint32_t ntouch = counters[CNT_PAIRC];
-    if (threadIdx.x <= WAVE) cls[threadIdx.x] = counters[CNT_CLASS + threadIdx.x] + (threadIdx.x == 2 ? ntouch : 0u);
+    const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
+    if (threadIdx.x <= WAVE) cls[threadIdx.x] = counters[CNT_CLASS + threadIdx.x];
     __syncthreads();
     wave_plan(cls, wb);
     const uint32_t nbig = counters[CNT_CLASS + WAVE + 1];
@@ -1130,7 +1172,7 @@ __global__ __launch_bounds__(256) void k_island_place(const uint32_t* __restrict
     }
     const uint32_t na = counters[CNT_ACTIVE];
     for (uint32_t a = blockIdx.x * 256 + threadIdx.x; a < na; a += gridDim.x * 256)
-        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, ntouch);
+        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, pairs, walls);
 }
 
 // Candidate constants for the sub-steps.  K0 = r_c^2 - |r0|^2 is formed in
@@ -1250,12 +1292,11 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
     const uint32_t* __restrict__ aidx, uint32_t* parent, uint32_t* isize, uint32_t* irank, uint32_t* fill,
     int* lanemember, uint32_t* loc, uint32_t* bigroot, uint32_t* bigoff, uint32_t* bigmember, CandData* cdata, MdBuf md,
     uint32_t* counters, long long lane_cap) {
-    __shared__ uint32_t ccls[WAVE + 3];     // [WAVE + 2]: touching pairs
+    __shared__ uint32_t ccls[WAVE + 4];     // the last two: touching pairs, touching a wall
     __shared__ uint32_t wbase[WAVE + 1];
-    __shared__ uint32_t nwaves;
     const uint32_t t = threadIdx.x;
     const uint32_t na = counters[CNT_ACTIVE];
-    if (t < WAVE + 3) ccls[t] = 0;
+    if (t < WAVE + 4) ccls[t] = 0;
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS) uf_hook_one(a, alist, ccount, prefix, cand, aidx, parent);
     __syncthreads();
@@ -1269,15 +1310,14 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         if (parent[a] != a) continue;
         uint32_t sz = isize[a];
         uint32_t cls = sz <= WAVE ? sz : WAVE + 1;
-        if (cls == 2 && pair_touching<D>(a, A, alist, ccount, prefix, cand)) cls = WAVE + 2;
+        if (cls <= 2 && island_touching<D>(a, cls, A, c, alist, ccount, prefix, cand))
+            cls = cls == 2 ? CLS_PAIR : CLS_WALL;
         uint32_t r = atomicAdd(&ccls[cls], 1u);
-        irank[a] = cls == WAVE + 2 ? (r | TOUCH_BIT) : r;
+        irank[a] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
         if (cls == WAVE + 1) bigroot[r] = a;
     }
     __syncthreads();
-    const uint32_t ntouch = ccls[WAVE + 2];
-    if (t == 0) ccls[2] += ntouch;
-    __syncthreads();
+    const uint32_t pairs = ccls[CLS_PAIR], walls = ccls[CLS_WALL];
     wave_plan(ccls, wbase);
     __syncthreads();
     if (t < WAVE) {
@@ -1285,7 +1325,8 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         counters[CNT_CLASS + t + 1] = ccls[t + 1];
     }
     if (t == 0) {
-        nwaves = wbase[0];
+        counters[CNT_PAIRC] = pairs;
+        counters[CNT_WALLC] = walls;
         counters[CNT_WAVES] = wbase[0];
         const uint32_t nbig = ccls[WAVE + 1];
         counters[CNT_CLASS + WAVE + 1] = nbig;
@@ -1298,7 +1339,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
     }
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
-        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, ntouch);
+        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, pairs, walls);
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
         cand_prep_one<D>(a, A, c, alist, ccount, prefix, cand, aidx, loc, cdata, md);
@@ -2305,33 +2346,53 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     __shared__ int sallow[WAVE];
     __shared__ CandData scd[WAVE * CAND_LDS];
     const uint32_t nw = counters[CNT_WAVES];
+    const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
+    const TouchPlan tp = touch_plan(pairs, 2), tw = touch_plan(walls, 1);
     const int lane = threadIdx.x;
     // first wave of size class lane + 1 (non-decreasing in the class)
     const uint32_t wb_lane = counters[CNT_WAVEBASE + 1 + lane];
-    // Without Mindlin, each packed wave is worked by QUARTERS workgroups:
-    // quarter q takes the islands of one or two at its lanes
-    // [16 q, 16 q + 16) in the split form (or in the general loop below,
-    // restricted to those lanes, when one of them does not qualify); a wave
-    // of larger islands is worked by quarter 0 alone.
+    // The touching islands come first, a few per workgroup.  Of the packed
+    // waves, without Mindlin, each is worked by QUARTERS workgroups: quarter q
+    // takes the islands of one or two at its lanes [16 q, 16 q + 16) in the
+    // split form (or in the general loop below, restricted to those lanes,
+    // when one of them does not qualify); a wave of larger islands is worked
+    // by quarter 0 alone.
     constexpr uint32_t QUARTERS = MD ? 1u : 4u;
-    for (uint32_t v = blockIdx.x; v < nw * QUARTERS; v += gridDim.x) {
-        const uint32_t w = v / QUARTERS, part = v % QUARTERS;
-        // the wave's size class is the largest whose first wave is <= w;
-        // its islands fill lanes [0, islands_here * size)
-        const unsigned long long le = __ballot(wb_lane <= w);
-        const int sz = 64 - __clzll(le);
-        const uint32_t per = WAVE / sz;
-        const uint32_t nisl = counters[CNT_CLASS + sz] + (sz == 2 ? counters[CNT_PAIRC] : 0u);
-        const uint32_t idx = w - counters[CNT_WAVEBASE + sz];
-        const uint32_t here = min(per, nisl - idx * per);
-        const bool quartered = !MD && sz <= 2;
-        if (!quartered && part != 0) continue;
-        if (quartered) {
-            // the split form: original lane ol of this quarter for each group of four lanes
-            const int ol = (int)part * 16 +
-                           (sz == 2 ? (((lane >> 4) << 2) | (((lane >> 2) & 1) << 1) | ((lane >> 3) & 1)) : (lane >> 2));
-            const bool sv = (uint32_t)ol < here * (uint32_t)sz;
-            const uint32_t ss = sv ? alist[lanemember[(long long)w * WAVE + ol]] : 0;
+    const uint32_t nt = tp.groups + tw.groups;
+    for (uint32_t v = blockIdx.x; v < nt + nw * QUARTERS; v += gridDim.x) {
+        // islands of size sz at lanes [lane0, lane0 + nl) of the entries from `member`
+        int sz, lane0 = 0, nl;
+        const int* member;
+        bool split = !MD;
+        if (v < nt) {
+            sz = v < tp.groups ? 2 : 1;
+            const uint32_t i0 = sz == 2 ? v * tp.per : (v - tp.groups) * tw.per;
+            nl = sz * (int)(sz == 2 ? min(tp.per, pairs - i0) : min(tw.per, walls - i0));
+            member = lanemember + (sz == 2 ? 2 * i0 : 2 * pairs + i0);
+        } else {
+            // the wave's size class is the largest whose first wave is <= w;
+            // its islands fill lanes [0, islands_here * size)
+            const uint32_t w = (v - nt) / QUARTERS, part = (v - nt) % QUARTERS;
+            const unsigned long long le = __ballot(wb_lane <= w);
+            sz = 64 - __clzll(le);
+            const uint32_t per = WAVE / sz;
+            const uint32_t idx = w - counters[CNT_WAVEBASE + sz];
+            nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
+            member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
+            split = split && sz <= 2;
+            if (!split && part != 0) continue;
+            if (split) {
+                lane0 = (int)part * 16;
+                nl = min(nl - lane0, 16);
+                if (nl <= 0) continue;
+            }
+        }
+        if (split) {
+            // the split form: original lane ol of the 16 for each group of four lanes
+            const int ol = lane0 + (sz == 2 ? (((lane >> 4) << 2) | (((lane >> 2) & 1) << 1) | ((lane >> 3) & 1))
+                                            : (lane >> 2));
+            const bool sv = ol < lane0 + nl;
+            const uint32_t ss = sv ? alist[member[ol]] : 0;
             Active<D> P;
             CandData cd{};
             if (sv) {
@@ -2354,9 +2415,9 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 continue;
             }
         }
-        // the general loop: the whole wave, or this quarter's lanes of it
-        bool valid = (uint32_t)lane < here * (uint32_t)sz && (!quartered || (uint32_t)(lane >> 4) == part);
-        int a = valid ? lanemember[(long long)w * WAVE + lane] : -1;
+        // the general loop: the whole wave, or this workgroup's lanes of it
+        bool valid = lane >= lane0 && lane < lane0 + nl;
+        int a = valid ? member[lane] : -1;
         uint32_t s = valid ? alist[a] : 0;
         Active<D> P;
         int nfirst = 0, isz = 1;
@@ -3127,7 +3188,7 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
         hipLaunchKernelGGL(k_uf_hook, dim3(grid_act), dim3(256), 0, s, b.alist, b.ccount, b.prefix, b.cand, b.aidx, b.parent,
                            b.counters);
         hipLaunchKernelGGL(k_uf_flatten, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.counters);
-        hipLaunchKernelGGL(k_island_class<D>, dim3(grid_act), dim3(256), 0, s, b.A, b.alist, b.ccount, b.prefix,
+        hipLaunchKernelGGL(k_island_class<D>, dim3(grid_act), dim3(256), 0, s, b.A, c, b.alist, b.ccount, b.prefix,
                            b.cand, b.parent, b.isize, b.irank, b.bigroot,
                            b.counters);
         hipLaunchKernelGGL(k_island_place, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.irank, b.fill,

@@ -255,6 +255,7 @@ enum {
     CNT_WAVES = 2,       // packed waves of small islands
     CNT_BIG = 3,         // islands larger than one wave
     CNT_PAIRC = 4,       // islands of two whose members touch at the start of the step
+    CNT_WALLC = 5,       // islands of one that touch a wall at the start of the step
     CNT_CLASS = 8,       // 65 class counters (index 1..64 sizes, 65 big) at 8..73
     CNT_WAVEBASE = 80,   // 66 prefix entries at 80..145
     CNT_SIZE = 160
@@ -262,6 +263,7 @@ enum {
 
 constexpr int WAVE = 64;
 constexpr unsigned NUM_XCD = 8;
+constexpr unsigned NUM_CU = 256;
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  Map dispatch index b (on XCD b % 8) to a logical block so that every

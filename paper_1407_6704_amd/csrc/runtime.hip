@@ -314,7 +314,7 @@ size_t carve(pibm_ctx& c, char* base) {
         b.cand_cap = np * (long long)c.cfg.max_candidates;
         b.cand = cv.take<uint32_t>(b.cand_cap);
         b.cdata = (CandData*)cv.take<char>(b.cand_cap * CAND_BYTES);
-        b.lane_cap = 2 * np + (long long)(WAVE + 2) * WAVE;
+        b.lane_cap = 2 * np + (long long)(WAVE + 3) * WAVE;
         b.lanemember = cv.take<int>(b.lane_cap);
         b.gdx = cv.take<float>(19 * np);
         b.gu = cv.take<float>(6 * np);
