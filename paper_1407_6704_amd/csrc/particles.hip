@@ -1013,9 +1013,6 @@ __device__ __forceinline__ bool island_touching(uint32_t a, uint32_t size, const
                                                 const uint32_t* __restrict__ ccount,
                                                 const unsigned long long* __restrict__ prefix,
                                                 const uint32_t* __restrict__ cand) {
-    // (the Hertz-Mindlin loop, whose waves wait for memory, is faster packed:
-    // 64^3 with 40 touching pairs 24.4 against 26.3 ms for 6 steps)
-    if (c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) return false;
     const uint32_t s = alist[a];
     float us = 0.f;
 #pragma unroll
@@ -1731,14 +1728,15 @@ __device__ __forceinline__ void pair_force(const Active<D>& P, const CandData& c
     for (int a = 0; a < D; a++) F[a] += mag * n[a];
 }
 
-// Hertz-Mindlin pair contact: Hertz normal force, tangential force T
-// (carried in cmd, the force on this particle), torque of T about the
-// centre.  Partner spin ow; contact point at -R_self n from this centre and
-// at +R_partner n from the partner's.
+// Hertz-Mindlin pair contact: Hertz normal force, tangential force T, torque
+// of T about the centre.  S: the tangential state of the contact (T, the
+// force on this particle, first), kt8r = 8 G* sqrt(R*).  Partner spin ow;
+// contact point at -R_self n from this centre and at +R_partner n from the
+// partner's.
 template <int D>
-__device__ __forceinline__ void pair_force_md(const Active<D>& P, const CandData& cd, float4* __restrict__ cmd,
-                                              float4* __restrict__ cms, const float* odx, const float* ou,
-                                              const float* ow, const PCfg& c, float* F, float* tq) {
+__device__ __forceinline__ void pair_contact_md(const Active<D>& P, const CandData& cd, float kt8r, float* S,
+                                                const float* odx, const float* ou, const float* ow, const PCfg& c,
+                                                float* F, float* tq) {
     float r[3] = {0, 0, 0};
     float rd = 0.f, dd = 0.f;
 #pragma unroll
@@ -1749,14 +1747,10 @@ __device__ __forceinline__ void pair_force_md(const Active<D>& P, const CandData
         dd += del * del;
     }
     const float num = cd.K0 - (2.0f * rd + dd);          // r_c^2 - |r|^2
-    float4 m = *cmd;
     if (!(num > 0.f)) {
         // out of contact: no tangential state
-        if (m.x != 0.f || m.y != 0.f || m.z != 0.f) *cmd = make_float4(0.f, 0.f, 0.f, m.w);
-        if (c.microslip) {
-            cms[0] = make_float4(0.f, 0.f, 0.f, 0.f);
-            cms[1] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+#pragma unroll
+        for (int q = 0; q < TSN; q++) S[q] = 0.f;
         return;
     }
     float r2 = 0.f;
@@ -1778,26 +1772,85 @@ __device__ __forceinline__ void pair_force_md(const Active<D>& P, const CandData
     for (int a = 0; a < 3; a++) vrel[a] = (((a < D ? P.u[a] : 0.f) - ou[a]) + ws[a]) - wt[a];
     const float sd = sqrt_fast(delta);
     const float Fn = cd.gam * delta * sd;
-    float T[TSN] = {m.x, m.y, m.z, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (c.microslip) {
-        const float4 s0 = cms[0], s1 = cms[1];
-        T[3] = s0.x; T[4] = s0.y; T[5] = s0.z; T[9] = s0.w;
-        T[6] = s1.x; T[7] = s1.y; T[8] = s1.z;
-    }
-    tangential_update(c, n, vrel, Fn, m.w * sd, T);
-    *cmd = make_float4(T[0], T[1], T[2], m.w);
-    if (c.microslip) {
-        cms[0] = make_float4(T[3], T[4], T[5], T[9]);
-        cms[1] = make_float4(T[6], T[7], T[8], 0.f);
-    }
+    tangential_update(c, n, vrel, Fn, kt8r * sd, S);
     float t[3];
-    cross3(as, T, t);
+    cross3(as, S, t);
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-        if (a < D) F[a] += Fn * n[a] + T[a];
+        if (a < D) F[a] += Fn * n[a] + S[a];
         tq[a] += t[a];
     }
 }
+
+// The same in the no-slip limit as straight-line code (S: T alone).  The
+// operations of pair_contact_md and tangential_update in their order; out of
+// contact the force and the state are zero.
+template <int D>
+__device__ __forceinline__ void pair_contact_flat(const Active<D>& P, const CandData& cd, float kt8r, float* S,
+                                                  const float* odx, const float* ou, const float* ow, const PCfg& c,
+                                                  float* F, float* tq) {
+    float del[3] = {0, 0, 0}, r[3] = {0, 0, 0}, inv, delta;
+#pragma unroll
+    for (int a = 0; a < D; a++) del[a] = P.dx[a] - odx[a];
+    const bool on = pair_geom<D, true>(cd, del, r, inv, delta);
+    float n[3], as[3], at[3], ws[3], wt[3], vrel[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        n[a] = r[a] * inv;
+        as[a] = -P.R * n[a];
+        at[a] = (cd.rc - P.R) * n[a];
+    }
+    cross3(P.W, as, ws);
+    cross3(ow, at, wt);
+#pragma unroll
+    for (int a = 0; a < 3; a++) vrel[a] = (((a < D ? P.u[a] : 0.f) - ou[a]) + ws[a]) - wt[a];
+    const float sd = sqrt_fast(delta);
+    const float Fn = cd.gam * delta * sd;
+    float T[3] = {S[0], S[1], S[2]};
+    into_plane(n, T);
+    const float vn = vrel[0] * n[0] + vrel[1] * n[1] + vrel[2] * n[2];
+#pragma unroll
+    for (int a = 0; a < 3; a++) T[a] += -(kt8r * sd) * c.h * (vrel[a] - vn * n[a]);
+    const float tl2 = T[0] * T[0] + T[1] * T[1] + T[2] * T[2];
+    const float lim = c.mu * Fn;
+    const float sc = tl2 > lim * lim ? lim * rsq_fast(tl2) : 1.0f;
+#pragma unroll
+    for (int a = 0; a < 3; a++) S[a] = on ? T[a] * sc : 0.f;
+    float t[3];
+    cross3(as, S, t);
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        if (a < D) F[a] = on ? Fn * n[a] + S[a] : 0.f;
+        tq[a] = on ? t[a] : 0.f;
+    }
+}
+
+// The tangential state of a candidate entry (cmd, and with micro-slip its
+// two cms words), in global memory or through LDS pointers (as_lds).
+template <class V4>
+__device__ __forceinline__ float md_state_load(V4* cmd, V4* cms, bool microslip, float* S) {
+    S[0] = cmd->x; S[1] = cmd->y; S[2] = cmd->z;
+#pragma unroll
+    for (int q = 3; q < TSN; q++) S[q] = 0.f;
+    if (microslip) {
+        S[3] = cms[0].x; S[4] = cms[0].y; S[5] = cms[0].z; S[9] = cms[0].w;
+        S[6] = cms[1].x; S[7] = cms[1].y; S[8] = cms[1].z;
+    }
+    return cmd->w;
+}
+template <class V4>
+__device__ __forceinline__ void md_state_store(V4* cmd, V4* cms, bool microslip, const float* S, float kt8r) {
+    cmd->x = S[0]; cmd->y = S[1]; cmd->z = S[2]; cmd->w = kt8r;
+    if (microslip) {
+        cms[0].x = S[3]; cms[0].y = S[4]; cms[0].z = S[5]; cms[0].w = S[9];
+        cms[1].x = S[6]; cms[1].y = S[7]; cms[1].z = S[8]; cms[1].w = 0.f;
+    }
+}
+struct V4 {
+    float x, y, z, w;
+};
+using LdsV4 = __attribute__((address_space(3))) V4;
+__device__ __forceinline__ LdsV4* as_lds(float4* p) { return (LdsV4*)p; }
 
 // Candidate k of a particle: the first n1 from `first`, the rest from global
 // memory.  With LDS (the small-island waves cache their first candidates in
@@ -1833,10 +1886,14 @@ __device__ __forceinline__ CandData cand_at(const CandData* first, int n1, const
 template <int D, bool MD>
 __device__ __forceinline__ void substep_update(Active<D>& P, const PCfg& c, const float* F, const float* tq);
 
+// With MD and LDS the tangential states of the first nfirst contacts are in
+// `smd` (MD_LDS float4 each: cmd, then cms[0..1]), the others in md.
+constexpr int MD_LDS = 3;
 template <int D, bool MD, bool LDS = false>
 __device__ __forceinline__ void active_substep(Active<D>& P, const PCfg& c, const CandData* first, int nfirst,
                                                const CandData* __restrict__ rest, const float* sdx,
-                                               const float* su, const float* sw, int stride, const MdBuf& md) {
+                                               const float* su, const float* sw, int stride, const MdBuf& md,
+                                               float4* smd = nullptr) {
     float F[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};
     if (P.wall) {
         if (MD) wall_force_md<D>(P, c, F, tq);
@@ -1872,7 +1929,12 @@ __device__ __forceinline__ void active_substep(Active<D>& P, const PCfg& c, cons
         }
         if (k + 1 < P.cnt) fetch(k + 1);
         if (MD) {
-            pair_force_md<D>(P, cd, md.cmd + P.off + k, md.cms + 2 * (P.off + k), odx, ou, ow, c, F, tq);
+            float S[TSN], kt8r;
+            if (LDS && k < n1) kt8r = md_state_load(as_lds(smd) + MD_LDS * k, as_lds(smd) + MD_LDS * k + 1, c.microslip, S);
+            else kt8r = md_state_load(md.cmd + P.off + k, md.cms + 2 * (P.off + k), c.microslip, S);
+            pair_contact_md<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
+            if (LDS && k < n1) md_state_store(as_lds(smd) + MD_LDS * k, as_lds(smd) + MD_LDS * k + 1, c.microslip, S, kt8r);
+            else md_state_store(md.cmd + P.off + k, md.cms + 2 * (P.off + k), c.microslip, S, kt8r);
         } else {
             pair_force<D>(P, cd, odx, ou, c, F);
         }
@@ -2093,21 +2155,27 @@ __device__ __forceinline__ int free_allowance_one(const Active<D>& P, const PCfg
 // Advance P by m contact-free sub-steps in closed form:
 //   U^{k+m} = U_eq + (U^k - U_eq) q^m,  sum_{i=1..m} U^{k+i} = m U_eq + (U^k - U_eq) q S,
 //   sum_{i<m} g^{k+i} = 2 rho_i (m slip + (U^k - U_eq) S),  S = (1 - q^m)/(1 - q).
+// With MD the tangential states lapse: those of the first nfirst contacts in
+// smd (see active_substep), the others in md.
 template <int D, bool MD>
-__device__ __forceinline__ void active_jump(Active<D>& P, const PCfg& c, int m, const MdBuf& md) {
+__device__ __forceinline__ void active_jump(Active<D>& P, const PCfg& c, int m, const MdBuf& md,
+                                            float4* smd = nullptr, int nfirst = 0) {
     if (MD) {
         // no contact along the stretch: every tangential force lapses, the
         // spin is unchanged
+        float Z[TSN];
+#pragma unroll
+        for (int q = 0; q < TSN; q++) Z[q] = 0.f;
 #pragma unroll
         for (int a = 0; a < 3; a++)
 #pragma unroll
             for (int q = 0; q < TSN; q++) P.wT[a][q] = 0.f;
         for (int k = 0; k < P.cnt; k++) {
-            const float4 q = md.cmd[P.off + k];
-            if (q.x != 0.f || q.y != 0.f || q.z != 0.f) md.cmd[P.off + k] = make_float4(0.f, 0.f, 0.f, q.w);
-            if (c.microslip) {
-                md.cms[2 * (P.off + k)] = make_float4(0.f, 0.f, 0.f, 0.f);
-                md.cms[2 * (P.off + k) + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < nfirst) {
+                LdsV4* q = as_lds(smd) + MD_LDS * k;
+                md_state_store(q, q + 1, c.microslip, Z, q->w);
+            } else {
+                md_state_store(md.cmd + P.off + k, md.cms + 2 * (P.off + k), c.microslip, Z, md.cmd[P.off + k].w);
             }
         }
     }
@@ -2326,6 +2394,110 @@ __device__ __forceinline__ void split_wave(Active<D>& P, const PCfg& c, bool val
     quad_gather<D>(fs, P.fs);
 }
 
+// The value of the lane that differs in bit 0.
+__device__ __forceinline__ float pair_swap(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
+}
+__device__ __forceinline__ int pair_swap(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false); }
+
+// All sub-steps of a wave of Hertz-Mindlin islands of one (NC = 0) or of two
+// (NC = 1), one lane per particle, the members of a pair in neighbouring
+// lanes: the candidate and the contacts' tangential state in registers, the
+// partner's state by a lane swap.  The decisions and arithmetic of the
+// general island loop, which reads and writes the tangential state in LDS
+// on every sub-step.  A serial chain bound by the issue of one wave: FLAT
+// (NC = 1: no-slip contacts and no wall in reach), a sub-step is 182
+// straight-line instructions, 0.3 us.  64^3 with 40 touching pairs, 6 steps of
+// 3109 sub-steps: 24.2 ms with every state in global memory and the general
+// loop for all islands, 11.9 ms now (what is left is an island of three in
+// the general loop, 0.6 us a sub-step, 1.2 us before).  The lanes a swap reads
+// from belong to the reading lane's own island, which takes the same
+// branches, so they are active whenever the reader is.
+template <int D, int NC, bool FLAT>
+__device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid, const CandData& cd,
+                                        const MdBuf& md) {
+    if (!valid) P = Active<D>{};      // padding lanes: a zero state, never stored
+    const float oveq = NC ? pair_swap(P.veq) : 0.f;
+    float S[TSN], kt8r = 0.f;
+#pragma unroll
+    for (int q = 0; q < TSN; q++) S[q] = 0.f;
+    if (NC && valid) kt8r = md_state_load(md.cmd + P.off, md.cms + 2 * P.off, !FLAT && c.microslip, S);
+    auto partner = [&](float* odx, float* ou) {
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            odx[a] = NC && a < D ? pair_swap(P.dx[a]) : 0.f;
+            ou[a] = NC && a < D ? pair_swap(P.u[a]) : 0.f;
+        }
+    };
+    auto substep = [&]() {
+        float F[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};
+        float odx[3], ou[3], ow[3];
+        partner(odx, ou);
+#pragma unroll
+        for (int a = 0; a < 3; a++) ow[a] = NC && (D == 3 || a == 2) ? pair_swap(P.W[a]) : 0.f;
+        if (FLAT) {
+            pair_contact_flat<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
+        } else {
+            if (P.wall) wall_force_md<D>(P, c, F, tq);
+            if (NC) pair_contact_md<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
+        }
+        substep_update<D, true>(P, c, F, tq);
+    };
+    // the loop of split_wave: each island on its own trip count
+    int k = 0, backoff = 1, trip = 0;
+    while (__any(valid && k < c.n_sub)) {
+        bool more, check;
+        int m;
+        for (;;) {
+            more = valid && k < c.n_sub;
+            check = more && (trip & (backoff - 1)) == 0;
+            m = 0;
+            if (__any(check)) {
+                float odx[3], ou[3];
+                partner(odx, ou);
+                int allow = 0;
+                if (check) {
+                    if (NC) allow = free_allowance_one<D>(P, c, cd, odx, ou, oveq, c.n_sub - k);
+                    else allow = free_allowance<D>(P, c, nullptr, 0, nullptr, nullptr, nullptr, nullptr, 0, c.n_sub - k);
+                }
+                const int other = NC ? pair_swap(allow) : allow;
+                m = check ? min(allow, other) : 0;
+            }
+            const bool jump = more && m >= 2;
+            if (!__any(jump)) break;
+            if (jump) {
+                // no contact along the stretch: every tangential force lapses
+#pragma unroll
+                for (int a = 0; a < 3; a++)
+#pragma unroll
+                    for (int q = 0; q < TSN; q++) P.wT[a][q] = 0.f;
+#pragma unroll
+                for (int q = 0; q < TSN; q++) S[q] = 0.f;
+                active_jump<D, false>(P, c, m, md);
+                k += m;
+                backoff = 1;
+                trip += 1;
+            }
+        }
+        if (more) {
+            substep();
+            k += 1;
+            trip += 1;
+            if (check) backoff = min(2 * backoff, 64);
+        }
+        // plain sub-steps up to the next check of any island or its end
+        const bool run = valid && k < c.n_sub;
+        int T = __ockl_wfred_min_i32(run ? min((-trip) & (backoff - 1), c.n_sub - k) : INT_MAX);
+        if (T == INT_MAX) T = 0;
+        if (run) {
+            for (int t = 0; t < T; t++) substep();
+            k += T;
+            trip += T;
+        }
+    }
+    if (NC && valid) md_state_store(md.cmd + P.off, md.cms + 2 * P.off, !FLAT && c.microslip, S, kt8r);
+}
+
 template <int D, bool MD>
 __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np, PCfg c,
                                                      const int* __restrict__ lanemember,
@@ -2345,6 +2517,7 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     __shared__ float sveq[WAVE];
     __shared__ int sallow[WAVE];
     __shared__ CandData scd[WAVE * CAND_LDS];
+    __shared__ float4 smd[MD ? WAVE * CAND_LDS * MD_LDS : 1];
     const uint32_t nw = counters[CNT_WAVES];
     const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
     const TouchPlan tp = touch_plan(pairs, 2), tw = touch_plan(walls, 1);
@@ -2421,10 +2594,33 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
         uint32_t s = valid ? alist[a] : 0;
         Active<D> P;
         int nfirst = 0, isz = 1;
+        if (valid) active_load<D, MD>(P, A, c, s, drho_i, j_i, np, ccount, prefix, md);
+        if constexpr (MD) {
+            if (sz <= 2) {
+                CandData cd{};
+                if (valid && sz == 2 && P.cnt > 0) cd = cdata[P.off];
+                const bool ok = valid && (sz == 1 ? (P.cnt == 0 && !P.fixed)
+                                                  : (P.cnt == 1 && !P.fixed && cd.local == (lane ^ 1)));
+                if (__all(!valid || ok)) {
+                    if (sz == 1) md_wave<D, 0, false>(P, c, valid, cd, md);
+                    else if (!c.microslip && !__any(valid && P.wall)) md_wave<D, 1, true>(P, c, valid, cd, md);
+                    else md_wave<D, 1, false>(P, c, valid, cd, md);
+                    if (valid) active_store<D, MD>(P, Bn, c, s, np, srec, fc, flags, md);
+                    continue;
+                }
+            }
+        }
         if (valid) {
-            active_load<D, MD>(P, A, c, s, drho_i, j_i, np, ccount, prefix, md);
             nfirst = min(P.cnt, CAND_LDS);
-            for (int k = 0; k < nfirst; k++) scd[lane * CAND_LDS + k] = cdata[P.off + k];
+            for (int k = 0; k < nfirst; k++) {
+                scd[lane * CAND_LDS + k] = cdata[P.off + k];
+                if (MD) {
+                    float4* q = smd + (lane * CAND_LDS + k) * MD_LDS;
+                    q[0] = md.cmd[P.off + k];
+                    q[1] = md.cms[2 * (P.off + k)];
+                    q[2] = md.cms[2 * (P.off + k) + 1];
+                }
+            }
             isz = (int)isize[parent[a]];
         }
         const int ibase = (lane / isz) * isz;
@@ -2471,12 +2667,12 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             }
             if (more) {
                 if (m >= 2) {
-                    active_jump<D, MD>(P, c, m, md);
+                    active_jump<D, MD>(P, c, m, md, smd + lane * CAND_LDS * MD_LDS, nfirst);
                     k += m;
                     backoff = 1;
                 } else {
                     active_substep<D, MD, true>(P, c, scd + lane * CAND_LDS, nfirst, rest, sdx[cur], su[cur],
-                                                MD ? sw[cur] : nullptr, WAVE, md);
+                                                MD ? sw[cur] : nullptr, WAVE, md, smd + lane * CAND_LDS * MD_LDS);
                     k += 1;
                     if (check) backoff = min(2 * backoff, 64);
                 }
@@ -2492,7 +2688,16 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 cur ^= 1;
             }
         }
-        if (valid) active_store<D, MD>(P, Bn, c, s, np, srec, fc, flags, md);
+        if (valid) {
+            if (MD)
+                for (int k = 0; k < nfirst; k++) {
+                    const float4* q = smd + (lane * CAND_LDS + k) * MD_LDS;
+                    md.cmd[P.off + k] = q[0];
+                    md.cms[2 * (P.off + k)] = q[1];
+                    md.cms[2 * (P.off + k) + 1] = q[2];
+                }
+            active_store<D, MD>(P, Bn, c, s, np, srec, fc, flags, md);
+        }
         __syncthreads();
     }
 }
