@@ -31,6 +31,9 @@ long long scan_blocks(long long n);
 void particles_sort(int D, PBuf& b, int np, const PCfg& c, hipStream_t s);
 void particles_interp(int D, PBuf& b, int np, const Grid& g, const PCfg& c, const float4* mom, hipStream_t s);
 void particles_unpermute_spin(int D, PBuf& b, int np, float* out, hipStream_t s);
+bool particles_interp_by_nodes(int D, int np);
+void particles_interp_nodes(int Q, PBuf& b, int np, const Grid& g, const PCfg& c, const void* f, int fp16, int sl2,
+                            hipStream_t s);
 void particles_interp_from_populations(PBuf& b, int np, const Grid& g, const PCfg& c, const void* f, int fp16,
                                        int sl2, hipStream_t s);
 void particles_dem(int D, PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t s);
@@ -943,7 +946,8 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     const float ff[3] = {(float)c->cfg.fluid_force[0], (float)c->cfg.fluid_force[1], (float)c->cfg.fluid_force[2]};
     const bool spread = c->np > 0 && c->cfg.two_way;
     const bool fuse_sc = spread && !want_F && c->D == 3 && c->pc.L == 0 && !c->fp16;
-    // D2Q9 interpolation takes the moments straight from the populations of
+    // Few particles in 3D take the moments of their support nodes straight from
+    // the populations.  Otherwise D2Q9 interpolation takes the moments straight from the populations of
     // the tiles that hold particles; 3D (15 or 19 planes, a larger halo) and
     // the coarse-bin path read them from a moments pass, which the cell list
     // restricts to the node rows that the particles' stencils reach
@@ -951,14 +955,16 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     q(mark(c, row, 0));
     if (c->np > 0) particles_sort(c->D, c->pb, c->np, c->pc, c->stream);
     q(mark(c, row, 1));
-    if (c->np > 0 && !fused) {
+    const bool nodes = particles_interp_by_nodes(c->D, c->np);
+    if (c->np > 0 && !fused && !nodes) {
         RowMask m{c->pb.start, {c->pc.n[0], c->pc.n[1], c->pc.n[2]}, {c->pc.nb[0], c->pc.nb[1], c->pc.nb[2]},
                   c->pc.L};
         lattice_moments(c->Q, c->fp16, c->sl2, fin, c->mom, c->N, m, c->stream);
     }
     q(mark(c, row, 2));
     if (c->np > 0) {
-        if (fused) particles_interp_from_populations(c->pb, c->np, c->grid, c->pc, fin, c->fp16, c->sl2, c->stream);
+        if (nodes) particles_interp_nodes(c->Q, c->pb, c->np, c->grid, c->pc, fin, c->fp16, c->sl2, c->stream);
+        else if (fused) particles_interp_from_populations(c->pb, c->np, c->grid, c->pc, fin, c->fp16, c->sl2, c->stream);
         else particles_interp(c->D, c->pb, c->np, c->grid, c->pc, c->mom, c->stream);
     }
     q(mark(c, row, 3));
