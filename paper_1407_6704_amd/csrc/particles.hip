@@ -1078,6 +1078,7 @@ __device__ __forceinline__ bool island_touching(uint32_t a, uint32_t size, const
     for (int ax = 0; ax < D; ax++) us += A.u[ax][s] * A.u[ax][s];
     us = sqrtf(us);
     if (size == 1) {
+        if (c.contact != PIBM_CONTACT_LSD) return false;       // packed in any case (touch_plan)
         bool near = false;
 #pragma unroll
         for (int ax = 0; ax < D; ax++) {
@@ -1101,18 +1102,22 @@ __device__ __forceinline__ bool island_touching(uint32_t a, uint32_t size, const
 
 // Layout of the touching islands: `per` of them to a workgroup of the
 // sub-step kernel, in `groups` workgroups.  The sub-steps of one such island
-// are a serial chain that a wave runs no faster for holding fewer islands,
-// but several islands that bounce hold each other up (their checks and jumps
-// fall on different trips), and two busy waves slow each other on one compute
-// unit: so as thin as one workgroup per compute unit allows.  100 touching
+// are a serial chain that a wave runs no faster for holding fewer islands.
+// But islands that bounce (the spring-dashpot's restitution) hold each other
+// up in a wave, as their checks and jumps fall on different trips: they are
+// laid out as thinly as one workgroup per compute unit allows.  100 touching
 // pairs in 203 x 187 x 211 (3109 sub-steps): the sub-step kernel takes 0.55-0.7
-// ms a step, against 1.0-1.7 ms with eight pairs to a workgroup.
+// ms a step, 1.0 ms in 64 workgroups, 1.2-1.5 ms with eight pairs to a
+// workgroup.  The Hertz laws' contacts are soft and last; they run the same
+// sub-steps in any layout, and few busy compute units are clocked higher than
+// many: 20 pairs in 40 x 61 x 93 0.49 ms packed, 0.55 ms in 10 or 20 workgroups.
 struct TouchPlan {
     uint32_t per, groups;
 };
-__device__ __forceinline__ TouchPlan touch_plan(uint32_t islands, uint32_t size) {
+__device__ __forceinline__ TouchPlan touch_plan(uint32_t islands, uint32_t size, const PCfg& c) {
     TouchPlan p;
-    p.per = min(max((islands + NUM_CU - 1) / NUM_CU, 1u), 16u / size);
+    const uint32_t most = 16u / size;
+    p.per = c.contact == PIBM_CONTACT_LSD ? min(max((islands + NUM_CU - 1) / NUM_CU, 1u), most) : most;
     p.groups = (islands + p.per - 1) / p.per;
     return p;
 }
@@ -1165,7 +1170,7 @@ __global__ __launch_bounds__(256) void k_island_class(PState A, PCfg c, const ui
 
 // Lane (small islands, packed by size into waves) or slot (large islands)
 // of active particle a; wavebase[s] = first wave of size class s.
-__device__ __forceinline__ void island_place_one(uint32_t a, const uint32_t* __restrict__ parent,
+__device__ __forceinline__ void island_place_one(uint32_t a, const PCfg& c, const uint32_t* __restrict__ parent,
                                                  const uint32_t* __restrict__ isize,
                                                  const uint32_t* __restrict__ irank, uint32_t* __restrict__ fill,
                                                  int* __restrict__ lanemember, uint32_t* __restrict__ loc,
@@ -1178,7 +1183,7 @@ __device__ __forceinline__ void island_place_one(uint32_t a, const uint32_t* __r
     if (sz <= WAVE && (irank[r] & TOUCH_BIT)) {
         const uint32_t ir = irank[r] & ~TOUCH_BIT;
         lanemember[sz == 2 ? 2 * ir + pos : 2 * pairs + ir] = (int)a;
-        loc[a] = (ir % touch_plan(sz == 2 ? pairs : walls, sz).per) * sz + pos;
+        loc[a] = (ir % touch_plan(sz == 2 ? pairs : walls, sz, c).per) * sz + pos;
     } else if (sz <= WAVE) {
         uint32_t ir = irank[r];
         uint32_t per = WAVE / sz;
@@ -1195,7 +1200,7 @@ __device__ __forceinline__ void island_place_one(uint32_t a, const uint32_t* __r
 // Every block first forms the wave plan and the large-island offsets itself
 // (a few hundred loads; it saves a one-block launch); block 0 stores the
 // plan for the sub-step kernels, and every block writes the same offsets.
-__global__ __launch_bounds__(256) void k_island_place(const uint32_t* __restrict__ parent,
+__global__ __launch_bounds__(256) void k_island_place(PCfg c, const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ isize,
                                                       const uint32_t* __restrict__ irank, uint32_t* __restrict__ fill,
                                                       int* __restrict__ lanemember, uint32_t* __restrict__ loc,
@@ -1228,7 +1233,7 @@ __global__ __launch_bounds__(256) void k_island_place(const uint32_t* __restrict
     }
     const uint32_t na = counters[CNT_ACTIVE];
     for (uint32_t a = blockIdx.x * 256 + threadIdx.x; a < na; a += gridDim.x * 256)
-        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, pairs, walls);
+        island_place_one(a, c, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, pairs, walls);
 }
 
 // Candidate constants for the sub-steps.  K0 = r_c^2 - |r0|^2 is formed in
@@ -1395,7 +1400,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
     }
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
-        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, pairs, walls);
+        island_place_one(a, c, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, pairs, walls);
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
         cand_prep_one<D>(a, A, c, alist, ccount, prefix, cand, aidx, loc, cdata, md);
@@ -2579,7 +2584,7 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     __shared__ float4 smd[MD ? WAVE * CAND_LDS * MD_LDS : 1];
     const uint32_t nw = counters[CNT_WAVES];
     const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
-    const TouchPlan tp = touch_plan(pairs, 2), tw = touch_plan(walls, 1);
+    const TouchPlan tp = touch_plan(pairs, 2, c), tw = touch_plan(walls, 1, c);
     const int lane = threadIdx.x;
     // first wave of size class lane + 1 (non-decreasing in the class)
     const uint32_t wb_lane = counters[CNT_WAVEBASE + 1 + lane];
@@ -3483,7 +3488,7 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
         hipLaunchKernelGGL(k_island_class<D>, dim3(grid_act), dim3(256), 0, s, b.A, c, b.alist, b.ccount, b.prefix,
                            b.cand, b.parent, b.isize, b.irank, b.bigroot,
                            b.counters);
-        hipLaunchKernelGGL(k_island_place, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.irank, b.fill,
+        hipLaunchKernelGGL(k_island_place, dim3(grid_act), dim3(256), 0, s, c, b.parent, b.isize, b.irank, b.fill,
                            b.lanemember, b.loc, b.bigoff, b.bigmember, b.bigroot, b.counters);
         hipLaunchKernelGGL(k_cand_prep<D>, dim3(grid_act), dim3(256), 0, s, b.A, c, b.alist, b.ccount, b.prefix, b.cand,
                            b.aidx, b.loc, b.cdata, md, b.counters);
