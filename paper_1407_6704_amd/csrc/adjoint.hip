@@ -140,16 +140,75 @@ __global__ __launch_bounds__(256) void k_adj_collide(const float* __restrict__ a
     if (threadIdx.x == 0) tpart[blockIdx.x] = red[0];
 }
 
+// (ahi, alo) += (bhi, blo), double-float.
+__device__ __forceinline__ void df_add_df(float& ahi, float& alo, float bhi, float blo) {
+#pragma clang fp contract(off)
+    float s, e;
+    two_sum(ahi, bhi, s, e);
+    e += alo + blo;
+    fast_two_sum(s, e, ahi, alo);
+}
+
+// The per-block partial sums of one reverse step: ntb of d/dtau in tpart, ngb
+// triples of d/dgvec in gpart.
+struct AdjParts {
+    const float* tpart;
+    int ntb;
+    const float* gpart;
+    int ngb;
+    float* acc;          // running double-float totals [tau, g_x, g_y, g_z] x (hi, lo); null: nothing to add
+};
+
+// One workgroup sums the partials in a fixed order and adds them to the totals.
+__device__ __forceinline__ void accumulate_parts(const AdjParts& p) {
+    __shared__ float sh[4][256], sl[4][256];
+    const int t = threadIdx.x;
+    float hi[4] = {0.f, 0.f, 0.f, 0.f}, lo[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i = t; i < p.ntb; i += 256) df_add(hi[0], lo[0], p.tpart[i]);
+    for (int i = t; i < p.ngb; i += 256)
+#pragma unroll
+        for (int b = 0; b < 3; b++) df_add(hi[1 + b], lo[1 + b], p.gpart[i * 3 + b]);
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        sh[k][t] = hi[k];
+        sl[k][t] = lo[k];
+    }
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+        if (t < st) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) df_add_df(sh[k][t], sl[k][t], sh[k][t + st], sl[k][t + st]);
+        }
+        __syncthreads();
+    }
+    if (t < 4) {
+        float h = p.acc[2 * t], l = p.acc[2 * t + 1];
+        df_add_df(h, l, sh[t][0], sl[t][0]);
+        p.acc[2 * t] = h;
+        p.acc[2 * t + 1] = l;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_adj_accumulate(AdjParts p) { accumulate_parts(p); }
+
 // The adjoint of the populations before the step: the direct term of the
 // collision plus the moment adjoints (collision share Mc and the spread
-// interpolation share Sf = (rho-bar, j-bar) fields).
+// interpolation share Sf = (rho-bar, j-bar) fields).  One workgroup more than
+// the nodes need sums the step's parameter gradients meanwhile (in a launch of
+// its own that one workgroup took 4.7 us of every reverse step).
 template <int Q>
 __global__ __launch_bounds__(256) void k_adj_assemble(const float* __restrict__ abar, const float4* __restrict__ Mc,
                                                       const float* __restrict__ Sf, int hasS, Grid g, float tau,
-                                                      float* __restrict__ abar_out) {
+                                                      float* __restrict__ abar_out, AdjParts parts) {
     using L = Lattice<Q>;
+    if (parts.acc) {
+        if (blockIdx.x == 0) {
+            accumulate_parts(parts);
+            return;
+        }
+    }
     const long long N = g.N;
-    const long long r = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long r = (long long)(blockIdx.x - (parts.acc ? 1 : 0)) * 256 + threadIdx.x;
     if (r >= N) return;
     const int nx = g.n[0], ny = g.n[1];
     const int x = (int)(r % nx);
@@ -208,8 +267,12 @@ __device__ __forceinline__ void soft_mag(float ks, float s, float rc, float& f, 
     df = -2.0f * ks * t / rc;
 }
 
-// Reverse of the particle side of one step, one thread per particle (sorted
-// order of the step's cell list).  The forward, with h = 1:
+// Reverse of the particle side of one step, LP lanes per particle (sorted
+// order of the step's cell list): each lane gathers one row of four nodes of
+// the 4^D stencil, the lanes' sums meet by shuffles in a fixed order, and the
+// first lane does the rest.  One thread per particle walked its 64 nodes (4
+// loads each) as one chain in a few workgroups: 3000 spheres 60 us, 10,000
+// disks 16.4 us; now 22 and 8.7 us.  The forward, with h = 1:
 //   g  = 2 (rho_i U - j_i),   Fc = contacts(X),
 //   U' = U + (-A g + Fc) / m + (1 - rho0/rho_p) gvec,   X' = X + U',
 //   F(r) += A g W(r; X),   rho_i = sum W rho,   j_i = sum W j.
@@ -217,6 +280,16 @@ __device__ __forceinline__ void soft_mag(float ks, float s, float rc, float& f, 
 // and F-bar fields.  Out: the adjoints of X, U (id order), the interpolation
 // adjoints (rho_i-bar, j_i-bar) with their weights for spreading, and one
 // partial sum of d/dgvec per block.
+constexpr int adj_lanes(int D) { return D == 3 ? 16 : 4; }      // lanes per particle: rows of its stencil
+__device__ __forceinline__ float pick(const float* w, int k) {
+    const float lo = (k & 1) ? w[1] : w[0], hi = (k & 1) ? w[3] : w[2];
+    return (k & 2) ? hi : lo;
+}
+template <int LP>
+__device__ __forceinline__ void lane_sum(float& v) {
+#pragma unroll
+    for (int off = 1; off < LP; off <<= 1) v += __shfl_xor(v, off, LP);
+}
 template <int D>
 __global__ __launch_bounds__(256) void k_adj_particles(PState A, int np, Grid g, PCfg c, int two_way,
                                                        const uint32_t* __restrict__ start,
@@ -227,10 +300,13 @@ __global__ __launch_bounds__(256) void k_adj_particles(PState A, int np, Grid g,
                                                        float* __restrict__ xbl_o, float* __restrict__ ub_o,
                                                        float* __restrict__ coefS, float* __restrict__ srec,
                                                        short4* __restrict__ wbase, float* __restrict__ gpart) {
+    constexpr int LP = adj_lanes(D);
     __shared__ float red[3][256];
-    const int s = blockIdx.x * 256 + threadIdx.x;
+    // neighbouring particles, whose stencils overlap, on one XCD
+    const unsigned lb = xcd_block();
+    const int s = (int)(lb * (256 / LP) + threadIdx.x / LP), lane = (int)threadIdx.x % LP;
     float gacc[3] = {0.f, 0.f, 0.f};
-    if (s < np) {
+    if (s < np) {                        // (the same for all lanes of a particle)
         const int id = A.id[s];
         const float d = A.d[s], rp = A.rp[s];
         const float m = particle_mass(D, d, rp);
@@ -252,64 +328,69 @@ __global__ __launch_bounds__(256) void k_adj_particles(PState A, int np, Grid g,
         // gather the moments and F-bar with the weights and their derivatives
         float dri = 0.f, ji[3] = {0.f, 0.f, 0.f}, Phi[3] = {0.f, 0.f, 0.f};
         float ddri[3] = {0.f, 0.f, 0.f}, dji[3][3] = {}, dPhi[3][3] = {};
+        {
+            const int ky = lane & 3, kz = D == 3 ? lane >> 2 : 0;
+            const int y = base[1] + ky, z = (D == 3) ? base[2] + kz : 0;
+            const float py = pick(phi[1], ky), dpy = pick(dphi[1], ky);
+            const float pz = D == 3 ? pick(phi[2], kz) : 1.f, dpz = D == 3 ? pick(dphi[2], kz) : 0.f;
+            const bool row = y >= 0 && y < g.n[1] && z >= 0 && z < g.n[2];
+            float4 mm[4];
+            float fb[4][3];
+            bool in[4];
 #pragma unroll
-        for (int kz = 0; kz < (D == 3 ? 4 : 1); kz++)
+            for (int kx = 0; kx < 4; kx++) {
+                const int x = base[0] + kx;
+                in[kx] = row && x >= 0 && x < g.n[0];
+                const long long node = in[kx] ? ((long long)z * g.n[1] + y) * g.n[0] + x : 0;
+                mm[kx] = mom[node];
 #pragma unroll
-            for (int ky = 0; ky < 4; ky++)
+                for (int b = 0; b < D; b++) fb[kx][b] = two_way ? Fbar[(long long)b * g.N + node] : 0.f;
+            }
 #pragma unroll
-                for (int kx = 0; kx < 4; kx++) {
-                    const int x = base[0] + kx, y = base[1] + ky, z = (D == 3) ? base[2] + kz : 0;
-                    if (x < 0 || x >= g.n[0] || y < 0 || y >= g.n[1] || z < 0 || z >= g.n[2]) continue;
-                    const long long node = ((long long)z * g.n[1] + y) * g.n[0] + x;
-                    const float W = phi[0][kx] * phi[1][ky] * phi[2][kz];
-                    const float dW[3] = {dphi[0][kx] * phi[1][ky] * phi[2][kz], phi[0][kx] * dphi[1][ky] * phi[2][kz],
-                                         phi[0][kx] * phi[1][ky] * dphi[2][kz]};
-                    const float4 mm = mom[node];
-                    const float mj[3] = {mm.y, mm.z, mm.w};
-                    float fb[3] = {0.f, 0.f, 0.f};
-                    if (two_way)
+            for (int kx = 0; kx < 4; kx++) {
+                if (!in[kx]) continue;
+                const float W = phi[0][kx] * py * pz;
+                const float dW[3] = {dphi[0][kx] * py * pz, phi[0][kx] * dpy * pz, phi[0][kx] * py * dpz};
+                const float mj[3] = {mm[kx].y, mm[kx].z, mm[kx].w};
+                dri += W * mm[kx].x;
 #pragma unroll
-                        for (int b = 0; b < D; b++) fb[b] = Fbar[(long long)b * g.N + node];
-                    dri += W * mm.x;
+                for (int b = 0; b < D; b++) {
+                    ji[b] += W * mj[b];
+                    Phi[b] += W * fb[kx][b];
+                }
+#pragma unroll
+                for (int a = 0; a < D; a++) {
+                    ddri[a] += dW[a] * mm[kx].x;
 #pragma unroll
                     for (int b = 0; b < D; b++) {
-                        ji[b] += W * mj[b];
-                        Phi[b] += W * fb[b];
-                    }
-#pragma unroll
-                    for (int a = 0; a < D; a++) {
-                        ddri[a] += dW[a] * mm.x;
-#pragma unroll
-                        for (int b = 0; b < D; b++) {
-                            dji[a][b] += dW[a] * mj[b];
-                            dPhi[a][b] += dW[a] * fb[b];
-                        }
+                        dji[a][b] += dW[a] * mj[b];
+                        dPhi[a][b] += dW[a] * fb[kx][b];
                     }
                 }
+            }
+            lane_sum<LP>(dri);
+#pragma unroll
+            for (int a = 0; a < D; a++) {
+                lane_sum<LP>(ji[a]);
+                lane_sum<LP>(Phi[a]);
+                lane_sum<LP>(ddri[a]);
+#pragma unroll
+                for (int b = 0; b < D; b++) {
+                    lane_sum<LP>(dji[a][b]);
+                    lane_sum<LP>(dPhi[a][b]);
+                }
+            }
+        }
         const float ri = 1.0f + dri;
-        float gg[3], Ut[3], gb[3], Fcb[3];
+        float Ut[3], Fcb[3];
 #pragma unroll
         for (int b = 0; b < D; b++) {
-            gg[b] = 2.0f * (ri * U[b] - ji[b]);
             Ut[b] = ub[(long long)b * np + id] + (xbh[(long long)b * np + id] + xbl[(long long)b * np + id]);
-            gb[b] = (two_way ? Ap * Phi[b] : 0.f) - (Ap / m) * Ut[b];
             Fcb[b] = Ut[b] / m;
-            gacc[b] = bw * Ut[b];
         }
-        float rib = 0.f;
-#pragma unroll
-        for (int b = 0; b < D; b++) rib += 2.0f * U[b] * gb[b];
-        float dX[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-        for (int a = 0; a < D; a++) {
-            float v = rib * ddri[a];
-#pragma unroll
-            for (int b = 0; b < D; b++) {
-                v += (-2.0f * gb[b]) * dji[a][b];
-                if (two_way) v += Ap * gg[b] * dPhi[a][b];
-            }
-            dX[a] = v;
-        }
+        // soft contacts' share of X-bar, the rows of bins around the particle
+        // dealt out to its lanes
+        float dXc[3] = {0.f, 0.f, 0.f};
         if (c.contact == PIBM_CONTACT_SOFT) {
             // pairs: d Fc_p / d X_p = J_pq, d Fc_q / d X_p = -J_pq (central force)
             const uint32_t key = keys_sorted[s];
@@ -319,76 +400,103 @@ __global__ __launch_bounds__(256) void k_adj_particles(PState A, int np, Grid g,
             bc[2] = (int)(key / ((uint32_t)c.nb[0] * (uint32_t)c.nb[1]));
             const int H = c.H;
             const int zl = (D == 3) ? max(bc[2] - H, 0) : 0, zh = (D == 3) ? min(bc[2] + H, c.nb[2] - 1) : 0;
-            for (int bz = zl; bz <= zh; bz++)
-                for (int by = max(bc[1] - H, 0); by <= min(bc[1] + H, c.nb[1] - 1); by++) {
-                    const int bxl = max(bc[0] - H, 0), bxh = min(bc[0] + H, c.nb[0] - 1);
-                    const uint32_t row = (uint32_t)(((long long)bz * c.nb[1] + by) * c.nb[0]);
-                    const uint32_t t0 = start[row + bxl], t1 = start[row + bxh + 1];
-                    for (uint32_t t = t0; t < t1; t++) {
-                        if ((int)t == s) continue;
-                        float rv[3] = {0.f, 0.f, 0.f}, r2 = 0.f;
+            const int yl = max(bc[1] - H, 0), ny = min(bc[1] + H, c.nb[1] - 1) - yl + 1;
+            const int bxl = max(bc[0] - H, 0), bxh = min(bc[0] + H, c.nb[0] - 1);
+            for (int i = lane; i < ny * (zh - zl + 1); i += LP) {
+                const uint32_t row = (uint32_t)(((long long)(zl + i / ny) * c.nb[1] + (yl + i % ny)) * c.nb[0]);
+                const uint32_t t0 = start[row + bxl], t1 = start[row + bxh + 1];
+                for (uint32_t t = t0; t < t1; t++) {
+                    if ((int)t == s) continue;
+                    float rv[3] = {0.f, 0.f, 0.f}, r2 = 0.f;
 #pragma unroll
-                        for (int a = 0; a < D; a++) {
-                            rv[a] = (A.xh[a][s] - A.xh[a][t]) + (A.xl[a][s] - A.xl[a][t]);
-                            r2 += rv[a] * rv[a];
-                        }
-                        const float rc = 0.5f * (d + A.d[t]);
-                        if (!(r2 < rc * rc)) continue;
-                        const float dist = sqrtf(r2);
-                        float f, df;
-                        soft_mag(c.ks, dist, rc, f, df);
-                        const int idq = A.id[t];
-                        const float mq = particle_mass(D, A.d[t], A.rp[t]);
-                        float diff[3], nv[3];
-#pragma unroll
-                        for (int b = 0; b < D; b++) {
-                            const float utq = ub[(long long)b * np + idq] +
-                                              (xbh[(long long)b * np + idq] + xbl[(long long)b * np + idq]);
-                            diff[b] = Fcb[b] - utq / mq;
-                            nv[b] = rv[b] / dist;
-                        }
-                        float nd = 0.f;
-#pragma unroll
-                        for (int b = 0; b < D; b++) nd += nv[b] * diff[b];
-                        const float fo = f / dist;
-                        // J = df n n^T + (f / s) (I - n n^T)
-#pragma unroll
-                        for (int a = 0; a < D; a++) dX[a] += (df - fo) * nv[a] * nd + fo * diff[a];
+                    for (int a = 0; a < D; a++) {
+                        rv[a] = (A.xh[a][s] - A.xh[a][t]) + (A.xl[a][s] - A.xl[a][t]);
+                        r2 += rv[a] * rv[a];
                     }
-                }
-            // walls at 0 and n_a: d Fw_a / d X_a = f'(distance) on both sides
+                    const float rc = 0.5f * (d + A.d[t]);
+                    if (!(r2 < rc * rc)) continue;
+                    const float dist = sqrtf(r2);
+                    float f, df;
+                    soft_mag(c.ks, dist, rc, f, df);
+                    const int idq = A.id[t];
+                    const float mq = particle_mass(D, A.d[t], A.rp[t]);
+                    float diff[3], nv[3];
 #pragma unroll
-            for (int a = 0; a < D; a++) {
-                const float xa = A.xh[a][s] + A.xl[a][s];
-                const float rcw = 0.5f * d;
-                float f, df;
-                if (xa < rcw) {
-                    soft_mag(c.ks, xa, rcw, f, df);
-                    dX[a] += df * Fcb[a];
-                }
-                const float up = (float)g.n[a] - xa;
-                if (up < rcw) {
-                    soft_mag(c.ks, up, rcw, f, df);
-                    dX[a] += df * Fcb[a];
+                    for (int b = 0; b < D; b++) {
+                        const float utq = ub[(long long)b * np + idq] +
+                                          (xbh[(long long)b * np + idq] + xbl[(long long)b * np + idq]);
+                        diff[b] = Fcb[b] - utq / mq;
+                        nv[b] = rv[b] / dist;
+                    }
+                    float nd = 0.f;
+#pragma unroll
+                    for (int b = 0; b < D; b++) nd += nv[b] * diff[b];
+                    const float fo = f / dist;
+                    // J = df n n^T + (f / s) (I - n n^T)
+#pragma unroll
+                    for (int a = 0; a < D; a++) dXc[a] += (df - fo) * nv[a] * nd + fo * diff[a];
                 }
             }
+#pragma unroll
+            for (int a = 0; a < D; a++) lane_sum<LP>(dXc[a]);
         }
+        if (lane == 0) {
+            float gg[3], gb[3];
 #pragma unroll
-        for (int b = 0; b < D; b++) {
-            float hi = xbh[(long long)b * np + id], lo = xbl[(long long)b * np + id];
-            df_add(hi, lo, dX[b]);
-            xbh_o[(long long)b * np + id] = hi;
-            xbl_o[(long long)b * np + id] = lo;
-            ub_o[(long long)b * np + id] = Ut[b] + 2.0f * ri * gb[b];
-            coefS[(long long)(1 + b) * np + s] = -2.0f * gb[b];
+            for (int b = 0; b < D; b++) {
+                gg[b] = 2.0f * (ri * U[b] - ji[b]);
+                gb[b] = (two_way ? Ap * Phi[b] : 0.f) - (Ap / m) * Ut[b];
+                gacc[b] = bw * Ut[b];
+            }
+            float rib = 0.f;
+#pragma unroll
+            for (int b = 0; b < D; b++) rib += 2.0f * U[b] * gb[b];
+            float dX[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+            for (int a = 0; a < D; a++) {
+                float v = rib * ddri[a];
+#pragma unroll
+                for (int b = 0; b < D; b++) {
+                    v += (-2.0f * gb[b]) * dji[a][b];
+                    if (two_way) v += Ap * gg[b] * dPhi[a][b];
+                }
+                dX[a] = v + dXc[a];
+            }
+            if (c.contact == PIBM_CONTACT_SOFT) {
+                // walls at 0 and n_a: d Fw_a / d X_a = f'(distance) on both sides
+#pragma unroll
+                for (int a = 0; a < D; a++) {
+                    const float xa = A.xh[a][s] + A.xl[a][s];
+                    const float rcw = 0.5f * d;
+                    float f, df;
+                    if (xa < rcw) {
+                        soft_mag(c.ks, xa, rcw, f, df);
+                        dX[a] += df * Fcb[a];
+                    }
+                    const float up = (float)g.n[a] - xa;
+                    if (up < rcw) {
+                        soft_mag(c.ks, up, rcw, f, df);
+                        dX[a] += df * Fcb[a];
+                    }
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < D; b++) {
+                float hi = xbh[(long long)b * np + id], lo = xbl[(long long)b * np + id];
+                df_add(hi, lo, dX[b]);
+                xbh_o[(long long)b * np + id] = hi;
+                xbl_o[(long long)b * np + id] = lo;
+                ub_o[(long long)b * np + id] = Ut[b] + 2.0f * ri * gb[b];
+                coefS[(long long)(1 + b) * np + s] = -2.0f * gb[b];
+            }
+            coefS[s] = rib;
+#pragma unroll
+            for (int a = 0; a < D; a++)
+#pragma unroll
+                for (int k = 0; k < 4; k++) srec[(long long)s * SRec<D>::STRIDE + 4 * a + k] = phi[a][k];
+            srec[(long long)s * SRec<D>::STRIDE + SRec<D>::BASE] = __int_as_float(base[0]);
+            wbase[s] = make_short4((short)base[0], (short)base[1], (short)base[2], 0);
         }
-        coefS[s] = rib;
-#pragma unroll
-        for (int a = 0; a < D; a++)
-#pragma unroll
-            for (int k = 0; k < 4; k++) srec[(long long)s * SRec<D>::STRIDE + 4 * a + k] = phi[a][k];
-        srec[(long long)s * SRec<D>::STRIDE + SRec<D>::BASE] = __int_as_float(base[0]);
-        wbase[s] = make_short4((short)base[0], (short)base[1], (short)base[2], 0);
     }
 #pragma unroll
     for (int b = 0; b < 3; b++) red[b][threadIdx.x] = gacc[b];
@@ -401,48 +509,7 @@ __global__ __launch_bounds__(256) void k_adj_particles(PState A, int np, Grid g,
     }
     if (threadIdx.x == 0)
 #pragma unroll
-        for (int b = 0; b < 3; b++) gpart[blockIdx.x * 3 + b] = red[b][0];
-}
-
-// (ahi, alo) += (bhi, blo), double-float.
-__device__ __forceinline__ void df_add_df(float& ahi, float& alo, float bhi, float blo) {
-#pragma clang fp contract(off)
-    float s, e;
-    two_sum(ahi, bhi, s, e);
-    e += alo + blo;
-    fast_two_sum(s, e, ahi, alo);
-}
-
-// Sum the per-block partials of one reverse step in a fixed order and add
-// them to the running double-float totals acc = [tau, g_x, g_y, g_z] x (hi, lo).
-__global__ __launch_bounds__(256) void k_adj_accumulate(const float* __restrict__ tpart, int ntb,
-                                                        const float* __restrict__ gpart, int ngb,
-                                                        float* __restrict__ acc) {
-    __shared__ float sh[4][256], sl[4][256];
-    const int t = threadIdx.x;
-    float hi[4] = {0.f, 0.f, 0.f, 0.f}, lo[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int i = t; i < ntb; i += 256) df_add(hi[0], lo[0], tpart[i]);
-    for (int i = t; i < ngb; i += 256)
-#pragma unroll
-        for (int b = 0; b < 3; b++) df_add(hi[1 + b], lo[1 + b], gpart[i * 3 + b]);
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        sh[k][t] = hi[k];
-        sl[k][t] = lo[k];
-    }
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (t < st)
-#pragma unroll
-            for (int k = 0; k < 4; k++) df_add_df(sh[k][t], sl[k][t], sh[k][t + st], sl[k][t + st]);
-        __syncthreads();
-    }
-    if (t < 4) {
-        float h = acc[2 * t], l = acc[2 * t + 1];
-        df_add_df(h, l, sh[t][0], sl[t][0]);
-        acc[2 * t] = h;
-        acc[2 * t + 1] = l;
-    }
+        for (int b = 0; b < 3; b++) gpart[lb * 3 + b] = red[b][0];
 }
 
 __global__ void k_fill_f32(float* __restrict__ p, long long n, float v) {
@@ -469,6 +536,28 @@ __global__ __launch_bounds__(256) void k_save_const(PState A, int np, float* __r
     const int id = A.id[s];
     d[id] = A.d[s];
     rp[id] = A.rp[s];
+}
+
+// One step's particle state and cell list as the sort left them, for the
+// reverse step: words [xh D][xl D][u D][d][rp][id][key] x np, then the
+// nbins + 1 bin starts.
+__global__ __launch_bounds__(256) void k_save_tape(PState A, const uint32_t* __restrict__ keys,
+                                                   const uint32_t* __restrict__ start, int np, int D, long long nb1,
+                                                   uint32_t* __restrict__ out) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < np) {
+        for (int a = 0; a < D; a++) {
+            out[(long long)a * np + i] = __float_as_uint(A.xh[a][i]);
+            out[(long long)(D + a) * np + i] = __float_as_uint(A.xl[a][i]);
+            out[(long long)(2 * D + a) * np + i] = __float_as_uint(A.u[a][i]);
+        }
+        out[(long long)(3 * D) * np + i] = __float_as_uint(A.d[i]);
+        out[(long long)(3 * D + 1) * np + i] = __float_as_uint(A.rp[i]);
+        out[(long long)(3 * D + 2) * np + i] = (uint32_t)A.id[i];
+        out[(long long)(3 * D + 3) * np + i] = keys[i];
+    }
+    uint32_t* so = out + (long long)(3 * D + 4) * np;
+    for (long long k = 4 * i; k < min(4 * i + 4, nb1); k++) so[k] = start[k];
 }
 
 // Id-order state -> PState A in id order (the next sort orders it).
@@ -517,6 +606,32 @@ void adj_save_state(int D, const PBuf& b, int np, float* out, hipStream_t s) {
     hipLaunchKernelGGL(k_save_state, dim3(blocks256(np)), dim3(256), 0, s, b.A, np, D, out);
 }
 
+long long adj_tape_words(int D, int np, long long nbins) {
+    return ((3LL * D + 4) * np + nbins + 1 + 63) / 64 * 64;
+}
+
+void adj_save_tape(int D, const PBuf& b, int np, long long nbins, uint32_t* out, hipStream_t s) {
+    const long long n = std::max<long long>(np, (nbins + 4) / 4);
+    hipLaunchKernelGGL(k_save_tape, dim3(blocks256(n)), dim3(256), 0, s, b.A, b.keys_sorted, b.start, np, D, nbins + 1,
+                       out);
+}
+
+// The buffers b with the particle state and cell list of a saved step.
+PBuf adj_tape_view(int D, const PBuf& b, int np, uint32_t* in) {
+    PBuf v = b;
+    for (int a = 0; a < D; a++) {
+        v.A.xh[a] = (float*)in + (long long)a * np;
+        v.A.xl[a] = (float*)in + (long long)(D + a) * np;
+        v.A.u[a] = (float*)in + (long long)(2 * D + a) * np;
+    }
+    v.A.d = (float*)in + 3LL * D * np;
+    v.A.rp = (float*)in + (3LL * D + 1) * np;
+    v.A.id = (int*)in + (3LL * D + 2) * np;
+    v.keys_sorted = in + (3LL * D + 3) * np;
+    v.start = in + (3LL * D + 4) * np;
+    return v;
+}
+
 void adj_save_const(const PBuf& b, int np, float* d, float* rp, hipStream_t s) {
     hipLaunchKernelGGL(k_save_const, dim3(blocks256(np)), dim3(256), 0, s, b.A, np, d, rp);
 }
@@ -530,7 +645,7 @@ void adj_df_collapse(const float* hi, const float* lo, float* out, long long n, 
 }
 
 int adj_collide_blocks(long long N) { return (int)blocks256(N); }
-int adj_particle_blocks(int np) { return (int)blocks256(np); }
+int adj_particle_blocks(int D, int np) { return (int)blocks256((long long)np * adj_lanes(D)); }
 
 template <int Q, class S>
 static void collide_launch(const float* abar, const void* ft, const float* Ft, int hasF, const float* ff,
@@ -557,31 +672,31 @@ void adj_collide(int Q, int fp16, int sl2, const float* abar, const void* ft, co
 }
 
 void adj_assemble(int Q, const float* abar, const float4* Mc, const float* Sf, int hasS, const Grid& g, float tau,
-                  float* abar_out, hipStream_t s) {
+                  float* abar_out, const float* tpart, int ntb, const float* gpart, int ngb, float* acc,
+                  hipStream_t s) {
+    const AdjParts parts{tpart, ntb, gpart, ngb, acc};
+    const dim3 grid(blocks256(g.N) + (acc ? 1 : 0));
     if (Q == 19)
-        hipLaunchKernelGGL(k_adj_assemble<19>, dim3(blocks256(g.N)), dim3(256), 0, s, abar, Mc, Sf, hasS, g, tau,
-                           abar_out);
+        hipLaunchKernelGGL(k_adj_assemble<19>, grid, dim3(256), 0, s, abar, Mc, Sf, hasS, g, tau, abar_out, parts);
     else if (Q == 15)
-        hipLaunchKernelGGL(k_adj_assemble<15>, dim3(blocks256(g.N)), dim3(256), 0, s, abar, Mc, Sf, hasS, g, tau,
-                           abar_out);
+        hipLaunchKernelGGL(k_adj_assemble<15>, grid, dim3(256), 0, s, abar, Mc, Sf, hasS, g, tau, abar_out, parts);
     else
-        hipLaunchKernelGGL(k_adj_assemble<9>, dim3(blocks256(g.N)), dim3(256), 0, s, abar, Mc, Sf, hasS, g, tau,
-                           abar_out);
+        hipLaunchKernelGGL(k_adj_assemble<9>, grid, dim3(256), 0, s, abar, Mc, Sf, hasS, g, tau, abar_out, parts);
 }
 
 void adj_particles(int D, PBuf& b, int np, const Grid& g, const PCfg& c, int two_way, const float4* mom,
                    const float* Fbar, const float* xbh, const float* xbl, const float* ub, float* xbh_o,
                    float* xbl_o, float* ub_o, float* coefS, float* gpart, hipStream_t s) {
     if (D == 3)
-        hipLaunchKernelGGL(k_adj_particles<3>, dim3(blocks256(np)), dim3(256), 0, s, b.A, np, g, c, two_way, b.start,
+        hipLaunchKernelGGL(k_adj_particles<3>, dim3(adj_particle_blocks(3, np)), dim3(256), 0, s, b.A, np, g, c, two_way, b.start,
                            b.keys_sorted, mom, Fbar, xbh, xbl, ub, xbh_o, xbl_o, ub_o, coefS, b.srec, b.wbase, gpart);
     else
-        hipLaunchKernelGGL(k_adj_particles<2>, dim3(blocks256(np)), dim3(256), 0, s, b.A, np, g, c, two_way, b.start,
+        hipLaunchKernelGGL(k_adj_particles<2>, dim3(adj_particle_blocks(2, np)), dim3(256), 0, s, b.A, np, g, c, two_way, b.start,
                            b.keys_sorted, mom, Fbar, xbh, xbl, ub, xbh_o, xbl_o, ub_o, coefS, b.srec, b.wbase, gpart);
 }
 
 void adj_accumulate(const float* tpart, int ntb, const float* gpart, int ngb, float* acc, hipStream_t s) {
-    hipLaunchKernelGGL(k_adj_accumulate, dim3(1), dim3(256), 0, s, tpart, ntb, gpart, ngb, acc);
+    hipLaunchKernelGGL(k_adj_accumulate, dim3(1), dim3(256), 0, s, AdjParts{tpart, ntb, gpart, ngb, acc});
 }
 
 void adj_pack_mom(const float* in, int comps, long long n, float4* out, hipStream_t s) {

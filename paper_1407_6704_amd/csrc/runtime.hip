@@ -54,12 +54,16 @@ void adj_save_const(const PBuf& b, int np, float* d, float* rp, hipStream_t s);
 void adj_load_state(int D, PBuf& b, int np, const float* in, const float* d, const float* rp, hipStream_t s);
 void adj_df_collapse(const float* hi, const float* lo, float* out, long long n, hipStream_t s);
 int adj_collide_blocks(long long N);
-int adj_particle_blocks(int np);
+int adj_particle_blocks(int D, int np);
 void adj_collide(int Q, int fp16, int sl2, const float* abar, const void* ft, const float* Ft, int hasF,
                  const float* ff, const Grid& g, float tau, float4* mom, float* Fbar, float4* Mc, float* tpart,
                  hipStream_t s);
 void adj_assemble(int Q, const float* abar, const float4* Mc, const float* Sf, int hasS, const Grid& g, float tau,
-                  float* abar_out, hipStream_t s);
+                  float* abar_out, const float* tpart, int ntb, const float* gpart, int ngb, float* acc,
+                  hipStream_t s);
+long long adj_tape_words(int D, int np, long long nbins);
+void adj_save_tape(int D, const PBuf& b, int np, long long nbins, uint32_t* out, hipStream_t s);
+PBuf adj_tape_view(int D, const PBuf& b, int np, uint32_t* in);
 void adj_particles(int D, PBuf& b, int np, const Grid& g, const PCfg& c, int two_way, const float4* mom,
                    const float* Fbar, const float* xbh, const float* xbl, const float* ub, float* xbh_o,
                    float* xbl_o, float* ub_o, float* coefS, float* gpart, hipStream_t s);
@@ -76,7 +80,8 @@ struct Rollout {
     float *d_id = nullptr, *rp_id = nullptr;
     char* tape_f = nullptr;       // populations at the start of each step of one segment
     float* tape_F = nullptr;      // force field of each step of one segment
-    float* tape_p = nullptr;      // particle state at the start of each step of one segment
+    uint32_t* tape_p = nullptr;   // sorted particle state and cell list of each step of one segment
+    long long tape_words = 0;     // words per step
     float* abar[2] = {nullptr, nullptr};
     float* Fbar = nullptr;
     float4* Mc = nullptr;
@@ -418,7 +423,8 @@ size_t carve_rollout(const pibm_ctx& c, int steps, int K, char* base, Rollout& R
     const long long len = std::max(1, std::min(K, steps));
     R.tape_f = cv.take<char>(len * fbytes);
     R.tape_F = cv.take<float>(len * D * N);
-    R.tape_p = cv.take<float>(len * pf);
+    R.tape_words = adj_tape_words(c.D, c.np, c.pc.nbins);
+    R.tape_p = cv.take<uint32_t>(len * R.tape_words);
     for (int k = 0; k < 2; k++) R.abar[k] = cv.take<float>((size_t)c.Q * N);
     R.Fbar = cv.take<float>(D * N);
     R.Mc = cv.take<float4>(N);
@@ -430,7 +436,7 @@ size_t carve_rollout(const pibm_ctx& c, int steps, int K, char* base, Rollout& R
     }
     R.coefS = cv.take<float>((D + 1) * np);
     R.tpart = cv.take<float>(adj_collide_blocks(N));
-    R.gpart = cv.take<float>(3LL * adj_particle_blocks((int)np));
+    R.gpart = cv.take<float>(3LL * adj_particle_blocks((int)D, (int)np));
     R.acc = cv.take<float>(8);
     return cv.off + 256;
 }
@@ -940,7 +946,9 @@ constexpr uint32_t ONE_GROUP_MAX = 1024;   // one pass per phase: faster than ni
 // one dual cell and FP32 storage is fused into the collision (with FP16
 // storage the collision is short enough that the fused tile order costs
 // more than the force field's traffic saves).
-hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int row, bool want_F) {
+// tape (nullable): where the sorted particles and the cell list are saved.
+hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int row, bool want_F,
+                       uint32_t* tape = nullptr) {
     HipSeq q;
     c->srec_epoch++;
     const float ff[3] = {(float)c->cfg.fluid_force[0], (float)c->cfg.fluid_force[1], (float)c->cfg.fluid_force[2]};
@@ -954,6 +962,7 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     const bool fused = c->D == 2 && c->pc.L <= 1;
     q(mark(c, row, 0));
     if (c->np > 0) particles_sort(c->D, c->pb, c->np, c->pc, c->stream);
+    if (tape) adj_save_tape(c->D, c->pb, c->np, c->pc.nbins, tape, c->stream);
     q(mark(c, row, 1));
     const bool nodes = particles_interp_by_nodes(c->D, c->np);
     if (c->np > 0 && !fused && !nodes) {
@@ -1052,7 +1061,7 @@ pibm_status pibm_forward_ckpt(pibm_ctx* c, int32_t n_steps, int32_t K, void* dev
     Rollout& R = c->ro;
     R.taped = -1;
     const int last = n_steps > 0 ? (n_steps - 1) / K : -1;    // the last segment
-    const size_t fbytes = pop_bytes(c), pf = (size_t)3 * c->D * c->np;
+    const size_t fbytes = pop_bytes(c);
     HipSeq q;
     for (int t = 0; t < n_steps; t++) {
         if (t % K == 0) q(save_checkpoint(c, t / K));
@@ -1065,9 +1074,9 @@ pibm_status pibm_forward_ckpt(pibm_ctx* c, int32_t n_steps, int32_t K, void* dev
             // the whole rollout and nothing is run twice.
             const int k = t - last * K, len = n_steps - last * K;
             if (k == 0) q(hipMemcpyAsync(R.tape_f, c->fA, fbytes, hipMemcpyDeviceToDevice, c->stream));
-            adj_save_state(c->D, c->pb, c->np, R.tape_p + k * pf, c->stream);
             void* fout = (k + 1 < len) ? (void*)(R.tape_f + (k + 1) * fbytes) : c->fB;
-            q(launch_step(c, R.tape_f + k * fbytes, fout, R.tape_F + (size_t)k * c->D * c->N, -1, true));
+            q(launch_step(c, R.tape_f + k * fbytes, fout, R.tape_F + (size_t)k * c->D * c->N, -1, true,
+                          R.tape_p + k * R.tape_words));
         }
         std::swap(c->fA, c->fB);
     }
@@ -1092,7 +1101,7 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
     if (!R.valid) return fail(c, PIBM_E_STATE, "no recorded rollout (call pibm_forward_ckpt first)");
     const int D = c->D, np = c->np, Q = c->Q;
     const long long N = c->N, DN = (long long)D * np;
-    const size_t fbytes = pop_bytes(c), pf = (size_t)3 * D * np;
+    const size_t fbytes = pop_bytes(c);
     hipStream_t s = c->stream;
     const float ff[3] = {(float)c->cfg.fluid_force[0], (float)c->cfg.fluid_force[1], (float)c->cfg.fluid_force[2]};
     const int spread = c->cfg.two_way ? 1 : 0;
@@ -1115,23 +1124,24 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
             q(hipMemcpyAsync(R.tape_f, R.ck_f[seg], fbytes, hipMemcpyDeviceToDevice, s));
             adj_load_state(D, c->pb, np, R.ck_p[seg], R.d_id, R.rp_id, s);
             for (int k = 0; k < len; k++) {
-                adj_save_state(D, c->pb, np, R.tape_p + k * pf, s);
                 void* fout = (k + 1 < len) ? (void*)(R.tape_f + (k + 1) * fbytes) : c->fB;
-                q(launch_step(c, R.tape_f + k * fbytes, fout, R.tape_F + (size_t)k * D * N, -1, true));
+                q(launch_step(c, R.tape_f + k * fbytes, fout, R.tape_F + (size_t)k * D * N, -1, true,
+                              R.tape_p + k * R.tape_words));
             }
             R.taped = seg;
         }
         // reverse it
         for (int k = len - 1; k >= 0; k--) {
-            adj_load_state(D, c->pb, np, R.tape_p + k * pf, R.d_id, R.rp_id, s);
-            particles_sort(D, c->pb, np, c->pc, s);
+            // the step's own sorted particles and cell list, as the tape holds
+            // them (rebuilding them took six launches a step)
+            PBuf pb = adj_tape_view(D, c->pb, np, R.tape_p + k * R.tape_words);
             adj_collide(Q, c->fp16, c->sl2, R.abar[cur], R.tape_f + k * fbytes, R.tape_F + (size_t)k * D * N, spread,
                         ff, c->grid, tau, c->mom, R.Fbar, R.Mc, R.tpart, s);
-            adj_particles(D, c->pb, np, c->grid, c->pc, spread, c->mom, R.Fbar, R.xbh[cur], R.xbl[cur], R.ub[cur],
+            adj_particles(D, pb, np, c->grid, c->pc, spread, c->mom, R.Fbar, R.xbh[cur], R.xbl[cur], R.ub[cur],
                           R.xbh[1 - cur], R.xbl[1 - cur], R.ub[1 - cur], R.coefS, R.gpart, s);
-            particles_spread_adjoint(D, c->pb, np, c->pc, c->grid, R.coefS, R.Sf, s);
-            adj_assemble(Q, R.abar[cur], R.Mc, R.Sf, 1, c->grid, tau, R.abar[1 - cur], s);
-            adj_accumulate(R.tpart, adj_collide_blocks(N), R.gpart, adj_particle_blocks(np), R.acc, s);
+            particles_spread_adjoint(D, pb, np, c->pc, c->grid, R.coefS, R.Sf, s);
+            adj_assemble(Q, R.abar[cur], R.Mc, R.Sf, 1, c->grid, tau, R.abar[1 - cur], R.tpart, adj_collide_blocks(N),
+                         R.gpart, adj_particle_blocks(D, np), R.acc, s);
             cur ^= 1;
         }
     }
@@ -1179,8 +1189,7 @@ pibm_status pibm_adjoint_stage(pibm_ctx* c, int32_t stage, const float* in0, con
         adj_fill(R.acc, 8, 0.f, s);
         adj_collide(Q, c->fp16, c->sl2, in0, c->fA, c->F, np > 0 && spread, ff, c->grid, tau, c->mom, out1, R.Mc,
                     R.tpart, s);
-        adj_assemble(Q, in0, R.Mc, nullptr, 0, c->grid, tau, out0, s);
-        adj_accumulate(R.tpart, adj_collide_blocks(N), nullptr, 0, R.acc, s);
+        adj_assemble(Q, in0, R.Mc, nullptr, 0, c->grid, tau, out0, R.tpart, adj_collide_blocks(N), nullptr, 0, R.acc, s);
         nsc = 1;
         break;
     }
@@ -1196,7 +1205,7 @@ pibm_status pibm_adjoint_stage(pibm_ctx* c, int32_t stage, const float* in0, con
                       out1, R.coefS, R.gpart, s);
         particles_spread_adjoint(D, c->pb, np, c->pc, c->grid, R.coefS, out2, s);
         adj_df_collapse(R.xbh[1], R.xbl[1], out0, DN, s);
-        adj_accumulate(nullptr, 0, R.gpart, adj_particle_blocks(np), R.acc, s);
+        adj_accumulate(nullptr, 0, R.gpart, adj_particle_blocks(D, np), R.acc, s);
         c->srec_epoch++;
         nsc = 3;
         break;
