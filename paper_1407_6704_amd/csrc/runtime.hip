@@ -28,7 +28,7 @@ int lattice_totals_blocks();
 void lattice_totals(int Q, int fp16, int sl2, const void* f, long long N, double* part, double* out,
                     hipStream_t s);
 long long scan_blocks(long long n);
-void particles_sort(int D, PBuf& b, int np, const PCfg& c, hipStream_t s);
+void particles_sort(int D, PBuf& b, int np, const PCfg& c, bool unordered, hipStream_t s);
 void particles_interp(int D, PBuf& b, int np, const Grid& g, const PCfg& c, const float4* mom, hipStream_t s);
 void particles_unpermute_spin(int D, PBuf& b, int np, float* out, hipStream_t s);
 bool particles_interp_by_nodes(int D, int np);
@@ -42,7 +42,7 @@ void particles_spread_collide(int Q, int fp16, int sl2, const PBuf& b, int np, c
                               const void* fin, void* fout, const float* ff, float tau, hipStream_t s);
 int particles_totals_blocks();
 void particles_totals(int D, PBuf& b, int np, double* part, double* out, hipStream_t s);
-void particles_unpermute(int D, PBuf& b, int np, bool have_forces, float* out, hipStream_t s);
+void particles_unpermute(int D, PBuf& b, int np, bool have_forces, float* const* out, hipStream_t s);
 void particles_set_state(int D, PBuf& b, int np, const Grid& g, const float* xh, const float* xl, const float* v,
                          const float* d, const float* rp, float dmax, hipStream_t s);
 void lattice_add_const(const float* in, float* out, long long N, int D, const float* c, hipStream_t s);
@@ -114,6 +114,9 @@ struct pibm_ctx {
     Rollout ro{};
     bool particles_set = false;
     bool stepped = false;
+    // the particle state has not been sorted since it was handed over or
+    // loaded from a checkpoint (id order)
+    bool unordered = true;
     // the spreading records change with every step, particle hand-over and
     // particle adjoint stage; PIBM_STAGE_INTERP_T needs those of the last
     // PIBM_STAGE_INTERP
@@ -470,11 +473,26 @@ hipError_t clear_spin_history(pibm_ctx* c) {
 
 // The force field of the last step in F, spread again from the records the
 // step left (the same sums in the same order: bitwise the field the fused
-// collision used).  Before anything that rewrites the records.
+// collision used).  Before anything that rewrites the records or the cell
+// list but a step, which leaves a force field of its own (newly set particles
+// leave both as they are).
 void ensure_force(pibm_ctx* c) {
     if (!c->F_stale) return;
     particles_spread(c->D, c->pb, c->np, c->pc, c->grid, c->F, c->stream);
     c->F_stale = false;
+}
+
+void sort_particles(pibm_ctx* c) {
+    particles_sort(c->D, c->pb, c->np, c->pc, c->unordered, c->stream);
+    c->unordered = false;
+}
+
+// The particle state in id order in the staging area, laid out as
+// [x_hi D][x_lo D][v D][f_hydro D][f_contact D] x np.
+void unpermute_to_stage(pibm_ctx* c) {
+    float* out[5];
+    for (int k = 0; k < 5; k++) out[k] = c->stage + (size_t)k * c->D * c->np;
+    particles_unpermute(c->D, c->pb, c->np, c->stepped, out, c->stream);
 }
 
 pibm_status sync_and_flags(pibm_ctx* c) {
@@ -643,7 +661,6 @@ pibm_status pibm_read_populations(pibm_ctx* c, float* h) {
 pibm_status pibm_set_particles(pibm_ctx* c, const double* x, const double* v, const double* d,
                                const double* rho_p) {
     if (!c) return PIBM_E_ARG;
-    ensure_force(c);
     if (c->np == 0) {
         c->particles_set = true;
         c->srec_epoch++;
@@ -693,6 +710,7 @@ pibm_status pibm_set_particles(pibm_ctx* c, const double* x, const double* v, co
     c->body_of.assign(np, -1);
     set_stencil(*c, dmax);
     c->particles_set = true;
+    c->unordered = true;
     c->srec_epoch++;
     c->stepped = false;
     c->device_input_unchecked = false;
@@ -702,7 +720,6 @@ pibm_status pibm_set_particles(pibm_ctx* c, const double* x, const double* v, co
 pibm_status pibm_set_particles_device(pibm_ctx* c, const float* x_hi, const float* x_lo, const float* v,
                                       const float* d, const float* rho_p, double d_max) {
     if (!c) return PIBM_E_ARG;
-    ensure_force(c);
     if (c->np == 0) {
         c->particles_set = true;
         c->srec_epoch++;
@@ -718,6 +735,7 @@ pibm_status pibm_set_particles_device(pibm_ctx* c, const float* x_hi, const floa
     c->body_of.assign(c->np, -1);
     set_stencil(*c, (double)dmax);
     c->particles_set = true;
+    c->unordered = true;
     c->srec_epoch++;
     c->stepped = false;
     c->device_input_unchecked = true;
@@ -781,7 +799,7 @@ pibm_status pibm_read_bodies(pibm_ctx* c, int32_t n_bodies, double* f_hydro, dou
     if (c->np == 0 || n_bodies == 0) return PIBM_OK;
     if (!c->particles_set) return fail(c, PIBM_E_STATE, "particles not set");
     const int D = c->D, np = c->np;
-    particles_unpermute(D, c->pb, np, c->stepped, c->stage, c->stream);
+    unpermute_to_stage(c);
     HIP_TRY(c, hipGetLastError(), "unpermute launch");
     std::vector<float> buf((size_t)5 * D * np);
     if (pibm_status s = check_hip(c, hipMemcpyAsync(buf.data(), c->stage, buf.size() * 4, hipMemcpyDeviceToHost, c->stream), "copy particles")) return s;
@@ -840,16 +858,9 @@ pibm_status pibm_read_particles_device(pibm_ctx* c, float* x_hi, float* x_lo, fl
     if (!c) return PIBM_E_ARG;
     if (c->np == 0) return PIBM_OK;
     if (!c->particles_set) return fail(c, PIBM_E_STATE, "particles not set");
-    const int D = c->D, np = c->np;
-    particles_unpermute(D, c->pb, np, c->stepped, c->stage, c->stream);
-    HIP_TRY(c, hipGetLastError(), "unpermute launch");
-    // staging layout [x_hi D][x_lo D][v D][f_hydro D][f_contact D] x np
-    float* out[5] = {x_hi, x_lo, v, f_hydro, f_contact};
-    const size_t plane = sizeof(float) * (size_t)D * np;
-    HipSeq q;
-    for (int k = 0; k < 5; k++)
-        if (out[k]) q(hipMemcpyAsync(out[k], c->stage + (size_t)k * D * np, plane, hipMemcpyDeviceToDevice, c->stream));
-    return check_hip(c, q.e, "copy particles");
+    float* const out[5] = {x_hi, x_lo, v, f_hydro, f_contact};
+    particles_unpermute(c->D, c->pb, c->np, c->stepped, out, c->stream);
+    return check_hip(c, hipGetLastError(), "unpermute launch");
 }
 
 pibm_status pibm_read_particles(pibm_ctx* c, double* x, double* v, double* f_hydro, double* f_contact) {
@@ -857,7 +868,7 @@ pibm_status pibm_read_particles(pibm_ctx* c, double* x, double* v, double* f_hyd
     if (c->np == 0) return PIBM_OK;
     if (!c->particles_set) return fail(c, PIBM_E_STATE, "particles not set");
     const int D = c->D, np = c->np;
-    particles_unpermute(D, c->pb, np, c->stepped, c->stage, c->stream);
+    unpermute_to_stage(c);
     HIP_TRY(c, hipGetLastError(), "unpermute launch");
     std::vector<float> buf((size_t)5 * D * np);
     if (pibm_status s = check_hip(c, hipMemcpyAsync(buf.data(), c->stage, buf.size() * 4, hipMemcpyDeviceToHost, c->stream), "copy particles")) return s;
@@ -961,7 +972,7 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     // restricts to the node rows that the particles' stencils reach
     const bool fused = c->D == 2 && c->pc.L <= 1;
     q(mark(c, row, 0));
-    if (c->np > 0) particles_sort(c->D, c->pb, c->np, c->pc, c->stream);
+    if (c->np > 0) sort_particles(c);
     if (tape) adj_save_tape(c->D, c->pb, c->np, c->pc.nbins, tape, c->stream);
     q(mark(c, row, 1));
     const bool nodes = particles_interp_by_nodes(c->D, c->np);
@@ -1123,6 +1134,7 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
         if (seg != R.taped) {
             q(hipMemcpyAsync(R.tape_f, R.ck_f[seg], fbytes, hipMemcpyDeviceToDevice, s));
             adj_load_state(D, c->pb, np, R.ck_p[seg], R.d_id, R.rp_id, s);
+            c->unordered = true;
             for (int k = 0; k < len; k++) {
                 void* fout = (k + 1 < len) ? (void*)(R.tape_f + (k + 1) * fbytes) : c->fB;
                 q(launch_step(c, R.tape_f + k * fbytes, fout, R.tape_F + (size_t)k * D * N, -1, true,
@@ -1152,6 +1164,7 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
     // leave the context in the final state of the rollout
     q(hipMemcpyAsync(c->fA, R.ck_f[R.nck - 1], fbytes, hipMemcpyDeviceToDevice, s));
     adj_load_state(D, c->pb, np, R.ck_p[R.nck - 1], R.d_id, R.rp_id, s);
+    c->unordered = true;
     if (q.e != hipSuccess) {
         (void)hipStreamSynchronize(s);          // acc is written by the copy above
         return check_hip(c, q.e, "backward: copy");
@@ -1197,7 +1210,7 @@ pibm_status pibm_adjoint_stage(pibm_ctx* c, int32_t stage, const float* in0, con
         if (!in0 || !in1 || !in2 || !out0 || !out1 || !out2)
             return fail(c, PIBM_E_ARG, "particle stage: null array");
         if (np == 0) return fail(c, PIBM_E_STATE, "particle stage: no particles");
-        particles_sort(D, c->pb, np, c->pc, s);
+        sort_particles(c);
         lattice_moments(Q, c->fp16, c->sl2, c->fA, c->mom, N, RowMask{}, s);
         adj_fill(R.acc, 8, 0.f, s);
         adj_fill(R.xbl[0], DN, 0.f, s);
@@ -1213,7 +1226,7 @@ pibm_status pibm_adjoint_stage(pibm_ctx* c, int32_t stage, const float* in0, con
     case PIBM_STAGE_INTERP: {
         if (!in0 || !out0) return fail(c, PIBM_E_ARG, "interpolation stage: null array");
         if (np == 0) return fail(c, PIBM_E_STATE, "interpolation stage: no particles");
-        particles_sort(D, c->pb, np, c->pc, s);
+        sort_particles(c);
         adj_pack_mom(in0, 1 + D, N, c->mom, s);
         particles_interp(D, c->pb, np, c->grid, c->pc, c->mom, s);
         q(hipMemcpyAsync(out0, c->pb.drho_i, 4 * (size_t)np, hipMemcpyDeviceToDevice, s));
