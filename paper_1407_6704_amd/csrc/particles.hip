@@ -1002,11 +1002,155 @@ __global__ __launch_bounds__(256, 8) void k_classify(PState A, PState Bn, int np
     if (threadIdx.x == 0) bsum[lb] = tot;
 }
 
+// Touching islands: an island of two whose members touch at the start of the
+// step, or would close their gap within it at their present speeds, and an
+// island of one in the same position to a wall.  Such an island is likely to
+// be in contact for most of the step and so to take every sub-step, one
+// after the other.  They are ranked apart (rank | TOUCH_BIT) and laid out
+// thinly, ahead of the packed waves (touch_plan).  Only the layout depends on
+// this test: an island's result does not depend on its wave.
+constexpr uint32_t TOUCH_BIT = 0x80000000u;
+constexpr uint32_t CLS_PAIR = WAVE + 2, CLS_WALL = WAVE + 3;     // rank classes of the touching islands
+// What k_collect leaves in irank for the class of the islands: the particle
+// touches its first candidate, a wall.
+constexpr uint32_t TOUCHES_PAIR = 1u, TOUCHES_WALL = 2u;
+template <int D>
+__device__ __forceinline__ float speed_of(const PState& A, uint32_t s) {
+    float us = 0.f;
+#pragma unroll
+    for (int ax = 0; ax < D; ax++) us += A.u[ax][s] * A.u[ax][s];
+    return sqrtf(us);
+}
+template <int D>
+__device__ __forceinline__ bool touching_wall(uint32_t s, const PState& A, const PCfg& c) {
+    if (c.contact != PIBM_CONTACT_LSD) return false;           // packed in any case (touch_plan)
+    const float us = speed_of<D>(A, s);
+    bool near = false;
+#pragma unroll
+    for (int ax = 0; ax < D; ax++) {
+        const float x = A.xh[ax][s] + A.xl[ax][s];
+        near = near || fminf(x, (float)c.n[ax] - x) - 0.5f * A.d[s] < us;
+    }
+    return near;
+}
+template <int D>
+__device__ __forceinline__ bool touching_pair(uint32_t s, uint32_t t, const PState& A) {
+    float r2 = 0.f;
+#pragma unroll
+    for (int ax = 0; ax < D; ax++) {
+        const float e = (A.xh[ax][s] - A.xh[ax][t]) + (A.xl[ax][s] - A.xl[ax][t]);
+        r2 += e * e;
+    }
+    const float reach = 0.5f * (A.d[s] + A.d[t]) + speed_of<D>(A, s) + speed_of<D>(A, t);
+    return r2 < reach * reach;
+}
+// Candidate constants for the sub-steps of particle s and its candidate t (all
+// but the partner's place), candidate entry `entry`.  K0 = r_c^2 - |r0|^2 is formed in
+// double-float so that overlaps far below the FP32 spacing of positions
+// (1e-9 .. 1e-6 for stiff springs and slow particles) stay resolved.
+template <int D>
+__device__ __forceinline__ CandData cand_entry(uint32_t s, uint32_t t, uint32_t entry, float ms, const PState& A,
+                                               const PCfg& c, const MdBuf& md) {
+#pragma clang fp contract(off)
+    CandData cd;
+    cd.local = 0;
+    // r0 = X_s - X_t in double-float, |r0|^2 in double-float
+    float sh = 0.f, sl = 0.f;
+    float r0[3] = {0, 0, 0};
+#pragma unroll
+    for (int ax = 0; ax < D; ax++) {
+        float hi, e;
+        two_sum(A.xh[ax][s], -A.xh[ax][t], hi, e);
+        float lo = e + (A.xl[ax][s] - A.xl[ax][t]);
+        float rh, rl;
+        fast_two_sum(hi, lo, rh, rl);
+        r0[ax] = rh;
+        // (rh + rl)^2 = rh^2 + 2 rh rl (+ rl^2, negligible)
+        float p = rh * rh;
+        float pe = fmaf(rh, rh, -p);
+        pe = fmaf(2.0f * rh, rl, pe);
+        float ns, ne;
+        two_sum(sh, p, ns, ne);
+        sl += ne + pe;
+        sh = ns;
+    }
+    // r_c = (d_s + d_t)/2 exactly as a double-float, then r_c^2
+    float dsum, derr;
+    two_sum(A.d[s], A.d[t], dsum, derr);
+    float rch = 0.5f * dsum, rcl = 0.5f * derr;
+    float q = rch * rch;
+    float qe = fmaf(rch, rch, -q);
+    qe = fmaf(2.0f * rch, rcl, qe);
+    // K0 = (q + qe) - (sh + sl)
+    float k0h, k0e;
+    two_sum(q, -sh, k0h, k0e);
+    cd.K0 = k0h + (k0e + (qe - sl));
+    cd.rc = rch;
+    cd.r0[0] = r0[0]; cd.r0[1] = r0[1]; cd.r0[2] = r0[2];
+    if (c.contact == PIBM_CONTACT_HERTZ || c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) {
+        // Hertz: gam holds the pair's stiffness (4/3) E* sqrt(R*)
+        const float rs = 0.5f * A.d[s], rt = 0.5f * A.d[t];
+        const float rstar = rs * rt / (rs + rt);
+        cd.gam = c.hk * sqrtf(rstar);
+        if (md.cmd) {
+            // the tangential force this pair carried at the end of the last step
+            const int pid = A.id[t];
+            const long long base = (long long)A.id[s] * c.hmax;
+            const uint32_t hn = md.hcnt[A.id[s]];
+            float S[TSN];
+#pragma unroll
+            for (int q = 0; q < TSN; q++) S[q] = 0.f;
+            for (uint32_t e = 0; e < hn; e++)
+                if (md.hkey[base + e] == pid) {
+#pragma unroll
+                    for (int q = 0; q < TSN; q++) S[q] = md.hT[TSN * (base + e) + q];
+                    break;
+                }
+            md.cmd[entry] = make_float4(S[0], S[1], S[2], c.kt8 * sqrtf(rstar));
+            md.cms[2 * entry] = make_float4(S[3], S[4], S[5], S[9]);
+            md.cms[2 * entry + 1] = make_float4(S[6], S[7], S[8], 0.f);
+            md.cpid[entry] = pid;
+        }
+    } else {
+        float mt = particle_mass(D, A.d[t], A.rp[t]);
+        float meff = ms * mt / (ms + mt);
+        if (A.fixa) {                            // a fixed partner has infinite mass
+            if (A.fixa[t] > 0.f) meff = ms;
+            else if (A.fixa[s] > 0.f) meff = mt;
+        }
+        cd.gam = 2.0f * c.zeta * sqrtf(c.kn * meff);
+    }
+    return cd;
+}
+
+// The candidate constants of active particle s (candidates cand[off .. off + n))
+// and what it touches.
+template <int D>
+__device__ __forceinline__ uint32_t cand_prep(uint32_t s, uint32_t off, int n, const uint32_t* __restrict__ cand,
+                                              const PState& A, const PCfg& c, CandData* __restrict__ cdata,
+                                              const MdBuf& md) {
+    uint32_t touch = touching_wall<D>(s, A, c) ? TOUCHES_WALL : 0u;
+    if (n > 0) {
+        const float ms = particle_mass(D, A.d[s], A.rp[s]);
+        if (touching_pair<D>(s, cand[off], A)) touch |= TOUCHES_PAIR;
+        for (int k = 0; k < n; k++) cdata[off + k] = cand_entry<D>(s, cand[off + k], off + k, ms, A, c, md);
+    }
+    return touch;
+}
+
 // active particles: compact index, candidate list (active partners only; a
-// free partner provably never touches), union-find init.  RAW: bsum holds
+// free partner provably never touches), union-find init; and, where one
+// workgroup sets up the islands, the candidates' constants: they gather some
+// 20 words from two particles per pair, which costs that one workgroup, whose
+// unit looks up a line a cycle, 16 us of its 24 at 700 active particles, and 5
+// us more here, where the active particles are spread over the chip (128^3
+// with obstacles: collection and set-up 10.4 + 27.9 -> 15.4 + 8.1 us; disks
+// 1501x1103 6.3 + 26.1 -> 9.1 + 7.2 us).  With many active particles, packed
+// lanes of k_uf_hook do it faster (256^3: 14 us here).  RAW: bsum holds
 // the blocks' unscanned totals and each block adds up those before it (for
 // up to RAW_MAX_BLOCKS blocks; beyond, a one-block scan runs first).
-template <int D, bool RAW>
+// PREP: the constants are formed here (else by k_uf_hook).
+template <int D, bool RAW, bool PREP>
 __global__ __launch_bounds__(256) void k_collect(PState A, int np, PCfg c, const uint32_t* __restrict__ start,
                                                  const float4* __restrict__ pos4,
                                                  const uint32_t* __restrict__ keys_sorted,
@@ -1016,7 +1160,9 @@ __global__ __launch_bounds__(256) void k_collect(PState A, int np, PCfg c, const
                                                  uint32_t* __restrict__ alist, uint32_t* __restrict__ aidx,
                                                  uint32_t* __restrict__ cand, uint32_t* __restrict__ ccount,
                                                  uint32_t* __restrict__ parent, uint32_t* __restrict__ isize,
-                                                 uint32_t* __restrict__ fill, uint32_t* __restrict__ counters) {
+                                                 uint32_t* __restrict__ irank, uint32_t* __restrict__ fill,
+                                                 CandData* __restrict__ cdata, MdBuf md,
+                                                 uint32_t* __restrict__ counters) {
     __shared__ unsigned long long sh4[4];
     const unsigned lb = xcd_block();
     int s = lb * 256 + threadIdx.x;
@@ -1056,7 +1202,9 @@ __global__ __launch_bounds__(256) void k_collect(PState A, int np, PCfg c, const
     isize[a] = 0;
     fill[a] = 0;
     int n = cap > 0 ? collect_neighbours<D>(pos4, start, keys_sorted, c, s, actcc, cand + off, cap, A.fixa) : 0;
-    ccount[s] = (uint32_t)min(n, cap);
+    n = min(n, cap);
+    ccount[s] = (uint32_t)n;
+    if (PREP) irank[a] = cand_prep<D>(s, off, n, cand, A, c, cdata, md);
 }
 
 __device__ __forceinline__ uint32_t uf_find(uint32_t* parent, uint32_t x) {
@@ -1068,36 +1216,52 @@ __device__ __forceinline__ uint32_t uf_find(uint32_t* parent, uint32_t x) {
     return x;
 }
 
-// Union active particle a with its later candidates (the larger root is
-// hooked under the smaller, so every island's root is its smallest index).
+// Union of a's and b's islands; of a pair that names each other the later
+// member's call is left out (b <= a).
+__device__ __forceinline__ void uf_union(uint32_t* parent, uint32_t a, uint32_t b) {
+    if (b <= a) return;
+    while (true) {
+        uint32_t ra = uf_find(parent, a), rb = uf_find(parent, b);
+        if (ra == rb) break;
+        if (ra > rb) { const uint32_t t = ra; ra = rb; rb = t; }
+        if (atomicCAS(&parent[rb], rb, ra) == rb) break;
+    }
+}
+
+// The union of every active particle with its later candidates (the larger
+// root is hooked under the smaller, so every island's root is its smallest
+// index).
 __device__ __forceinline__ void uf_hook_one(uint32_t a, const uint32_t* __restrict__ alist,
                                             const uint32_t* __restrict__ ccount,
                                             const unsigned long long* __restrict__ prefix,
                                             const uint32_t* __restrict__ cand, const uint32_t* __restrict__ aidx,
                                             uint32_t* parent) {
-    uint32_t s = alist[a];
-    uint32_t off = (uint32_t)(prefix[s] & 0xffffffffULL);
-    int cnt = (int)ccount[s];
-    for (int k = 0; k < cnt; k++) {
-        uint32_t b = aidx[cand[off + k]];
-        if (b <= a) continue;
-        while (true) {
-            uint32_t ra = uf_find(parent, a), rb = uf_find(parent, b);
-            if (ra == rb) break;
-            if (ra > rb) { uint32_t t = ra; ra = rb; rb = t; }
-            if (atomicCAS(&parent[rb], rb, ra) == rb) break;
-        }
-    }
+    const uint32_t s = alist[a];
+    const uint32_t off = (uint32_t)(prefix[s] & 0xffffffffULL);
+    const int cnt = (int)ccount[s];
+    for (int k = 0; k < cnt; k++) uf_union(parent, a, aidx[cand[off + k]]);
 }
 
-__global__ __launch_bounds__(256) void k_uf_hook(const uint32_t* __restrict__ alist,
-                                                 const uint32_t* __restrict__ ccount,
-                                                 const unsigned long long* __restrict__ prefix,
-                                                 const uint32_t* __restrict__ cand, const uint32_t* __restrict__ aidx,
-                                                 uint32_t* parent, const uint32_t* __restrict__ counters) {
-    uint32_t na = counters[CNT_ACTIVE];
-    for (uint32_t a = blockIdx.x * 256 + threadIdx.x; a < na; a += gridDim.x * 256)
-        uf_hook_one(a, alist, ccount, prefix, cand, aidx, parent);
+// Unions by the even workgroups, the candidates' constants by the odd ones
+// (one after the other they took 17.6 us at 256^3, 8.6 us so).
+template <int D>
+__global__ __launch_bounds__(64) void k_uf_hook(PState A, PCfg c, const uint32_t* __restrict__ alist,
+                                                const uint32_t* __restrict__ ccount,
+                                                const unsigned long long* __restrict__ prefix,
+                                                const uint32_t* __restrict__ cand, const uint32_t* __restrict__ aidx,
+                                                uint32_t* parent, uint32_t* __restrict__ irank,
+                                                CandData* __restrict__ cdata, MdBuf md,
+                                                const uint32_t* __restrict__ counters) {
+    const uint32_t na = counters[CNT_ACTIVE];
+    const uint32_t stride = (gridDim.x / 2) * 64;
+    for (uint32_t a = (blockIdx.x / 2) * 64 + threadIdx.x; a < na; a += stride) {
+        if ((blockIdx.x & 1) == 0) {
+            uf_hook_one(a, alist, ccount, prefix, cand, aidx, parent);
+        } else {
+            const uint32_t s = alist[a];
+            irank[a] = cand_prep<D>(s, (uint32_t)(prefix[s] & 0xffffffffULL), (int)ccount[s], cand, A, c, cdata, md);
+        }
+    }
 }
 
 __global__ __launch_bounds__(256) void k_uf_flatten(uint32_t* parent, uint32_t* __restrict__ isize,
@@ -1123,49 +1287,6 @@ __device__ __forceinline__ void wave_plan(const uint32_t* cls, uint32_t* wb) {
         wb[s] = inc - v;
         if (s == WAVE) wb[0] = inc;
     }
-}
-
-// Touching islands: an island of two whose members touch at the start of the
-// step, or would close their gap within it at their present speeds, and an
-// island of one in the same position to a wall.  Such an island is likely to
-// be in contact for most of the step and so to take every sub-step, one
-// after the other.  They are ranked apart (rank | TOUCH_BIT) and laid out
-// thinly, ahead of the packed waves (touch_plan).  Only the layout depends on
-// this test: an island's result does not depend on its wave.
-constexpr uint32_t TOUCH_BIT = 0x80000000u;
-constexpr uint32_t CLS_PAIR = WAVE + 2, CLS_WALL = WAVE + 3;     // rank classes of the touching islands
-template <int D>
-__device__ __forceinline__ bool island_touching(uint32_t a, uint32_t size, const PState& A, const PCfg& c,
-                                                const uint32_t* __restrict__ alist,
-                                                const uint32_t* __restrict__ ccount,
-                                                const unsigned long long* __restrict__ prefix,
-                                                const uint32_t* __restrict__ cand) {
-    const uint32_t s = alist[a];
-    float us = 0.f;
-#pragma unroll
-    for (int ax = 0; ax < D; ax++) us += A.u[ax][s] * A.u[ax][s];
-    us = sqrtf(us);
-    if (size == 1) {
-        if (c.contact != PIBM_CONTACT_LSD) return false;       // packed in any case (touch_plan)
-        bool near = false;
-#pragma unroll
-        for (int ax = 0; ax < D; ax++) {
-            const float x = A.xh[ax][s] + A.xl[ax][s];
-            near = near || fminf(x, (float)c.n[ax] - x) - 0.5f * A.d[s] < us;
-        }
-        return near;
-    }
-    if (ccount[s] == 0) return false;
-    const uint32_t t = cand[(uint32_t)(prefix[s] & 0xffffffffULL)];
-    float r2 = 0.f, ut = 0.f;
-#pragma unroll
-    for (int ax = 0; ax < D; ax++) {
-        const float e = (A.xh[ax][s] - A.xh[ax][t]) + (A.xl[ax][s] - A.xl[ax][t]);
-        r2 += e * e;
-        ut += A.u[ax][t] * A.u[ax][t];
-    }
-    const float reach = 0.5f * (A.d[s] + A.d[t]) + us + sqrtf(ut);
-    return r2 < reach * reach;
 }
 
 // Layout of the touching islands: `per` of them to a workgroup of the
@@ -1195,15 +1316,17 @@ __device__ __forceinline__ uint32_t touch_lanes(uint32_t pairs, uint32_t walls) 
     return (2 * pairs + walls + WAVE - 1) / WAVE * WAVE;
 }
 
+// Class of an island from its size and what its root touches.
+__device__ __forceinline__ uint32_t island_class(uint32_t size, uint32_t touch) {
+    if (size == 1 && (touch & TOUCHES_WALL)) return CLS_WALL;
+    if (size == 2 && (touch & TOUCHES_PAIR)) return CLS_PAIR;
+    return size <= WAVE ? size : WAVE + 1;
+}
+
 // islands by size class: 1..64 packed into waves, 65 = larger than a wave
 // (ranks within a class are counted in LDS per chunk of 256 and reserved
 // with one global atomic per class and chunk: no contended counter)
-template <int D>
-__global__ __launch_bounds__(256) void k_island_class(PState A, PCfg c, const uint32_t* __restrict__ alist,
-                                                      const uint32_t* __restrict__ ccount,
-                                                      const unsigned long long* __restrict__ prefix,
-                                                      const uint32_t* __restrict__ cand,
-                                                      const uint32_t* __restrict__ parent,
+__global__ __launch_bounds__(256) void k_island_class(const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ isize, uint32_t* __restrict__ irank,
                                                       uint32_t* __restrict__ bigroot, uint32_t* counters) {
     __shared__ uint32_t lc[WAVE + 4], gbase[WAVE + 4];     // the last two: touching pairs, touching a wall
@@ -1216,10 +1339,7 @@ __global__ __launch_bounds__(256) void k_island_class(PState A, PCfg c, const ui
         uint32_t cls = 0, lr = 0;
         const bool root = a < na && parent[a] == a;
         if (root) {
-            const uint32_t sz = isize[a];
-            cls = sz <= WAVE ? sz : WAVE + 1;
-            if (cls <= 2 && island_touching<D>(a, cls, A, c, alist, ccount, prefix, cand))
-                cls = cls == 2 ? CLS_PAIR : CLS_WALL;
+            cls = island_class(isize[a], irank[a]);
             lr = atomicAdd(&lc[cls], 1u);
         }
         __syncthreads();
@@ -1236,6 +1356,28 @@ __global__ __launch_bounds__(256) void k_island_class(PState A, PCfg c, const ui
     }
 }
 
+// Member `pos` of an island of size sz and rank `rank` in its class: its place
+// in its wave's or workgroup's lanes (an island larger than a wave: itself).
+__device__ __forceinline__ uint32_t island_place(uint32_t a, uint32_t pos, uint32_t sz, uint32_t rank, const PCfg& c,
+                                                 int* __restrict__ lanemember, const uint32_t* __restrict__ bigoff,
+                                                 uint32_t* __restrict__ bigmember, const uint32_t* wavebase,
+                                                 uint32_t pairs, uint32_t walls) {
+    if (sz <= WAVE && (rank & TOUCH_BIT)) {
+        const uint32_t ir = rank & ~TOUCH_BIT;
+        lanemember[sz == 2 ? 2 * ir + pos : 2 * pairs + ir] = (int)a;
+        return (ir % touch_plan(sz == 2 ? pairs : walls, sz, c).per) * sz + pos;
+    }
+    if (sz <= WAVE) {
+        const uint32_t per = WAVE / sz;
+        const uint32_t w = wavebase[sz] + rank / per;
+        const uint32_t lane = (rank % per) * sz + pos;
+        lanemember[touch_lanes(pairs, walls) + (long long)w * WAVE + lane] = (int)a;
+        return lane;
+    }
+    bigmember[bigoff[rank] + pos] = a;
+    return a;
+}
+
 // Lane (small islands, packed by size into waves) or slot (large islands)
 // of active particle a; wavebase[s] = first wave of size class s.
 __device__ __forceinline__ void island_place_one(uint32_t a, const PCfg& c, const uint32_t* __restrict__ parent,
@@ -1245,24 +1387,9 @@ __device__ __forceinline__ void island_place_one(uint32_t a, const PCfg& c, cons
                                                  const uint32_t* __restrict__ bigoff,
                                                  uint32_t* __restrict__ bigmember, const uint32_t* wavebase,
                                                  uint32_t pairs, uint32_t walls) {
-    uint32_t r = parent[a];
-    uint32_t pos = atomicAdd(&fill[r], 1u);
-    uint32_t sz = isize[r];
-    if (sz <= WAVE && (irank[r] & TOUCH_BIT)) {
-        const uint32_t ir = irank[r] & ~TOUCH_BIT;
-        lanemember[sz == 2 ? 2 * ir + pos : 2 * pairs + ir] = (int)a;
-        loc[a] = (ir % touch_plan(sz == 2 ? pairs : walls, sz, c).per) * sz + pos;
-    } else if (sz <= WAVE) {
-        uint32_t ir = irank[r];
-        uint32_t per = WAVE / sz;
-        uint32_t w = wavebase[sz] + ir / per;
-        uint32_t lane = (ir % per) * sz + pos;
-        lanemember[touch_lanes(pairs, walls) + (long long)w * WAVE + lane] = (int)a;
-        loc[a] = lane;
-    } else {
-        bigmember[bigoff[irank[r]] + pos] = a;
-        loc[a] = a;
-    }
+    const uint32_t r = parent[a];
+    const uint32_t pos = atomicAdd(&fill[r], 1u);
+    loc[a] = island_place(a, pos, isize[r], irank[r], c, lanemember, bigoff, bigmember, wavebase, pairs, walls);
 }
 
 // Every block first forms the wave plan and the large-island offsets itself
@@ -1304,128 +1431,120 @@ __global__ __launch_bounds__(256) void k_island_place(PCfg c, const uint32_t* __
         island_place_one(a, c, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, pairs, walls);
 }
 
-// Candidate constants for the sub-steps.  K0 = r_c^2 - |r0|^2 is formed in
-// double-float so that overlaps far below the FP32 spacing of positions
-// (1e-9 .. 1e-6 for stiff springs and slow particles) stay resolved.
-template <int D>
-__device__ __forceinline__ void cand_prep_one(uint32_t a, const PState& A, const PCfg& c,
-                                              const uint32_t* __restrict__ alist,
-                                              const uint32_t* __restrict__ ccount,
-                                              const unsigned long long* __restrict__ prefix,
-                                              const uint32_t* __restrict__ cand, const uint32_t* __restrict__ aidx,
-                                              const uint32_t* __restrict__ loc, CandData* __restrict__ cdata,
-                                              MdBuf md) {
-#pragma clang fp contract(off)
-    uint32_t s = alist[a];
-    uint32_t off = (uint32_t)(prefix[s] & 0xffffffffULL);
-    int cnt = (int)ccount[s];
-    float ms = particle_mass(D, A.d[s], A.rp[s]);
-    for (int k = 0; k < cnt; k++) {
-        uint32_t t = cand[off + k];
-        CandData cd;
-        cd.local = (int)loc[aidx[t]];
-        // r0 = X_s - X_t in double-float, |r0|^2 in double-float
-        float sh = 0.f, sl = 0.f;
-        float r0[3] = {0, 0, 0};
-#pragma unroll
-        for (int ax = 0; ax < D; ax++) {
-            float hi, e;
-            two_sum(A.xh[ax][s], -A.xh[ax][t], hi, e);
-            float lo = e + (A.xl[ax][s] - A.xl[ax][t]);
-            float rh, rl;
-            fast_two_sum(hi, lo, rh, rl);
-            r0[ax] = rh;
-            // (rh + rl)^2 = rh^2 + 2 rh rl (+ rl^2, negligible)
-            float p = rh * rh;
-            float pe = fmaf(rh, rh, -p);
-            pe = fmaf(2.0f * rh, rl, pe);
-            float ns, ne;
-            two_sum(sh, p, ns, ne);
-            sl += ne + pe;
-            sh = ns;
-        }
-        // r_c = (d_s + d_t)/2 exactly as a double-float, then r_c^2
-        float dsum, derr;
-        two_sum(A.d[s], A.d[t], dsum, derr);
-        float rch = 0.5f * dsum, rcl = 0.5f * derr;
-        float q = rch * rch;
-        float qe = fmaf(rch, rch, -q);
-        qe = fmaf(2.0f * rch, rcl, qe);
-        // K0 = (q + qe) - (sh + sl)
-        float k0h, k0e;
-        two_sum(q, -sh, k0h, k0e);
-        cd.K0 = k0h + (k0e + (qe - sl));
-        cd.rc = rch;
-        cd.r0[0] = r0[0]; cd.r0[1] = r0[1]; cd.r0[2] = r0[2];
-        if (c.contact == PIBM_CONTACT_HERTZ || c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) {
-            // Hertz: gam holds the pair's stiffness (4/3) E* sqrt(R*)
-            const float rs = 0.5f * A.d[s], rt = 0.5f * A.d[t];
-            const float rstar = rs * rt / (rs + rt);
-            cd.gam = c.hk * sqrtf(rstar);
-            if (md.cmd) {
-                // the tangential force this pair carried at the end of the last step
-                const int pid = A.id[t];
-                const long long base = (long long)A.id[s] * c.hmax;
-                const uint32_t hn = md.hcnt[A.id[s]];
-                float S[TSN];
-#pragma unroll
-                for (int q = 0; q < TSN; q++) S[q] = 0.f;
-                for (uint32_t e = 0; e < hn; e++)
-                    if (md.hkey[base + e] == pid) {
-#pragma unroll
-                        for (int q = 0; q < TSN; q++) S[q] = md.hT[TSN * (base + e) + q];
-                        break;
-                    }
-                md.cmd[off + k] = make_float4(S[0], S[1], S[2], c.kt8 * sqrtf(rstar));
-                md.cms[2 * (off + k)] = make_float4(S[3], S[4], S[5], S[9]);
-                md.cms[2 * (off + k) + 1] = make_float4(S[6], S[7], S[8], 0.f);
-                md.cpid[off + k] = pid;
-            }
-        } else {
-            float mt = particle_mass(D, A.d[t], A.rp[t]);
-            float meff = ms * mt / (ms + mt);
-            if (A.fixa) {                            // a fixed partner has infinite mass
-                if (A.fixa[t] > 0.f) meff = ms;
-                else if (A.fixa[s] > 0.f) meff = mt;
-            }
-            cd.gam = 2.0f * c.zeta * sqrtf(c.kn * meff);
-        }
-        cdata[off + k] = cd;
-    }
+// The partners' places in the candidates' constants.
+__device__ __forceinline__ void cand_place_one(uint32_t a, const uint32_t* __restrict__ alist,
+                                               const uint32_t* __restrict__ ccount,
+                                               const unsigned long long* __restrict__ prefix,
+                                               const uint32_t* __restrict__ cand, const uint32_t* __restrict__ aidx,
+                                               const uint32_t* __restrict__ loc, CandData* __restrict__ cdata) {
+    const uint32_t s = alist[a];
+    const uint32_t off = (uint32_t)(prefix[s] & 0xffffffffULL);
+    const int cnt = (int)ccount[s];
+    for (int k = 0; k < cnt; k++) cdata[off + k].local = (int)loc[aidx[cand[off + k]]];
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void k_cand_prep(PState A, PCfg c, const uint32_t* __restrict__ alist,
-                                                   const uint32_t* __restrict__ ccount,
-                                                   const unsigned long long* __restrict__ prefix,
-                                                   const uint32_t* __restrict__ cand, const uint32_t* __restrict__ aidx,
-                                                   const uint32_t* __restrict__ loc, CandData* __restrict__ cdata,
-                                                   MdBuf md, const uint32_t* __restrict__ counters) {
-    uint32_t na = counters[CNT_ACTIVE];
+__global__ __launch_bounds__(256) void k_cand_place(const uint32_t* __restrict__ alist,
+                                                    const uint32_t* __restrict__ ccount,
+                                                    const unsigned long long* __restrict__ prefix,
+                                                    const uint32_t* __restrict__ cand,
+                                                    const uint32_t* __restrict__ aidx,
+                                                    const uint32_t* __restrict__ loc, CandData* __restrict__ cdata,
+                                                    const uint32_t* __restrict__ counters) {
+    const uint32_t na = counters[CNT_ACTIVE];
     for (uint32_t a = blockIdx.x * 256 + threadIdx.x; a < na; a += gridDim.x * 256)
-        cand_prep_one<D>(a, A, c, alist, ccount, prefix, cand, aidx, loc, cdata, md);
+        cand_place_one(a, alist, ccount, prefix, cand, aidx, loc, cdata);
 }
 
 // The whole island set-up of one step in one 1024-thread workgroup, phase
 // after phase (for a few active particles this replaces five short
 // launches): union the candidates, flatten
 // and size the islands, class them by size, plan the waves, place every
-// member, and prepare the candidate constants.  Same results as the
+// member and its partners.  Same results as the
 // multi-kernel chain (roots are the smallest index; sub-step results do not
 // depend on lane placement).
 constexpr int SETUP_THREADS = 1024;
-template <int D>
 __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
-    PState A, PCfg c, const uint32_t* __restrict__ alist, const uint32_t* __restrict__ ccount,
+    PCfg c, const uint32_t* __restrict__ alist, const uint32_t* __restrict__ ccount,
     const unsigned long long* __restrict__ prefix, const uint32_t* __restrict__ cand,
     const uint32_t* __restrict__ aidx, uint32_t* parent, uint32_t* isize, uint32_t* irank, uint32_t* fill,
-    int* lanemember, uint32_t* loc, uint32_t* bigroot, uint32_t* bigoff, uint32_t* bigmember, CandData* cdata, MdBuf md,
-    uint32_t* counters, long long lane_cap) {
+    int* lanemember, uint32_t* loc, uint32_t* bigroot, uint32_t* bigoff, uint32_t* bigmember, CandData* cdata,
+    uint32_t* counters) {
     __shared__ uint32_t ccls[WAVE + 4];     // the last two: touching pairs, touching a wall
     __shared__ uint32_t wbase[WAVE + 1];
+    __shared__ uint32_t lpar[SETUP_THREADS], lsize[SETUP_THREADS], lrank[SETUP_THREADS], lfill[SETUP_THREADS],
+        lloc[SETUP_THREADS], lbig[SETUP_THREADS / WAVE], lbigoff[SETUP_THREADS / WAVE];
     const uint32_t t = threadIdx.x;
     const uint32_t na = counters[CNT_ACTIVE];
     if (t < WAVE + 4) ccls[t] = 0;
+    if (na <= SETUP_THREADS) {
+        // one active particle per thread, islands in LDS
+        const bool on = t < na;
+        constexpr int KEEP = 4;               // partners' active indices held in registers
+        uint32_t off = 0, part[KEEP];
+        int cnt = 0;
+        uint32_t touch = 0;
+        lpar[t] = t;
+        lsize[t] = lfill[t] = 0;
+        if (on) {
+            const uint32_t s = alist[t];
+            touch = irank[t];
+            off = (uint32_t)(prefix[s] & 0xffffffffULL);
+            cnt = (int)ccount[s];
+#pragma unroll
+            for (int k = 0; k < KEEP; k++)
+                if (k < cnt) part[k] = aidx[cand[off + k]];
+        }
+        __syncthreads();
+        auto partner = [&](int k) {
+            uint32_t b = 0;
+#pragma unroll
+            for (int q = 0; q < KEEP; q++) b = q == k ? part[q] : b;
+            return k < KEEP ? b : aidx[cand[off + k]];
+        };
+        for (int k = 0; k < cnt; k++) uf_union(lpar, t, partner(k));
+        __syncthreads();
+        const uint32_t root = uf_find(lpar, t);
+        if (on) atomicAdd(&lsize[root], 1u);
+        __syncthreads();
+        // (lpar[t] is not flattened in LDS: others may still walk it)
+        if (on && root == t) {
+            const uint32_t cls = island_class(lsize[t], touch);
+            const uint32_t r = atomicAdd(&ccls[cls], 1u);
+            lrank[t] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
+            if (cls == WAVE + 1) lbig[r] = t;
+        }
+        __syncthreads();
+        const uint32_t pairs = ccls[CLS_PAIR], walls = ccls[CLS_WALL], nbig = ccls[WAVE + 1];
+        wave_plan(ccls, wbase);
+        if (t == SETUP_THREADS - 1) {
+            uint32_t o = 0;
+            for (uint32_t k = 0; k < nbig; k++) {
+                lbigoff[k] = o;
+                bigoff[k] = o;
+                bigroot[k] = lbig[k];
+                o += lsize[lbig[k]];
+            }
+            counters[CNT_PAIRC] = pairs;
+            counters[CNT_WALLC] = walls;
+            counters[CNT_CLASS + WAVE + 1] = nbig;
+            counters[CNT_BIG] = nbig;
+        }
+        __syncthreads();
+        if (t < WAVE) {
+            counters[CNT_WAVEBASE + t + 1] = wbase[t + 1];
+            counters[CNT_CLASS + t + 1] = ccls[t + 1];
+        }
+        if (t == 0) counters[CNT_WAVES] = wbase[0];
+        if (on) {
+            const uint32_t pos = atomicAdd(&lfill[root], 1u), sz = lsize[root], rank = lrank[root];
+            lloc[t] = island_place(t, pos, sz, rank, c, lanemember, lbigoff, bigmember, wbase, pairs, walls);
+            parent[t] = root;
+            isize[t] = sz;
+        }
+        __syncthreads();
+        for (int k = 0; k < cnt; k++) cdata[off + k].local = (int)lloc[partner(k)];
+        return;
+    }
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS) uf_hook_one(a, alist, ccount, prefix, cand, aidx, parent);
     __syncthreads();
@@ -1437,10 +1556,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS) {
         if (parent[a] != a) continue;
-        uint32_t sz = isize[a];
-        uint32_t cls = sz <= WAVE ? sz : WAVE + 1;
-        if (cls <= 2 && island_touching<D>(a, cls, A, c, alist, ccount, prefix, cand))
-            cls = cls == 2 ? CLS_PAIR : CLS_WALL;
+        const uint32_t cls = island_class(isize[a], irank[a]);
         uint32_t r = atomicAdd(&ccls[cls], 1u);
         irank[a] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
         if (cls == WAVE + 1) bigroot[r] = a;
@@ -1471,7 +1587,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         island_place_one(a, c, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, pairs, walls);
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
-        cand_prep_one<D>(a, A, c, alist, ccount, prefix, cand, aidx, loc, cdata, md);
+        cand_place_one(a, alist, ccount, prefix, cand, aidx, loc, cdata);
 }
 
 // ---------------------------------------------------------------------------
@@ -3585,32 +3701,31 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
                        b.keys_sorted, b.drho_i, b.j_i, b.srec, b.fc, b.actcc, b.bsum64, b.counters, b.flags,
                        b.hcnt);
     // block offsets and the totals (candidates, active) -> counters[0..1]
-    if ((long long)nb256(np) <= RAW_MAX_BLOCKS) {
-        hipLaunchKernelGGL((k_collect<D, true>), dim3(nb256(np)), dim3(256), 0, s, b.A, np, c, b.start, b.pos4,
-                           b.keys_sorted, b.actcc, b.bsum64, b.prefix, b.alist, b.aidx, b.cand, b.ccount, b.parent,
-                           b.isize, b.fill, b.counters);
-    } else {
+    const bool raw = (long long)nb256(np) <= RAW_MAX_BLOCKS;
+    if (!raw)
         hipLaunchKernelGGL((k_scan_top<unsigned long long>), dim3(1), dim3(TOP_THREADS), 0, s, b.bsum64,
                            (long long)nb256(np), (unsigned long long*)(void*)b.counters);
-        hipLaunchKernelGGL((k_collect<D, false>), dim3(nb256(np)), dim3(256), 0, s, b.A, np, c, b.start, b.pos4,
-                           b.keys_sorted, b.actcc, b.bsum64, b.prefix, b.alist, b.aidx, b.cand, b.ccount, b.parent,
-                           b.isize, b.fill, b.counters);
-    }
+    auto collect = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb256(np)), dim3(256), 0, s, b.A, np, c, b.start, b.pos4, b.keys_sorted,
+                           b.actcc, b.bsum64, b.prefix, b.alist, b.aidx, b.cand, b.ccount, b.parent, b.isize, b.irank,
+                           b.fill, b.cdata, md, b.counters);
+    };
+    if (one_group) collect(raw ? &k_collect<D, true, true> : &k_collect<D, false, true>);
+    else collect(raw ? &k_collect<D, true, false> : &k_collect<D, false, false>);
     if (one_group) {
-        hipLaunchKernelGGL(k_island_setup<D>, dim3(1), dim3(SETUP_THREADS), 0, s, b.A, c, b.alist, b.ccount, b.prefix,
+        hipLaunchKernelGGL(k_island_setup, dim3(1), dim3(SETUP_THREADS), 0, s, c, b.alist, b.ccount, b.prefix,
                            b.cand, b.aidx, b.parent, b.isize, b.irank, b.fill, b.lanemember, b.loc, b.bigroot,
-                           b.bigoff, b.bigmember, b.cdata, md, b.counters, b.lane_cap);
+                           b.bigoff, b.bigmember, b.cdata, b.counters);
     } else {
-        hipLaunchKernelGGL(k_uf_hook, dim3(grid_act), dim3(256), 0, s, b.alist, b.ccount, b.prefix, b.cand, b.aidx, b.parent,
-                           b.counters);
+        hipLaunchKernelGGL(k_uf_hook<D>, dim3(8 * grid_act), dim3(64), 0, s, b.A, c, b.alist, b.ccount, b.prefix, b.cand,
+                           b.aidx, b.parent, b.irank, b.cdata, md, b.counters);
         hipLaunchKernelGGL(k_uf_flatten, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.counters);
-        hipLaunchKernelGGL(k_island_class<D>, dim3(grid_act), dim3(256), 0, s, b.A, c, b.alist, b.ccount, b.prefix,
-                           b.cand, b.parent, b.isize, b.irank, b.bigroot,
+        hipLaunchKernelGGL(k_island_class, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.irank, b.bigroot,
                            b.counters);
         hipLaunchKernelGGL(k_island_place, dim3(grid_act), dim3(256), 0, s, c, b.parent, b.isize, b.irank, b.fill,
                            b.lanemember, b.loc, b.bigoff, b.bigmember, b.bigroot, b.counters);
-        hipLaunchKernelGGL(k_cand_prep<D>, dim3(grid_act), dim3(256), 0, s, b.A, c, b.alist, b.ccount, b.prefix, b.cand,
-                           b.aidx, b.loc, b.cdata, md, b.counters);
+        hipLaunchKernelGGL(k_cand_place, dim3(grid_act), dim3(256), 0, s, b.alist, b.ccount, b.prefix, b.cand,
+                           b.aidx, b.loc, b.cdata, b.counters);
     }
     // (a workgroup per packed wave, four per wave of islands of one or two without Mindlin)
     const dim3 gsmall(std::max<unsigned>(grid_act * 4, 256u));
