@@ -329,6 +329,101 @@ __global__ __launch_bounds__(256) void k_reorder(PState A, PState B, const uint3
     pos4[o] = make_float4(A.xh[0][s], A.xh[1][s], D == 3 ? A.xh[2][s] : 0.f, A.d[s]);
 }
 
+// The cell list of few particles in one launch instead of five: the first
+// workgroup ranks them by (bin, id) and moves them, every other one counts
+// those of its stretch of the bins in LDS and writes the starts.  Launches
+// of 1.4 to 4 us each are all that a step of few particles consists of: one
+// particle in 10 x 10 x 50 12.4 -> 4.5 us a step, 200 disks in 128^2 13.5 -> 5.5
+// us.  The ranks cost one pass over all particles each, hence the limit.
+constexpr int CELLS_FEW = 512;
+constexpr int CELLS_BINS = 8 * CELLS_FEW;          // bins of a workgroup
+template <int D>
+__global__ __launch_bounds__(CELLS_FEW) void k_cells_few(PState A, PState B, int np, PCfg c,
+                                                         uint32_t* __restrict__ start,
+                                                         uint32_t* __restrict__ keys_sorted,
+                                                         float4* __restrict__ pos4, uint32_t* __restrict__ flags) {
+    __shared__ ulonglong2 order[CELLS_FEW / 2];
+    __shared__ uint32_t hist[CELLS_BINS];
+    __shared__ uint32_t sh[CELLS_FEW / WAVE];
+    const int t = threadIdx.x;
+    const bool on = t < np, move = blockIdx.x == 0;
+    uint32_t key = 0;
+    int id = 0;
+    float xh[3] = {0.f, 0.f, 0.f}, xl[3] = {0.f, 0.f, 0.f}, u[3], d = 0.f, rp = 0.f;
+    bool inside = true;
+    if (on) {
+        int b[3] = {0, 0, 0};
+#pragma unroll
+        for (int a = 0; a < D; a++) {
+            xh[a] = A.xh[a][t];
+            xl[a] = A.xl[a][t];
+        }
+        if (move) {
+            id = A.id[t];
+            d = A.d[t];
+            rp = A.rp[t];
+#pragma unroll
+            for (int a = 0; a < D; a++) u[a] = A.u[a][t];
+        }
+#pragma unroll
+        for (int a = 0; a < D; a++) {
+            inside = inside && (xh[a] > 0.0f) && (xh[a] < (float)c.n[a]) && isfinite(xh[a]);
+            b[a] = bin_of(c, xh[a], xl[a], a);
+        }
+        key = (uint32_t)(((long long)b[2] * c.nb[1] + b[1]) * c.nb[0] + b[0]);
+    }
+    if (move) {
+        // rank by (bin, id): the particles that come before
+        const unsigned long long mine = on ? ((unsigned long long)key << 32) | (uint32_t)id : ~0ULL;
+        ((unsigned long long*)order)[t] = mine;
+        __syncthreads();
+        if (!on) return;
+        if (!inside) atomicOr(flags, FLAG_UNSTABLE);
+        uint32_t o = 0;
+#pragma unroll 4
+        for (int j = 0; j < (np + 1) / 2; j++) {       // (past np: after all)
+            const ulonglong2 two = order[j];
+            o += (two.x < mine ? 1u : 0u) + (two.y < mine ? 1u : 0u);
+        }
+#pragma unroll
+        for (int a = 0; a < D; a++) {
+            B.xh[a][o] = xh[a];
+            B.xl[a][o] = xl[a];
+            B.u[a][o] = u[a];
+        }
+        B.d[o] = d;
+        B.rp[o] = rp;
+        B.id[o] = id;
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+            if (A.w[a]) B.w[a][o] = A.w[a][t];
+        if (A.fixa) B.fixa[o] = A.fixa[t];
+        keys_sorted[o] = key;
+        pos4[o] = make_float4(xh[0], xh[1], D == 3 ? xh[2] : 0.f, d);
+        return;
+    }
+    const long long first = (long long)(blockIdx.x - 1) * CELLS_BINS;
+    constexpr int PER = CELLS_BINS / CELLS_FEW;
+#pragma unroll
+    for (int k = 0; k < PER; k++) hist[k * CELLS_FEW + t] = 0u;
+    const uint32_t before = (uint32_t)__syncthreads_count(on && key < first);
+    if (on && key >= first && key < first + CELLS_BINS) atomicAdd(&hist[key - first], 1u);
+    __syncthreads();
+    uint32_t v[PER], sum = 0, all;
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        v[k] = hist[t * PER + k];
+        sum += v[k];
+    }
+    uint32_t run = block_exclusive_scan<uint32_t, CELLS_FEW / WAVE>(sum, sh, all) + before;
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const long long bin = first + t * PER + k;
+        if (bin <= c.nbins) start[bin] = run;
+        run += v[k];
+    }
+}
+
 // The sort of a state in no spatial order (just handed over, id order) sends
 // every particle to a place of its own, where a scattered 4-byte store costs
 // a memory line: 13 of them a particle.  From RECORD_MIN particles on, each
@@ -3599,6 +3694,12 @@ static inline unsigned nb256(long long n) { return (unsigned)((n + 255) / 256 > 
 
 template <int D>
 static void sort_impl(PBuf& b, int np, const PCfg& c, bool unordered, hipStream_t s) {
+    if (np <= CELLS_FEW) {
+        hipLaunchKernelGGL(k_cells_few<D>, dim3((unsigned)(c.nbins / CELLS_BINS + 2)), dim3(CELLS_FEW), 0, s, b.A, b.B,
+                           np, c, b.start, b.keys_sorted, b.pos4, b.flags);
+        std::swap(b.A, b.B);
+        return;
+    }
     // the bin counts are zero here: cleared at creation and by the scan of
     // the previous sort
     hipLaunchKernelGGL(k_bin_count<D>, dim3(nb256(np)), dim3(256), 0, s, b.A, np, c, b.cnt, b.keys, b.slot, b.flags);
@@ -3744,14 +3845,14 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
         hipLaunchKernelGGL((k_island_small<D, true>), gsmall, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
                            b.ccount, b.prefix, b.parent, b.isize, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags,
                            b.counters, md);
-        hipLaunchKernelGGL((k_island_big<D, true>), dim3(256), dim3(256), 0, s, b.A, b.Bn, np, c, b.bigmember,
+        if (np > WAVE) hipLaunchKernelGGL((k_island_big<D, true>), dim3(256), dim3(256), 0, s, b.A, b.Bn, np, c, b.bigmember,
                            b.bigoff, b.bigroot, b.isize, b.alist, b.ccount, b.prefix, b.cdata, b.drho_i, b.j_i,
                            b.srec, b.fc, b.gdx, b.gu, (long long)np, b.flags, b.counters, md);
     } else {
         hipLaunchKernelGGL((k_island_small<D, false>), gsplit, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
                            b.ccount, b.prefix, b.parent, b.isize, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags,
                            b.counters, md);
-        hipLaunchKernelGGL((k_island_big<D, false>), dim3(256), dim3(256), 0, s, b.A, b.Bn, np, c, b.bigmember,
+        if (np > WAVE) hipLaunchKernelGGL((k_island_big<D, false>), dim3(256), dim3(256), 0, s, b.A, b.Bn, np, c, b.bigmember,
                            b.bigoff, b.bigroot, b.isize, b.alist, b.ccount, b.prefix, b.cdata, b.drho_i, b.j_i,
                            b.srec, b.fc, b.gdx, b.gu, (long long)np, b.flags, b.counters, md);
     }
