@@ -2857,6 +2857,106 @@ __device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid,
     if (NC && valid) md_state_store(md.cmd + P.off, md.cms + 2 * P.off, !FLAT && c.microslip, S, kt8r);
 }
 
+// All sub-steps of Hertz-Mindlin islands of three to sixteen particles, each
+// member with at most four candidates, no-slip contacts and no wall in reach:
+// four lanes per member, each working one of its contacts (candidate and
+// tangential force in registers) on a copy of the member's state; the partner's
+// state by a lane shuffle, the contacts' forces added over the quad in the
+// order of the candidates.  `lane0`: the packed lane of the first member.  In
+// the general loop a sub-step of three particles in a row was the serial chain
+// of two contacts, their states read from and written to LDS, and three
+// barriers: 1.6 us; here it is one contact, 0.6 us (64^3 with 40 touching
+// pairs, one of them close to a third particle: 31.2 -> 11.7 ms).  The lanes a shuffle reads
+// from belong to the reading lane's own island, which takes the same branches.
+template <int D>
+__device__ __forceinline__ void md_multi(Active<D>& P, const PCfg& c, bool valid, const CandData& cd, int lane0,
+                                         int isz, const MdBuf& md) {
+    if (!valid) P = Active<D>{};
+    const int lane = threadIdx.x, kc = lane & 3;
+    const bool has = valid && kc < P.cnt;
+    const int partner = has ? (cd.local - lane0) * 4 + kc : lane;
+    const int base = ((lane >> 2) / isz) * isz * 4;          // the island's first lane
+    const float oveq = __shfl(P.veq, partner);
+    float S[TSN], kt8r = 0.f;
+#pragma unroll
+    for (int q = 0; q < TSN; q++) S[q] = 0.f;
+    if (has) kt8r = md_state_load(md.cmd + P.off + kc, md.cms + 2 * (P.off + kc), false, S);
+    auto fetch = [&](float* odx, float* ou) {
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            odx[a] = a < D ? __shfl(P.dx[a], partner) : 0.f;
+            ou[a] = a < D ? __shfl(P.u[a], partner) : 0.f;
+        }
+    };
+    auto quad_sum = [](float v) { return ((quad_get<0>(v) + quad_get<1>(v)) + quad_get<2>(v)) + quad_get<3>(v); };
+    auto substep = [&]() {
+        float F[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};
+        float odx[3], ou[3], ow[3];
+        fetch(odx, ou);
+#pragma unroll
+        for (int a = 0; a < 3; a++) ow[a] = (D == 3 || a == 2) ? __shfl(P.W[a], partner) : 0.f;
+        pair_contact_flat<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            F[a] = quad_sum(has ? F[a] : 0.f);
+            tq[a] = quad_sum(has ? tq[a] : 0.f);
+            S[a] = has ? S[a] : 0.f;
+        }
+        substep_update<D, true>(P, c, F, tq);
+    };
+    // the loop of split_wave: each island on its own trip count
+    int k = 0, backoff = 1, trip = 0;
+    while (__any(valid && k < c.n_sub)) {
+        bool more, check;
+        int m;
+        for (;;) {
+            more = valid && k < c.n_sub;
+            check = more && (trip & (backoff - 1)) == 0;
+            m = 0;
+            if (__any(check)) {
+                float odx[3], ou[3];
+                fetch(odx, ou);
+                int allow = c.n_sub - k;
+                if (check && has) allow = free_allowance_one<D>(P, c, cd, odx, ou, oveq, c.n_sub - k);
+                int low = allow;
+                for (int i = 0; i < 4 * isz; i++) low = min(low, __shfl(allow, base + i));
+                m = check ? low : 0;
+            }
+            const bool jump = more && m >= 2;
+            if (!__any(jump)) break;
+            if (jump) {
+                // no contact along the stretch: every tangential force lapses
+#pragma unroll
+                for (int a = 0; a < 3; a++)
+#pragma unroll
+                    for (int q = 0; q < TSN; q++) P.wT[a][q] = 0.f;
+#pragma unroll
+                for (int q = 0; q < TSN; q++) S[q] = 0.f;
+                active_jump<D, false>(P, c, m, md);
+                k += m;
+                backoff = 1;
+                trip += 1;
+            }
+        }
+        if (more) {
+            substep();
+            k += 1;
+            trip += 1;
+            if (check) backoff = min(2 * backoff, 64);
+        }
+        // plain sub-steps up to the next check of any island or its end
+        const bool run = valid && k < c.n_sub;
+        int T = __ockl_wfred_min_i32(run ? min((-trip) & (backoff - 1), c.n_sub - k) : INT_MAX);
+        if (T == INT_MAX) T = 0;
+        if (run) {
+            for (int t = 0; t < T; t++) substep();
+            k += T;
+            trip += T;
+        }
+    }
+    if (has) md_state_store(md.cmd + P.off + kc, md.cms + 2 * (P.off + kc), false, S, kt8r);
+}
+
 template <int D, bool MD>
 __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np, PCfg c,
                                                      const int* __restrict__ lanemember,
@@ -2888,14 +2988,15 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     // takes the islands of one or two at its lanes [16 q, 16 q + 16) in the
     // split form (or in the general loop below, restricted to those lanes,
     // when one of them does not qualify); a wave of larger islands is worked
-    // by quarter 0 alone.
-    constexpr uint32_t QUARTERS = MD ? 1u : 4u;
+    // by quarter 0 alone.  With Mindlin, part p of eight takes islands of three
+    // to sixteen, as many as fill 16 lanes, with four lanes per member (md_multi).
+    constexpr uint32_t QUARTERS = MD ? 8u : 4u;
     const uint32_t nt = tp.groups + tw.groups;
     for (uint32_t v = blockIdx.x; v < nt + nw * QUARTERS; v += gridDim.x) {
         // islands of size sz at lanes [lane0, lane0 + nl) of the entries from `member`
         int sz, lane0 = 0, nl;
         const int* member;
-        bool split = !MD;
+        bool split = !MD, multi = false;
         if (v < nt) {
             sz = v < tp.groups ? 2 : 1;
             const uint32_t i0 = sz == 2 ? v * tp.per : (v - tp.groups) * tw.per;
@@ -2912,7 +3013,14 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
             member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
             split = split && sz <= 2;
-            if (!split && part != 0) continue;
+            multi = MD && !c.microslip && sz >= 3 && sz <= 16;
+            if (!split && !multi && part != 0) continue;
+            if (multi) {
+                const int take = 16 / sz * sz;
+                lane0 = (int)part * take;
+                nl = min(nl - lane0, take);
+                if (nl <= 0) continue;
+            }
             if (split) {
                 lane0 = (int)part * 16;
                 nl = min(nl - lane0, 16);
@@ -2945,6 +3053,25 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 }
                 if (sv && (lane & 3) == 0) active_store<D, MD>(P, Bn, c, ss, np, srec, fc, flags, md);
                 continue;
+            }
+        }
+        if constexpr (MD) {
+            if (multi) {
+                const int ol = lane0 + (lane >> 2), kc = lane & 3;
+                const bool sv = ol < lane0 + nl;
+                const uint32_t ss = sv ? alist[member[ol]] : 0;
+                Active<D> P;
+                CandData cd{};
+                if (sv) {
+                    active_load<D, MD>(P, A, c, ss, drho_i, j_i, np, ccount, prefix, md);
+                    if (kc < P.cnt) cd = cdata[P.off + kc];
+                }
+                if (__all(!sv || (P.cnt >= 1 && P.cnt <= 4 && !P.fixed && !P.wall))) {
+                    md_multi<D>(P, c, sv, cd, lane0, sz, md);
+                    __syncthreads();                 // (the contacts' states, for the history)
+                    if (sv && kc == 0) active_store<D, MD>(P, Bn, c, ss, np, srec, fc, flags, md);
+                    continue;
+                }
             }
         }
         // the general loop: the whole wave, or this workgroup's lanes of it
@@ -3842,7 +3969,7 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
     const dim3 gsmall(std::max<unsigned>(grid_act * 4, 256u));
     const dim3 gsplit(4 * gsmall.x);
     if (c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) {
-        hipLaunchKernelGGL((k_island_small<D, true>), gsmall, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
+        hipLaunchKernelGGL((k_island_small<D, true>), gsplit, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
                            b.ccount, b.prefix, b.parent, b.isize, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags,
                            b.counters, md);
         if (np > WAVE) hipLaunchKernelGGL((k_island_big<D, true>), dim3(256), dim3(256), 0, s, b.A, b.Bn, np, c, b.bigmember,
