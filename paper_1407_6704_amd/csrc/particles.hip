@@ -2764,15 +2764,11 @@ __device__ __forceinline__ int pair_swap(int v) { return __builtin_amdgcn_mov_dp
 // lanes: the candidate and the contacts' tangential state in registers, the
 // partner's state by a lane swap.  The decisions and arithmetic of the
 // general island loop, which reads and writes the tangential state in LDS
-// on every sub-step.  A serial chain bound by the issue of one wave: FLAT
-// (NC = 1: no-slip contacts and no wall in reach), a sub-step is 182
-// straight-line instructions, 0.3 us.  64^3 with 40 touching pairs, 6 steps of
-// 3109 sub-steps: 24.2 ms with every state in global memory and the general
-// loop for all islands, 11.9 ms now (what is left is an island of three in
-// the general loop, 0.6 us a sub-step, 1.2 us before).  The lanes a swap reads
-// from belong to the reading lane's own island, which takes the same
-// branches, so they are active whenever the reader is.
-template <int D, int NC, bool FLAT>
+// on every sub-step.  For the islands that k_island_quads leaves: walls in
+// reach, micro-slip.  The lanes a swap reads from belong to the reading lane's
+// own island, which takes the same branches, so they are active whenever the
+// reader is.
+template <int D, int NC>
 __device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid, const CandData& cd,
                                         const MdBuf& md) {
     if (!valid) P = Active<D>{};      // padding lanes: a zero state, never stored
@@ -2780,7 +2776,7 @@ __device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid,
     float S[TSN], kt8r = 0.f;
 #pragma unroll
     for (int q = 0; q < TSN; q++) S[q] = 0.f;
-    if (NC && valid) kt8r = md_state_load(md.cmd + P.off, md.cms + 2 * P.off, !FLAT && c.microslip, S);
+    if (NC && valid) kt8r = md_state_load(md.cmd + P.off, md.cms + 2 * P.off, c.microslip, S);
     auto partner = [&](float* odx, float* ou) {
 #pragma unroll
         for (int a = 0; a < 3; a++) {
@@ -2794,12 +2790,8 @@ __device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid,
         partner(odx, ou);
 #pragma unroll
         for (int a = 0; a < 3; a++) ow[a] = NC && (D == 3 || a == 2) ? pair_swap(P.W[a]) : 0.f;
-        if (FLAT) {
-            pair_contact_flat<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
-        } else {
-            if (P.wall) wall_force_md<D>(P, c, F, tq);
-            if (NC) pair_contact_md<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
-        }
+        if (P.wall) wall_force_md<D>(P, c, F, tq);
+        if (NC) pair_contact_md<D>(P, cd, kt8r, S, odx, ou, ow, c, F, tq);
         substep_update<D, true>(P, c, F, tq);
     };
     // the loop of split_wave: each island on its own trip count
@@ -2854,7 +2846,173 @@ __device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid,
             trip += T;
         }
     }
-    if (NC && valid) md_state_store(md.cmd + P.off, md.cms + 2 * P.off, !FLAT && c.microslip, S, kt8r);
+    if (NC && valid) md_state_store(md.cmd + P.off, md.cms + 2 * P.off, c.microslip, S, kt8r);
+}
+
+// The value of the lane's next axis, and of the one after (lane 3 of a quad
+// repeats axis 2).
+__device__ __forceinline__ float quad_next(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x09, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float quad_after(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x52, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float quad_dot(float a, float b) {
+    const float p = a * b;
+    return (quad_get<0>(p) + quad_get<1>(p)) + quad_get<2>(p);
+}
+
+// All sub-steps of a wave of Hertz-Mindlin islands of two, no-slip contacts
+// and no wall in reach, in the split form of split_wave: lane l of a quad
+// holds axis min(l & 3, 2) of its particle's displacement, velocity, spin and
+// tangential force (in 2D the third axis carries the spin; the others' third
+// components stay zero).  A sub-step is a serial chain of one wave: 0.25 us,
+// where one lane per particle took 0.57; 64^3 with 40 touching pairs, 6 steps
+// of 3109 sub-steps, 11.3 -> 5.4 ms.  The contact point velocity as
+// du - (R W + R' W') x n.
+//
+// ROWS: islands of three to eight particles, each with at most two candidates:
+// a quad per contact, those of a member eight lanes apart (md_row_lane) with a
+// copy of its state each and their contacts' forces added; the partner's state
+// by a lane shuffle, 0.39 us a sub-step.  `lane0`: the packed lane of the first
+// member, isz: the island's size.
+__device__ __forceinline__ int md_row_lane(int member) { return (member >> 1) * 16 + (member & 1) * 4; }
+template <int D, bool ROWS>
+__device__ __forceinline__ void md_quad_wave(Active<D>& P, const PCfg& c, bool valid, const CandData& cd,
+                                             const MdBuf& md, int lane0 = 0, int isz = 2) {
+    const int ax = min((int)(threadIdx.x & 3u), 2);
+    if (!valid) P = Active<D>{};      // padding lanes: a zero state, never stored
+    const int lane = threadIdx.x, kc = ROWS ? (lane >> 3) & 1 : 0;
+    const bool has = valid && kc < P.cnt;
+    const int partner = ROWS && has ? md_row_lane(cd.local - lane0) + (lane & 11) : lane;
+    const int first = ((((lane >> 4) << 1) | ((lane >> 2) & 1)) / isz) * isz;       // the island's first member
+    auto other = [&](float v) { return ROWS ? __shfl(v, partner) : row_swap8(v); };
+    auto both = [&](float v) { return ROWS ? v + row_swap8(v) : v; };
+    const float oveq = other(P.veq);
+    float u = pick3(P.u, ax), cu = pick3(P.cu, ax), dx = pick3(P.dx, ax), cdx = pick3(P.cdx, ax);
+    float gs = pick3(P.gs, ax), fs = pick3(P.fs, ax), W = pick3(P.W, ax);
+    const float j = pick3(P.j, ax), hbw = pick3(P.hbw, ax), r0 = pick3(cd.r0, ax);
+    float kt8r = 0.f, T = 0.f;
+    if (has) {
+        float S[TSN];
+        kt8r = md_state_load(md.cmd + P.off + kc, md.cms + 2 * (P.off + kc), false, S);
+        T = pick3(S, ax);
+    }
+    const float Ro = cd.rc - P.R, kth = kt8r * c.h;
+    float vm = P.vmax2;
+    auto substep = [&]() {
+        float del[3], r[3], inv, delta;
+        const float dl = dx - other(dx);
+        quad_gather<3>(dl, del);
+        const bool on = pair_geom<3, true>(cd, del, r, inv, delta) && (!ROWS || has);
+        const float n = (r0 + dl) * inv, n1 = quad_next(n), n2 = quad_after(n);
+        const float om = P.R * W + Ro * other(W);
+        const float v = (u - other(u)) - (quad_next(om) * n2 - quad_after(om) * n1);
+        const float sd = sqrt_fast(delta);
+        const float Fn = cd.gam * delta * sd;
+        // the tangential force turned into the contact plane, its length kept
+        const float old2 = quad_dot(T, T);
+        float Pl = T - quad_dot(T, n) * n;
+        const float pl2 = quad_dot(Pl, Pl);
+        Pl *= pl2 > 0.f ? sqrt_fast(old2) * rsq_fast(pl2) : 0.f;
+        // its elastic increment, and the Coulomb limit
+        Pl -= (kth * sd) * (v - quad_dot(v, n) * n);
+        const float tl2 = quad_dot(Pl, Pl);
+        const float lim = c.mu * Fn;
+        Pl *= tl2 > lim * lim ? lim * rsq_fast(tl2) : 1.0f;
+        T = on ? Pl : 0.f;
+        const float tq = -P.R * (n1 * quad_after(T) - n2 * quad_next(T));
+        W += both(on ? tq * P.hI : 0.f);
+        const float F = both(on ? Fn * n + T : 0.f);
+        axis_update<D>(P, c, F, j, hbw, u, cu, dx, cdx, gs, fs);
+        vm = fmaxf(vm, quad_dot(u, u));
+    };
+    // the loop of split_wave: each island on its own trip count
+    int k = 0, backoff = 1, trip = 0;
+    while (__any(valid && k < c.n_sub)) {
+        bool more, check;
+        int m;
+        for (;;) {
+            more = valid && k < c.n_sub;
+            check = more && (trip & (backoff - 1)) == 0;
+            m = 0;
+            if (__any(check)) {
+                Active<D> Q = P;
+                quad_gather<D>(u, Q.u);
+                quad_gather<D>(cu, Q.cu);
+                quad_gather<D>(dx, Q.dx);
+                float odx[3] = {0.f, 0.f, 0.f}, ou[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+                for (int a = 0; a < D; a++) {
+                    odx[a] = other(Q.dx[a]);
+                    ou[a] = other(Q.u[a]);
+                }
+                int allow = c.n_sub - k;
+                if (check && has) allow = free_allowance_one<D>(Q, c, cd, odx, ou, oveq, c.n_sub - k);
+                allow = min(allow, row_swap8(allow));
+                if (ROWS) {
+                    int low = allow;
+                    for (int i = 0; i < isz; i++) low = min(low, __shfl(allow, md_row_lane(first + i)));
+                    allow = low;
+                }
+                m = check ? allow : 0;
+            }
+            const bool jump = more && m >= 2;
+            if (!__any(jump)) break;
+            if (jump) {
+                // no contact along the stretch: every tangential force lapses
+                T = 0.f;
+#pragma unroll
+                for (int a = 0; a < 3; a++)
+#pragma unroll
+                    for (int q = 0; q < TSN; q++) P.wT[a][q] = 0.f;
+                quad_gather<D>(u, P.u);
+                quad_gather<D>(cu, P.cu);
+                quad_gather<D>(dx, P.dx);
+                quad_gather<D>(cdx, P.cdx);
+                quad_gather<D>(gs, P.gs);
+                P.vmax2 = vm;
+                active_jump<D, false>(P, c, m, md);
+                vm = P.vmax2;
+                if (D == 3 || ax < 2) {
+                    u = pick3(P.u, ax);
+                    cu = pick3(P.cu, ax);
+                    dx = pick3(P.dx, ax);
+                    cdx = pick3(P.cdx, ax);
+                    gs = pick3(P.gs, ax);
+                }
+                k += m;
+                backoff = 1;
+                trip += 1;
+            }
+        }
+        if (more) {
+            substep();
+            k += 1;
+            trip += 1;
+            if (check) backoff = min(2 * backoff, 64);
+        }
+        // plain sub-steps up to the next check of any island or its end
+        const bool run = valid && k < c.n_sub;
+        int t1 = __ockl_wfred_min_i32(run ? min((-trip) & (backoff - 1), c.n_sub - k) : INT_MAX);
+        if (t1 == INT_MAX) t1 = 0;
+        if (run) {
+            for (int t = 0; t < t1; t++) substep();
+            k += t1;
+            trip += t1;
+        }
+    }
+    P.vmax2 = vm;
+    quad_gather<D>(u, P.u);
+    quad_gather<D>(cu, P.cu);
+    quad_gather<D>(dx, P.dx);
+    quad_gather<D>(cdx, P.cdx);
+    quad_gather<D>(gs, P.gs);
+    quad_gather<D>(fs, P.fs);
+    quad_gather<3>(W, P.W);
+    float S[TSN] = {};
+    quad_gather<3>(T, S);
+    if (has && (lane & 3) == 0) md_state_store(md.cmd + P.off + kc, md.cms + 2 * (P.off + kc), false, S, kt8r);
 }
 
 // All sub-steps of Hertz-Mindlin islands of three to sixteen particles, each
@@ -2865,9 +3023,8 @@ __device__ __forceinline__ void md_wave(Active<D>& P, const PCfg& c, bool valid,
 // order of the candidates.  `lane0`: the packed lane of the first member.  In
 // the general loop a sub-step of three particles in a row was the serial chain
 // of two contacts, their states read from and written to LDS, and three
-// barriers: 1.6 us; here it is one contact, 0.6 us (64^3 with 40 touching
-// pairs, one of them close to a third particle: 31.2 -> 11.7 ms).  The lanes a shuffle reads
-// from belong to the reading lane's own island, which takes the same branches.
+// barriers: 1.6 us; so it is 0.6 us.  The lanes a shuffle reads from belong to
+// the reading lane's own island, which takes the same branches.
 template <int D>
 __device__ __forceinline__ void md_multi(Active<D>& P, const PCfg& c, bool valid, const CandData& cd, int lane0,
                                          int isz, const MdBuf& md) {
@@ -2957,6 +3114,111 @@ __device__ __forceinline__ void md_multi(Active<D>& P, const PCfg& c, bool valid
     if (has) md_state_store(md.cmd + P.off + kc, md.cms + 2 * (P.off + kc), false, S, kt8r);
 }
 
+// Parts of a packed wave of no-slip Hertz-Mindlin islands of two to sixteen:
+// the pairs of 16 lanes, or as many larger islands as have eight members (one,
+// if it has more); at most MD_PARTS to a wave.
+constexpr uint32_t MD_PARTS = 16;
+__device__ __forceinline__ int md_take(int sz) { return sz == 2 ? 16 : (sz <= 8 ? 8 / sz * sz : sz); }
+
+// The form that a part qualifies for: none (the general loop), pairs, at most
+// two or at most four candidates per member; never with a wall in reach or a
+// fixed point.
+enum : int { MD_GENERAL = 0, MD_PAIRS = 1, MD_TWO = 2, MD_FOUR = 3 };
+template <int D>
+__device__ __forceinline__ int md_form(int sz, int lane0, int nl, const int* __restrict__ member, const PState& A,
+                                       const PCfg& c, const uint32_t* __restrict__ alist,
+                                       const uint32_t* __restrict__ ccount,
+                                       const unsigned long long* __restrict__ prefix,
+                                       const CandData* __restrict__ cdata) {
+    if (sz < 2 || sz > 16) return MD_GENERAL;
+    const int lane = threadIdx.x;
+    const bool on = lane < nl;
+    int cnt = 1;
+    bool ok = true;
+    if (on) {
+        const uint32_t s = alist[member[lane0 + lane]];
+        cnt = (int)ccount[s];
+        ok = cnt >= 1 && !(A.fixa && A.fixa[s] > 0.f);
+        const float r = 0.5f * A.d[s] + c.skin;
+#pragma unroll
+        for (int a = 0; a < D; a++) {
+            const float x = A.xh[a][s] + A.xl[a][s];
+            ok = ok && !(x < r) && !((float)c.n[a] - x < r);
+        }
+        if (ok && sz == 2)
+            ok = cnt == 1 && cdata[(uint32_t)(prefix[s] & 0xffffffffULL)].local == ((lane0 + lane) ^ 1);
+    }
+    if (!__all(ok)) return MD_GENERAL;
+    if (sz == 2) return MD_PAIRS;
+    if (sz <= 8 && __all(cnt <= 2)) return MD_TWO;
+    return __all(cnt <= 4) ? MD_FOUR : MD_GENERAL;
+}
+
+// The no-slip Hertz-Mindlin islands of two to sixteen that qualify (md_form).
+// A kernel of its own: in one with the general loop their registers spilled,
+// 64^3 with 40 touching pairs 6.2 instead of 5.4 ms.  With a third particle in
+// reach of one pair: 31.2 ms in the general loop, 11.7 by md_multi, 7.7 now.
+template <int D>
+__global__ __launch_bounds__(64) void k_island_quads(PState A, PState Bn, int np, PCfg c,
+                                                     const int* __restrict__ lanemember,
+                                                     const uint32_t* __restrict__ alist,
+                                                     const uint32_t* __restrict__ ccount,
+                                                     const unsigned long long* __restrict__ prefix,
+                                                     const CandData* __restrict__ cdata,
+                                                     const float* __restrict__ drho_i, const float* __restrict__ j_i,
+                                                     float* __restrict__ srec, float* __restrict__ fc,
+                                                     uint32_t* __restrict__ flags,
+                                                     const uint32_t* __restrict__ counters, MdBuf md) {
+    const uint32_t nw = counters[CNT_WAVES];
+    const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
+    const TouchPlan tp = touch_plan(pairs, 2, c);
+    const int lane = threadIdx.x;
+    const uint32_t wb_lane = counters[CNT_WAVEBASE + 1 + lane];
+    for (uint32_t v = blockIdx.x; v < tp.groups + nw * MD_PARTS; v += gridDim.x) {
+        int sz = 2, lane0 = 0, nl;
+        const int* member;
+        if (v < tp.groups) {
+            const uint32_t i0 = v * tp.per;
+            nl = 2 * (int)min(tp.per, pairs - i0);
+            member = lanemember + 2 * i0;
+        } else {
+            const uint32_t w = (v - tp.groups) / MD_PARTS, part = (v - tp.groups) % MD_PARTS;
+            const unsigned long long le = __ballot(wb_lane <= w);
+            sz = 64 - __clzll(le);
+            if (sz < 2 || sz > 16) continue;
+            const uint32_t per = WAVE / sz;
+            const uint32_t idx = w - counters[CNT_WAVEBASE + sz];
+            nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
+            member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
+            const int take = md_take(sz);
+            lane0 = (int)part * take;
+            nl = min(nl - lane0, take);
+            if (nl <= 0) continue;
+        }
+        const int form = md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata);
+        if (form == MD_GENERAL) continue;
+        // this lane's member and contact
+        int mi, kc = 0;
+        if (form == MD_PAIRS) mi = ((lane >> 4) << 2) | (((lane >> 2) & 1) << 1) | ((lane >> 3) & 1);
+        else if (form == MD_TWO) mi = ((lane >> 4) << 1) | ((lane >> 2) & 1), kc = (lane >> 3) & 1;
+        else mi = lane >> 2, kc = lane & 3;
+        const bool sv = mi < nl;
+        const uint32_t ss = sv ? alist[member[lane0 + mi]] : 0;
+        Active<D> P;
+        CandData cd{};
+        if (sv) {
+            active_load<D, true>(P, A, c, ss, drho_i, j_i, np, ccount, prefix, md);
+            if (kc < P.cnt) cd = cdata[P.off + kc];
+        }
+        if (form == MD_PAIRS) md_quad_wave<D, false>(P, c, sv, cd, md);
+        else if (form == MD_TWO) md_quad_wave<D, true>(P, c, sv, cd, md, lane0, sz);
+        else md_multi<D>(P, c, sv, cd, lane0, sz, md);
+        __syncthreads();                             // (the contacts' states, for the history)
+        if (sv && kc == 0 && (form == MD_FOUR || (lane & 3) == 0))
+            active_store<D, true>(P, Bn, c, ss, np, srec, fc, flags, md);
+    }
+}
+
 template <int D, bool MD>
 __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np, PCfg c,
                                                      const int* __restrict__ lanemember,
@@ -2988,15 +3250,15 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     // takes the islands of one or two at its lanes [16 q, 16 q + 16) in the
     // split form (or in the general loop below, restricted to those lanes,
     // when one of them does not qualify); a wave of larger islands is worked
-    // by quarter 0 alone.  With Mindlin, part p of eight takes islands of three
-    // to sixteen, as many as fill 16 lanes, with four lanes per member (md_multi).
-    constexpr uint32_t QUARTERS = MD ? 8u : 4u;
+    // by quarter 0 alone.  With Mindlin the parts are those of k_island_quads.
+    constexpr uint32_t QUARTERS = MD ? MD_PARTS : 4u;
     const uint32_t nt = tp.groups + tw.groups;
     for (uint32_t v = blockIdx.x; v < nt + nw * QUARTERS; v += gridDim.x) {
         // islands of size sz at lanes [lane0, lane0 + nl) of the entries from `member`
         int sz, lane0 = 0, nl;
         const int* member;
-        bool split = !MD, multi = false;
+        bool split = !MD;
+        const bool quads = MD && !c.microslip;
         if (v < nt) {
             sz = v < tp.groups ? 2 : 1;
             const uint32_t i0 = sz == 2 ? v * tp.per : (v - tp.groups) * tw.per;
@@ -3013,17 +3275,12 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
             member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
             split = split && sz <= 2;
-            multi = MD && !c.microslip && sz >= 3 && sz <= 16;
-            if (!split && !multi && part != 0) continue;
-            if (multi) {
-                const int take = 16 / sz * sz;
+            const bool part_of = split || (quads && sz <= 16 && sz != 1);
+            if (!part_of && part != 0) continue;
+            if (part_of) {
+                const int take = split ? 16 : md_take(sz);
                 lane0 = (int)part * take;
                 nl = min(nl - lane0, take);
-                if (nl <= 0) continue;
-            }
-            if (split) {
-                lane0 = (int)part * 16;
-                nl = min(nl - lane0, 16);
                 if (nl <= 0) continue;
             }
         }
@@ -3055,25 +3312,8 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 continue;
             }
         }
-        if constexpr (MD) {
-            if (multi) {
-                const int ol = lane0 + (lane >> 2), kc = lane & 3;
-                const bool sv = ol < lane0 + nl;
-                const uint32_t ss = sv ? alist[member[ol]] : 0;
-                Active<D> P;
-                CandData cd{};
-                if (sv) {
-                    active_load<D, MD>(P, A, c, ss, drho_i, j_i, np, ccount, prefix, md);
-                    if (kc < P.cnt) cd = cdata[P.off + kc];
-                }
-                if (__all(!sv || (P.cnt >= 1 && P.cnt <= 4 && !P.fixed && !P.wall))) {
-                    md_multi<D>(P, c, sv, cd, lane0, sz, md);
-                    __syncthreads();                 // (the contacts' states, for the history)
-                    if (sv && kc == 0) active_store<D, MD>(P, Bn, c, ss, np, srec, fc, flags, md);
-                    continue;
-                }
-            }
-        }
+        if (MD && quads && md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata) != MD_GENERAL)
+            continue;                                            // k_island_quads works them
         // the general loop: the whole wave, or this workgroup's lanes of it
         bool valid = lane >= lane0 && lane < lane0 + nl;
         int a = valid ? member[lane] : -1;
@@ -3088,9 +3328,8 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 const bool ok = valid && (sz == 1 ? (P.cnt == 0 && !P.fixed)
                                                   : (P.cnt == 1 && !P.fixed && cd.local == (lane ^ 1)));
                 if (__all(!valid || ok)) {
-                    if (sz == 1) md_wave<D, 0, false>(P, c, valid, cd, md);
-                    else if (!c.microslip && !__any(valid && P.wall)) md_wave<D, 1, true>(P, c, valid, cd, md);
-                    else md_wave<D, 1, false>(P, c, valid, cd, md);
+                    if (sz == 1) md_wave<D, 0>(P, c, valid, cd, md);
+                    else md_wave<D, 1>(P, c, valid, cd, md);
                     if (valid) active_store<D, MD>(P, Bn, c, s, np, srec, fc, flags, md);
                     continue;
                 }
@@ -3969,6 +4208,9 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
     const dim3 gsmall(std::max<unsigned>(grid_act * 4, 256u));
     const dim3 gsplit(4 * gsmall.x);
     if (c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) {
+        if (!c.microslip)
+            hipLaunchKernelGGL(k_island_quads<D>, gsplit, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
+                               b.ccount, b.prefix, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags, b.counters, md);
         hipLaunchKernelGGL((k_island_small<D, true>), gsplit, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
                            b.ccount, b.prefix, b.parent, b.isize, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags,
                            b.counters, md);
