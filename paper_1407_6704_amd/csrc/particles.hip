@@ -2615,13 +2615,29 @@ __device__ __forceinline__ float pick3(const float* v, int a) { return a == 0 ? 
 // candidate in registers.  The decisions and arithmetic are those of the
 // general island loop: every lane of a quad holds the same copy of the
 // particle's scalars and takes the same decisions.
+//
+// NC = 2: islands of three to eight particles, none with more than two
+// candidates: a quad per contact, those of a member eight lanes apart
+// (split_row_lane) with a copy of its state each, the partner's state by a lane
+// shuffle, the second contact's force added to the first's as in the general
+// loop (bit for bit its result).  `lane0`: the packed lane of the first member,
+// isz: the island's size.  In the general loop a touching pair with a third
+// particle in reach set the time of the whole kernel: 203x187x211 with 100
+// touching pairs, 6 steps, 20.2 ms where one had a third beside it, 10.4 ms now
+// (9.0 ms with pairs alone).
+__device__ __forceinline__ int split_row_lane(int member) { return (member >> 1) * 16 + (member & 1) * 4; }
 template <int D, int CT, int NC>
 __device__ __forceinline__ void split_wave(Active<D>& P, const PCfg& c, bool valid, const CandData& cd,
-                                           const MdBuf& md) {
+                                           const MdBuf& md, int lane0 = 0, int isz = 2) {
     const int ax = min((int)(threadIdx.x & 3u), D - 1);
     const int ct = CT < 0 ? c.contact : CT;
     if (!valid) P = Active<D>{};      // padding lanes: a zero state, never stored
-    const float oveq = NC ? row_swap8(P.veq) : 0.f;
+    const int lane = threadIdx.x, kc = NC == 2 ? (lane >> 3) & 1 : 0;
+    const bool has = NC != 2 || (valid && kc < P.cnt);
+    const int partner = NC == 2 && has ? split_row_lane(cd.local - lane0) + (lane & 11) : lane;
+    const int first = ((((lane >> 4) << 1) | ((lane >> 2) & 1)) / isz) * isz;       // the island's first member
+    auto other = [&](float v) { return NC == 2 ? __shfl(v, partner) : row_swap8(v); };
+    const float oveq = NC ? other(P.veq) : 0.f;
     // this lane's axis: the running state and the step's constants
     float u = pick3(P.u, ax), cu = pick3(P.cu, ax), dx = pick3(P.dx, ax), cdx = pick3(P.cdx, ax);
     float gs = pick3(P.gs, ax), fs = pick3(P.fs, ax);
@@ -2643,18 +2659,26 @@ __device__ __forceinline__ void split_wave(Active<D>& P, const PCfg& c, bool val
             // the relative displacement and velocity, axis by axis
             // (this lane's component of r = r0 + del is r0 + its own del)
             float del[3] = {0.f, 0.f, 0.f}, r[3], inv, delta;
-            const float dl = dx - row_swap8(dx);
+            const float dl = dx - other(dx);
             quad_gather<D>(dl, del);
-            const bool on = pair_geom<D, true>(cd, del, r, inv, delta);
+            const bool on = pair_geom<D, true>(cd, del, r, inv, delta) && has;
             const float n = (r0 + dl) * inv;
             float vn = 0.f;
             if (ct == PIBM_CONTACT_LSD) {
                 float pv[3] = {0.f, 0.f, 0.f};
-                quad_gather<D>((u - row_swap8(u)) * n, pv);
+                quad_gather<D>((u - other(u)) * n, pv);
                 vn = sum_d<D>(pv);
             }
-            const float Fp = F + pair_mag<CT>(cd, c, delta, vn) * n;
-            F = on ? Fp : F;
+            const float mag = pair_mag<CT>(cd, c, delta, vn);
+            if (NC == 2) {
+                const float F0 = row_swap8(on ? F + mag * n : F);      // (the lanes of contact 1 get contact 0's)
+                const float F1 = on ? F0 + mag * n : F0;
+                const float sum = row_swap8(F1);
+                F = kc == 0 ? sum : F1;
+            } else {
+                const float Fp = F + mag * n;
+                F = on ? Fp : F;
+            }
         }
         axis_update<D>(P, c, F, j, hbw, u, cu, dx, cdx, gs, fs);
         float sq[3] = {0.f, 0.f, 0.f};
@@ -2684,17 +2708,22 @@ __device__ __forceinline__ void split_wave(Active<D>& P, const PCfg& c, bool val
                 if (NC) {
 #pragma unroll
                     for (int a = 0; a < D; a++) {
-                        odx[a] = row_swap8(Q.dx[a]);
-                        ou[a] = row_swap8(Q.u[a]);
+                        odx[a] = other(Q.dx[a]);
+                        ou[a] = other(Q.u[a]);
                     }
                 }
-                int allow = 0;
-                if (check) {
+                int allow = NC == 2 ? c.n_sub - k : 0;
+                if (check && has) {
                     if (NC) allow = free_allowance_one<D>(Q, c, cd, odx, ou, oveq, c.n_sub - k);
                     else allow = free_allowance<D>(Q, c, nullptr, 0, nullptr, nullptr, nullptr, nullptr, 0, c.n_sub - k);
                 }
-                const int other = NC ? row_swap8(allow) : allow;
-                m = check ? min(allow, other) : 0;
+                allow = min(allow, NC ? row_swap8(allow) : allow);
+                if (NC == 2) {
+                    int low = allow;
+                    for (int i = 0; i < isz; i++) low = min(low, __shfl(allow, split_row_lane(first + i)));
+                    allow = low;
+                }
+                m = check ? allow : 0;
             }
             const bool jump = more && m >= 2;
             if (!__any(jump)) break;
@@ -2876,7 +2905,6 @@ __device__ __forceinline__ float quad_dot(float a, float b) {
 // copy of its state each and their contacts' forces added; the partner's state
 // by a lane shuffle, 0.39 us a sub-step.  `lane0`: the packed lane of the first
 // member, isz: the island's size.
-__device__ __forceinline__ int md_row_lane(int member) { return (member >> 1) * 16 + (member & 1) * 4; }
 template <int D, bool ROWS>
 __device__ __forceinline__ void md_quad_wave(Active<D>& P, const PCfg& c, bool valid, const CandData& cd,
                                              const MdBuf& md, int lane0 = 0, int isz = 2) {
@@ -2884,7 +2912,7 @@ __device__ __forceinline__ void md_quad_wave(Active<D>& P, const PCfg& c, bool v
     if (!valid) P = Active<D>{};      // padding lanes: a zero state, never stored
     const int lane = threadIdx.x, kc = ROWS ? (lane >> 3) & 1 : 0;
     const bool has = valid && kc < P.cnt;
-    const int partner = ROWS && has ? md_row_lane(cd.local - lane0) + (lane & 11) : lane;
+    const int partner = ROWS && has ? split_row_lane(cd.local - lane0) + (lane & 11) : lane;
     const int first = ((((lane >> 4) << 1) | ((lane >> 2) & 1)) / isz) * isz;       // the island's first member
     auto other = [&](float v) { return ROWS ? __shfl(v, partner) : row_swap8(v); };
     auto both = [&](float v) { return ROWS ? v + row_swap8(v) : v; };
@@ -2952,7 +2980,7 @@ __device__ __forceinline__ void md_quad_wave(Active<D>& P, const PCfg& c, bool v
                 allow = min(allow, row_swap8(allow));
                 if (ROWS) {
                     int low = allow;
-                    for (int i = 0; i < isz; i++) low = min(low, __shfl(allow, md_row_lane(first + i)));
+                    for (int i = 0; i < isz; i++) low = min(low, __shfl(allow, split_row_lane(first + i)));
                     allow = low;
                 }
                 m = check ? allow : 0;
@@ -3249,15 +3277,18 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     // waves, without Mindlin, each is worked by QUARTERS workgroups: quarter q
     // takes the islands of one or two at its lanes [16 q, 16 q + 16) in the
     // split form (or in the general loop below, restricted to those lanes,
-    // when one of them does not qualify); a wave of larger islands is worked
-    // by quarter 0 alone.  With Mindlin the parts are those of k_island_quads.
+    // when one of them does not qualify); islands of three to eight are worked
+    // eight members to a workgroup, a wave of larger ones by its first workgroup
+    // alone.  With Mindlin the parts are those of k_island_quads.
     constexpr uint32_t QUARTERS = MD ? MD_PARTS : 4u;
+    // islands of three to eight: parts of eight members (the split form NC = 2)
+    const uint32_t nw2 = MD ? nw : min(nw, counters[CNT_WAVEBASE + 3]);
     const uint32_t nt = tp.groups + tw.groups;
-    for (uint32_t v = blockIdx.x; v < nt + nw * QUARTERS; v += gridDim.x) {
+    for (uint32_t v = blockIdx.x; v < nt + nw2 * QUARTERS + (nw - nw2) * MD_PARTS; v += gridDim.x) {
         // islands of size sz at lanes [lane0, lane0 + nl) of the entries from `member`
         int sz, lane0 = 0, nl;
         const int* member;
-        bool split = !MD;
+        bool split = !MD, rows = false;
         const bool quads = MD && !c.microslip;
         if (v < nt) {
             sz = v < tp.groups ? 2 : 1;
@@ -3267,7 +3298,12 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
         } else {
             // the wave's size class is the largest whose first wave is <= w;
             // its islands fill lanes [0, islands_here * size)
-            const uint32_t w = (v - nt) / QUARTERS, part = (v - nt) % QUARTERS;
+            uint32_t w = (v - nt) / QUARTERS, part = (v - nt) % QUARTERS;
+            if (w >= nw2) {
+                const uint32_t q = v - nt - nw2 * QUARTERS;
+                w = nw2 + q / MD_PARTS;
+                part = q % MD_PARTS;
+            }
             const unsigned long long le = __ballot(wb_lane <= w);
             sz = 64 - __clzll(le);
             const uint32_t per = WAVE / sz;
@@ -3275,7 +3311,8 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
             member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
             split = split && sz <= 2;
-            const bool part_of = split || (quads && sz <= 16 && sz != 1);
+            rows = !MD && sz >= 3 && sz <= 8;
+            const bool part_of = split || rows || (quads && sz <= 16 && sz != 1);
             if (!part_of && part != 0) continue;
             if (part_of) {
                 const int take = split ? 16 : md_take(sz);
@@ -3310,6 +3347,25 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 }
                 if (sv && (lane & 3) == 0) active_store<D, MD>(P, Bn, c, ss, np, srec, fc, flags, md);
                 continue;
+            }
+        }
+        if constexpr (!MD) {
+            if (rows) {
+                const int ol = lane0 + (((lane >> 4) << 1) | ((lane >> 2) & 1)), kc = (lane >> 3) & 1;
+                const bool sv = ol < lane0 + nl;
+                const uint32_t ss = sv ? alist[member[ol]] : 0;
+                Active<D> P;
+                CandData cd{};
+                if (sv) {
+                    active_load<D, MD>(P, A, c, ss, drho_i, j_i, np, ccount, prefix, md);
+                    if (kc < P.cnt) cd = cdata[P.off + kc];
+                }
+                if (__all(!sv || (P.cnt >= 1 && P.cnt <= 2 && !P.fixed))) {
+                    if (c.contact == PIBM_CONTACT_LSD) split_wave<D, PIBM_CONTACT_LSD, 2>(P, c, sv, cd, md, lane0, sz);
+                    else split_wave<D, -1, 2>(P, c, sv, cd, md, lane0, sz);
+                    if (sv && kc == 0 && (lane & 3) == 0) active_store<D, MD>(P, Bn, c, ss, np, srec, fc, flags, md);
+                    continue;
+                }
             }
         }
         if (MD && quads && md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata) != MD_GENERAL)
