@@ -23,7 +23,7 @@ void lattice_init_eq(int Q, int fp16, int sl2, void* f, const float* rho, const 
                      hipStream_t s);
 void lattice_decode(int fp16, int sl2, const void* f, float* out, long long n, hipStream_t s);
 void lattice_encode(int fp16, int sl2, void* f, const float* in, long long n, hipStream_t s);
-void lattice_fields(const float4* mom, float* rho, float* u, long long N, int D, hipStream_t s);
+void lattice_fields(int Q, int fp16, int sl2, const void* f, float* rho, float* u, long long N, hipStream_t s);
 int lattice_totals_blocks();
 void lattice_totals(int Q, int fp16, int sl2, const void* f, long long N, double* part, double* out,
                     hipStream_t s);
@@ -887,8 +887,7 @@ pibm_status pibm_read_particles(pibm_ctx* c, double* x, double* v, double* f_hyd
 // Density and velocity of the stored populations into device arrays (the
 // caller's, or the staging area).
 hipError_t fields_to(pibm_ctx* c, float* rho, float* u) {
-    lattice_moments(c->Q, c->fp16, c->sl2, c->fA, c->mom, c->N, RowMask{}, c->stream);   // every node
-    lattice_fields(c->mom, rho, u, c->N, c->D, c->stream);
+    lattice_fields(c->Q, c->fp16, c->sl2, c->fA, rho, u, c->N, c->stream);
     return hipGetLastError();
 }
 
