@@ -719,15 +719,31 @@ __global__ __launch_bounds__(256) void k_interp_tile(PState A, int np, Grid g, P
         // outside the lattice read node 0 and are zeroed)
         constexpr int IT = (NX * NY * NZ + 255) / 256;
         constexpr int nh = lx * ly * lz;
+        // node i = t + 256 k, in 3D its place stepped instead of divided out
+        // (256 nodes on are DX along x and DR rows, DY along y, DZ along z): with
+        // 32-bit node numbers 128^3 35.2 -> 33.5 us, 150x131x170 42.7 -> 40.9 us
+        constexpr int DX = 256 % lx, DR = 256 / lx, DY = DR % ly, DZ = DR / ly;
         float4 v[IT];
+        int ix = t % lx, iy = (t / lx) % ly, iz = t / (lx * ly);
 #pragma unroll
         for (int k = 0; k < IT; k++) {
             const int i = t + k * 256;
-            const int ix = i % lx, iy = (i / lx) % ly, iz = i / (lx * ly);
             const int x = nx0 + ix, y = ny0 + iy, z = nz0 + iz;
-            const bool ok = i < nh && x >= 0 && x < g.n[0] && y >= 0 && y < g.n[1] && z >= 0 && z < g.n[2];
-            v[k] = src.at(ok ? ((long long)z * g.n[1] + y) * g.n[0] + x : 0LL, g.N);
+            const bool ok = i < nh && (unsigned)x < (unsigned)g.n[0] && (unsigned)y < (unsigned)g.n[1] &&
+                            (unsigned)z < (unsigned)g.n[2];
+            // (N < 2^31)
+            v[k] = src.at(ok ? (long long)((z * g.n[1] + y) * g.n[0] + x) : 0LL, g.N);
             if (!ok) v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (D == 3) {
+                ix += DX;
+                iy += DY;
+                iz += DZ;
+                if (ix >= lx) ix -= lx, iy++;
+                if (iy >= ly) iy -= ly, iz++;
+            } else {
+                ix = (i + 256) % lx;
+                iy = (i + 256) / lx;
+            }
         }
 #pragma unroll
         for (int k = 0; k < IT; k++)
