@@ -28,7 +28,7 @@ int lattice_totals_blocks();
 void lattice_totals(int Q, int fp16, int sl2, const void* f, long long N, double* part, double* out,
                     hipStream_t s);
 long long scan_blocks(long long n);
-void particles_sort(int D, PBuf& b, int np, const PCfg& c, bool unordered, hipStream_t s);
+bool particles_sort(int D, PBuf& b, int np, const PCfg& c, bool unordered, const PBuf* tape, hipStream_t s);
 void particles_interp(int D, PBuf& b, int np, const Grid& g, const PCfg& c, const float4* mom, hipStream_t s);
 void particles_unpermute_spin(int D, PBuf& b, int np, float* out, hipStream_t s);
 bool particles_interp_by_nodes(int D, int np);
@@ -482,8 +482,12 @@ void ensure_force(pibm_ctx* c) {
     c->F_stale = false;
 }
 
-void sort_particles(pibm_ctx* c) {
-    particles_sort(c->D, c->pb, c->np, c->pc, c->unordered, c->stream);
+// tape (nullable): where the sorted particles and the cell list are saved.
+void sort_particles(pibm_ctx* c, uint32_t* tape = nullptr) {
+    PBuf view;
+    if (tape) view = adj_tape_view(c->D, c->pb, c->np, tape);
+    const bool saved = particles_sort(c->D, c->pb, c->np, c->pc, c->unordered, tape ? &view : nullptr, c->stream);
+    if (tape && !saved) adj_save_tape(c->D, c->pb, c->np, c->pc.nbins, tape, c->stream);
     c->unordered = false;
 }
 
@@ -971,8 +975,7 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     // restricts to the node rows that the particles' stencils reach
     const bool fused = c->D == 2 && c->pc.L <= 1;
     q(mark(c, row, 0));
-    if (c->np > 0) sort_particles(c);
-    if (tape) adj_save_tape(c->D, c->pb, c->np, c->pc.nbins, tape, c->stream);
+    if (c->np > 0) sort_particles(c, tape);
     q(mark(c, row, 1));
     const bool nodes = particles_interp_by_nodes(c->D, c->np);
     if (c->np > 0 && !fused && !nodes) {
