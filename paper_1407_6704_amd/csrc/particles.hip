@@ -3182,11 +3182,10 @@ __device__ __forceinline__ void md_multi(Active<D>& P, const PCfg& c, bool valid
     if (has) md_state_store(md.cmd + P.off + kc, md.cms + 2 * (P.off + kc), false, S, kt8r);
 }
 
-// Parts of a packed wave of no-slip Hertz-Mindlin islands of two to sixteen:
-// the pairs of 16 lanes, or as many larger islands as have eight members (one,
-// if it has more); at most MD_PARTS to a wave.
+// Parts of a packed wave of islands of three to sixteen: as many islands as
+// have eight members (one, if it has more); at most MD_PARTS to a wave.
 constexpr uint32_t MD_PARTS = 16;
-__device__ __forceinline__ int md_take(int sz) { return sz == 2 ? 16 : (sz <= 8 ? 8 / sz * sz : sz); }
+__device__ __forceinline__ int md_take(int sz) { return sz <= 8 ? 8 / sz * sz : sz; }
 
 // The form that a part qualifies for: none (the general loop), pairs, at most
 // two or at most four candidates per member; never with a wall in reach or a
@@ -3222,7 +3221,11 @@ __device__ __forceinline__ int md_form(int sz, int lane0, int nl, const int* __r
     return __all(cnt <= 4) ? MD_FOUR : MD_GENERAL;
 }
 
-// The no-slip Hertz-Mindlin islands of two to sixteen that qualify (md_form).
+// The no-slip Hertz-Mindlin islands that qualify (md_form), of those that may
+// take every sub-step: the touching pairs and islands of three to sixteen.  (The
+// other pairs jump over most of theirs; 32 of them in a wave, one lane per
+// particle, cost less: 256^3 with 2M particles, 14,000 of them active, this and
+// k_island_small 26 + 19 us with every pair here, 13 + 15 us so.)
 // A kernel of its own: in one with the general loop their registers spilled,
 // 64^3 with 40 touching pairs 6.2 instead of 5.4 ms.  With a third particle in
 // reach of one pair: 31.2 ms in the general loop, 11.7 by md_multi, 7.7 now.
@@ -3242,7 +3245,8 @@ __global__ __launch_bounds__(64) void k_island_quads(PState A, PState Bn, int np
     const TouchPlan tp = touch_plan(pairs, 2, c);
     const int lane = threadIdx.x;
     const uint32_t wb_lane = counters[CNT_WAVEBASE + 1 + lane];
-    for (uint32_t v = blockIdx.x; v < tp.groups + nw * MD_PARTS; v += gridDim.x) {
+    const uint32_t nw2 = min(nw, counters[CNT_WAVEBASE + 3]);        // waves of islands of one and two
+    for (uint32_t v = blockIdx.x; v < tp.groups + (nw - nw2) * MD_PARTS; v += gridDim.x) {
         int sz = 2, lane0 = 0, nl;
         const int* member;
         if (v < tp.groups) {
@@ -3250,10 +3254,10 @@ __global__ __launch_bounds__(64) void k_island_quads(PState A, PState Bn, int np
             nl = 2 * (int)min(tp.per, pairs - i0);
             member = lanemember + 2 * i0;
         } else {
-            const uint32_t w = (v - tp.groups) / MD_PARTS, part = (v - tp.groups) % MD_PARTS;
+            const uint32_t w = nw2 + (v - tp.groups) / MD_PARTS, part = (v - tp.groups) % MD_PARTS;
             const unsigned long long le = __ballot(wb_lane <= w);
             sz = 64 - __clzll(le);
-            if (sz < 2 || sz > 16) continue;
+            if (sz > 16) continue;
             const uint32_t per = WAVE / sz;
             const uint32_t idx = w - counters[CNT_WAVEBASE + sz];
             nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
@@ -3319,10 +3323,11 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     // split form (or in the general loop below, restricted to those lanes,
     // when one of them does not qualify); islands of three to eight are worked
     // eight members to a workgroup, a wave of larger ones by its first workgroup
-    // alone.  With Mindlin the parts are those of k_island_quads.
-    constexpr uint32_t QUARTERS = MD ? MD_PARTS : 4u;
+    // alone.  With Mindlin a wave of pairs is one workgroup's, and the parts of
+    // larger islands are those of k_island_quads.
+    constexpr uint32_t QUARTERS = MD ? 1u : 4u;
     // islands of three to eight: parts of eight members (the split form NC = 2)
-    const uint32_t nw2 = MD ? nw : min(nw, counters[CNT_WAVEBASE + 3]);
+    const uint32_t nw2 = min(nw, counters[CNT_WAVEBASE + 3]);
     const uint32_t nt = tp.groups + tw.groups;
     for (uint32_t v = blockIdx.x; v < nt + nw2 * QUARTERS + (nw - nw2) * MD_PARTS; v += gridDim.x) {
         // islands of size sz at lanes [lane0, lane0 + nl) of the entries from `member`
@@ -3352,7 +3357,7 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
             split = split && sz <= 2;
             rows = !MD && sz >= 3 && sz <= 8;
-            const bool part_of = split || rows || (quads && sz <= 16 && sz != 1);
+            const bool part_of = split || rows || (quads && sz >= 3 && sz <= 16);
             if (!part_of && part != 0) continue;
             if (part_of) {
                 const int take = split ? 16 : md_take(sz);
@@ -3408,7 +3413,8 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 }
             }
         }
-        if (MD && quads && md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata) != MD_GENERAL)
+        if (MD && quads && (v < tp.groups || sz >= 3) &&
+            md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata) != MD_GENERAL)
             continue;                                            // k_island_quads works them
         // the general loop: the whole wave, or this workgroup's lanes of it
         bool valid = lane >= lane0 && lane < lane0 + nl;
@@ -4313,7 +4319,7 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
     const dim3 gsplit(4 * gsmall.x);
     if (c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) {
         if (!c.microslip)
-            hipLaunchKernelGGL(k_island_quads<D>, gsplit, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
+            hipLaunchKernelGGL(k_island_quads<D>, gsmall, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
                                b.ccount, b.prefix, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags, b.counters, md);
         hipLaunchKernelGGL((k_island_small<D, true>), gsplit, dim3(64), 0, s, b.A, b.Bn, np, c, b.lanemember, b.alist,
                            b.ccount, b.prefix, b.parent, b.isize, b.cdata, b.drho_i, b.j_i, b.srec, b.fc, b.flags,
