@@ -3187,22 +3187,34 @@ __device__ __forceinline__ void md_multi(Active<D>& P, const PCfg& c, bool valid
 constexpr uint32_t MD_PARTS = 16;
 __device__ __forceinline__ int md_take(int sz) { return sz <= 8 ? 8 / sz * sz : sz; }
 
-// The form that a part qualifies for: none (the general loop), pairs, at most
-// two or at most four candidates per member; never with a wall in reach or a
-// fixed point.
+// The form that an island of a part qualifies for: none (the general loop),
+// pairs, at most two or at most four candidates per member; never with a wall in
+// reach or a fixed point.  Each island's own members decide, not the part's:
+// the forms round differently, and which islands share a part depends on the
+// order in which they were ranked.
 enum : int { MD_GENERAL = 0, MD_PAIRS = 1, MD_TWO = 2, MD_FOUR = 3 };
+struct MdForms {
+    unsigned long long general, over2, over4;      // members (bits) that forbid the forms
+    int sz;
+    __device__ __forceinline__ int of(int member) const {
+        const unsigned long long in = ((1ULL << sz) - 1) << (member / sz * sz);
+        if ((general & in) != 0) return MD_GENERAL;
+        if (sz == 2) return MD_PAIRS;
+        if (sz <= 8 && (over2 & in) == 0) return MD_TWO;
+        return (over4 & in) == 0 ? MD_FOUR : MD_GENERAL;
+    }
+};
 template <int D>
-__device__ __forceinline__ int md_form(int sz, int lane0, int nl, const int* __restrict__ member, const PState& A,
-                                       const PCfg& c, const uint32_t* __restrict__ alist,
-                                       const uint32_t* __restrict__ ccount,
-                                       const unsigned long long* __restrict__ prefix,
-                                       const CandData* __restrict__ cdata) {
-    if (sz < 2 || sz > 16) return MD_GENERAL;
+__device__ __forceinline__ MdForms md_forms(int sz, int lane0, int nl, const int* __restrict__ member,
+                                            const PState& A, const PCfg& c, const uint32_t* __restrict__ alist,
+                                            const uint32_t* __restrict__ ccount,
+                                            const unsigned long long* __restrict__ prefix,
+                                            const CandData* __restrict__ cdata) {
     const int lane = threadIdx.x;
     const bool on = lane < nl;
     int cnt = 1;
-    bool ok = true;
-    if (on) {
+    bool ok = sz >= 2 && sz <= 16;
+    if (on && ok) {
         const uint32_t s = alist[member[lane0 + lane]];
         cnt = (int)ccount[s];
         ok = cnt >= 1 && !(A.fixa && A.fixa[s] > 0.f);
@@ -3215,13 +3227,10 @@ __device__ __forceinline__ int md_form(int sz, int lane0, int nl, const int* __r
         if (ok && sz == 2)
             ok = cnt == 1 && cdata[(uint32_t)(prefix[s] & 0xffffffffULL)].local == ((lane0 + lane) ^ 1);
     }
-    if (!__all(ok)) return MD_GENERAL;
-    if (sz == 2) return MD_PAIRS;
-    if (sz <= 8 && __all(cnt <= 2)) return MD_TWO;
-    return __all(cnt <= 4) ? MD_FOUR : MD_GENERAL;
+    return MdForms{__ballot(on && !ok), __ballot(on && cnt > 2), __ballot(on && cnt > 4), min(sz, 63)};
 }
 
-// The no-slip Hertz-Mindlin islands that qualify (md_form), of those that may
+// The no-slip Hertz-Mindlin islands that qualify (md_forms), of those that may
 // take every sub-step: the touching pairs and islands of three to sixteen.  (The
 // other pairs jump over most of theirs; 32 of them in a wave, one lane per
 // particle, cost less: 256^3 with 2M particles, 14,000 of them active, this and
@@ -3267,27 +3276,30 @@ __global__ __launch_bounds__(64) void k_island_quads(PState A, PState Bn, int np
             nl = min(nl - lane0, take);
             if (nl <= 0) continue;
         }
-        const int form = md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata);
-        if (form == MD_GENERAL) continue;
-        // this lane's member and contact
-        int mi, kc = 0;
-        if (form == MD_PAIRS) mi = ((lane >> 4) << 2) | (((lane >> 2) & 1) << 1) | ((lane >> 3) & 1);
-        else if (form == MD_TWO) mi = ((lane >> 4) << 1) | ((lane >> 2) & 1), kc = (lane >> 3) & 1;
-        else mi = lane >> 2, kc = lane & 3;
-        const bool sv = mi < nl;
-        const uint32_t ss = sv ? alist[member[lane0 + mi]] : 0;
-        Active<D> P;
-        CandData cd{};
-        if (sv) {
-            active_load<D, true>(P, A, c, ss, drho_i, j_i, np, ccount, prefix, md);
-            if (kc < P.cnt) cd = cdata[P.off + kc];
+        const MdForms forms = md_forms<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata);
+#pragma unroll
+        for (int form = MD_PAIRS; form <= MD_FOUR; form++) {
+            // this lane's member and contact in this form
+            int mi, kc = 0;
+            if (form == MD_PAIRS) mi = ((lane >> 4) << 2) | (((lane >> 2) & 1) << 1) | ((lane >> 3) & 1);
+            else if (form == MD_TWO) mi = ((lane >> 4) << 1) | ((lane >> 2) & 1), kc = (lane >> 3) & 1;
+            else mi = lane >> 2, kc = lane & 3;
+            const bool sv = mi < nl && forms.of(mi) == form;
+            if (!__any(sv)) continue;
+            const uint32_t ss = sv ? alist[member[lane0 + mi]] : 0;
+            Active<D> P;
+            CandData cd{};
+            if (sv) {
+                active_load<D, true>(P, A, c, ss, drho_i, j_i, np, ccount, prefix, md);
+                if (kc < P.cnt) cd = cdata[P.off + kc];
+            }
+            if (form == MD_PAIRS) md_quad_wave<D, false>(P, c, sv, cd, md);
+            else if (form == MD_TWO) md_quad_wave<D, true>(P, c, sv, cd, md, lane0, sz);
+            else md_multi<D>(P, c, sv, cd, lane0, sz, md);
+            __syncthreads();                             // (the contacts' states, for the history)
+            if (sv && kc == 0 && (form == MD_FOUR || (lane & 3) == 0))
+                active_store<D, true>(P, Bn, c, ss, np, srec, fc, flags, md);
         }
-        if (form == MD_PAIRS) md_quad_wave<D, false>(P, c, sv, cd, md);
-        else if (form == MD_TWO) md_quad_wave<D, true>(P, c, sv, cd, md, lane0, sz);
-        else md_multi<D>(P, c, sv, cd, lane0, sz, md);
-        __syncthreads();                             // (the contacts' states, for the history)
-        if (sv && kc == 0 && (form == MD_FOUR || (lane & 3) == 0))
-            active_store<D, true>(P, Bn, c, ss, np, srec, fc, flags, md);
     }
 }
 
@@ -3413,11 +3425,14 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
                 }
             }
         }
-        if (MD && quads && (v < tp.groups || sz >= 3) &&
-            md_form<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata) != MD_GENERAL)
-            continue;                                            // k_island_quads works them
         // the general loop: the whole wave, or this workgroup's lanes of it
         bool valid = lane >= lane0 && lane < lane0 + nl;
+        if (MD && quads && (v < tp.groups || sz >= 3)) {
+            // but for the islands that k_island_quads works
+            const MdForms forms = md_forms<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata);
+            valid = valid && forms.of(lane - lane0) == MD_GENERAL;
+            if (!__any(valid)) continue;
+        }
         int a = valid ? member[lane] : -1;
         uint32_t s = valid ? alist[a] : 0;
         Active<D> P;
@@ -3427,13 +3442,18 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             if (sz <= 2) {
                 CandData cd{};
                 if (valid && sz == 2 && P.cnt > 0) cd = cdata[P.off];
-                const bool ok = valid && (sz == 1 ? (P.cnt == 0 && !P.fixed)
-                                                  : (P.cnt == 1 && !P.fixed && cd.local == (lane ^ 1)));
-                if (__all(!valid || ok)) {
-                    if (sz == 1) md_wave<D, 0>(P, c, valid, cd, md);
-                    else md_wave<D, 1>(P, c, valid, cd, md);
-                    if (valid) active_store<D, MD>(P, Bn, c, s, np, srec, fc, flags, md);
-                    continue;
+                // (each island by its own members, as above)
+                bool ok = valid && (sz == 1 ? (P.cnt == 0 && !P.fixed)
+                                            : (P.cnt == 1 && !P.fixed && cd.local == (lane ^ 1)));
+                const bool partner = pair_swap((int)ok) != 0;
+                ok = ok && (sz == 1 || partner);
+                if (__any(ok)) {
+                    if (sz == 1) md_wave<D, 0>(P, c, ok, cd, md);
+                    else md_wave<D, 1>(P, c, ok, cd, md);
+                    if (ok) active_store<D, MD>(P, Bn, c, s, np, srec, fc, flags, md);
+                    valid = valid && !ok;
+                    if (!__any(valid)) continue;
+                    if (valid) active_load<D, MD>(P, A, c, s, drho_i, j_i, np, ccount, prefix, md);
                 }
             }
         }
