@@ -370,7 +370,8 @@ pibm_status pibm_backward(pibm_ctx* ctx, const float* dJ_dx_T, const float* dJ_d
  * PIBM_STAGE_INTERP_T: in0 = (1 + D) x np in the same order; out0 = the
  *   transpose of the last PIBM_STAGE_INTERP, (1 + D) x n: each particle
  *   value spread with the same weights (Eq. lbm10-lbm11).  PIBM_E_STATE
- *   unless PIBM_STAGE_INTERP came first. */
+ *   unless PIBM_STAGE_INTERP came first, with no step, hand-over of
+ *   particles, backward pass or PIBM_STAGE_PARTICLES_T in between. */
 enum { PIBM_STAGE_COLLIDE_T = 1, PIBM_STAGE_PARTICLES_T = 2, PIBM_STAGE_INTERP = 3, PIBM_STAGE_INTERP_T = 4 };
 pibm_status pibm_adjoint_stage(pibm_ctx* ctx, int32_t stage, const float* in0, const float* in1,
                                const float* in2, float* out0, float* out1, float* out2, double* scalars);

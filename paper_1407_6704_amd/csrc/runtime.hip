@@ -117,9 +117,9 @@ struct pibm_ctx {
     // the particle state has not been sorted since it was handed over or
     // loaded from a checkpoint (id order)
     bool unordered = true;
-    // the spreading records change with every step, particle hand-over and
-    // particle adjoint stage; PIBM_STAGE_INTERP_T needs those of the last
-    // PIBM_STAGE_INTERP
+    // the spreading records change with every step, particle hand-over,
+    // backward pass and particle adjoint stage; PIBM_STAGE_INTERP_T needs those
+    // of the last PIBM_STAGE_INTERP
     uint64_t srec_epoch = 0, interp_stage_epoch = ~0ull;
     // the last step spread its force straight into the collision: the field
     // in F is recomputed from the spreading records when someone needs it
@@ -1112,6 +1112,7 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
     ensure_force(c);
     Rollout& R = c->ro;
     if (!R.valid) return fail(c, PIBM_E_STATE, "no recorded rollout (call pibm_forward_ckpt first)");
+    c->srec_epoch++;                 // the reverse steps leave records of their own
     const int D = c->D, np = c->np, Q = c->Q;
     const long long N = c->N, DN = (long long)D * np;
     const size_t fbytes = pop_bytes(c);

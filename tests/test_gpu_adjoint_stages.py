@@ -203,3 +203,20 @@ def test_interpolation_transpose_dot_product(P, lattice):
     _flush(f"  <I m, c> {lhs:.9e}  <m, I^T c> {rhs:.9e}  diff {abs(lhs - rhs):.2e}  bound {bound:.2e}")
     assert abs(lhs - rhs) <= bound
     assert abs(lhs) > 1e-3 * A                         # not a cancelled sum
+
+
+@pytest.mark.parametrize("lattice", [9, 19])
+def test_transpose_refused_after_backward(P, lattice):
+    """The backward pass leaves weights and bins of its own steps: a transpose
+    after it would not be that of the interpolation before it."""
+    _flush(f"adjoint stage: transpose after backward, lattice {lattice}")
+    sim, cfg, n, d, rp = _case(P, lattice, seed=13)
+    c = np.ones((1 + sim.D, sim.np), np.float32)
+    sim.adjoint_stage("interp", np.ones((1 + sim.D, sim.N), np.float32))
+    sim.adjoint_stage("interp_t", c)
+    sim.backward(dJ_dx=np.ones((sim.D, sim.np)))
+    with pytest.raises(P.PibmError) as e:
+        sim.adjoint_stage("interp_t", c)
+    assert e.value.name == "E_STATE"
+    sim.adjoint_stage("interp", np.ones((1 + sim.D, sim.N), np.float32))
+    sim.adjoint_stage("interp_t", c)
