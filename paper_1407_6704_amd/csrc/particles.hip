@@ -453,7 +453,11 @@ __global__ __launch_bounds__(CELLS_FEW) void k_cells_few(PState A, PState B, int
 // a memory line: 13 of them a particle.  From RECORD_MIN particles on, each
 // particle is written there as one 64-byte record instead, and a second pass
 // lays the records out as arrays.  256^3 with 2M particles: 636 us in one
-// pass, 172 us in two.  (A state already sorted once moves little and keeps
+// pass, 172 us in two.  The line lies where it begins to pay (a hand-over and
+// its first step, us, one pass / records): 32,768 disks 101 / 98, 65,536
+// 105.6 / 104.7, 131,072 139 / 134; 32,768 spheres 118.8 / 118.3, 65,536
+// 150 / 145, 131,072 217 / 211; a read-out of 65,536 disks 18.7 / 19.4, 131,072
+// 23.3 / 21.6, of 65,536 spheres 21.7 / 19.6.  (A state already sorted once moves little and keeps
 // the one pass: 64 us.)  Angular velocities, rarely present, go directly.
 constexpr int RECORD_MIN = 65536;
 constexpr int RECORD_FLOATS = 16;
@@ -836,12 +840,17 @@ __global__ __launch_bounds__(256) void k_interp_tile(PState A, int np, Grid g, P
 // seven dependent trips to memory and one thread's 64 reads however few
 // particles it holds; here all loads of a particle are in flight at once,
 // and no moments pass runs before.  But a particle fetches 16 rows of every
-// population plane for itself, about 7 ns of the whole GPU each: one particle
-// on D3Q15 5.3 us against 11.0 + 2.9 us (tiles + moments), 3000 on D3Q19 24.4
-// against 12.5 + 7.9 us, 31,250 66 against 13.6 + 5.2 us, hence the limit.
+// population plane for itself, about 7 ns of the whole GPU each, while the
+// tiles' cost hardly grows with the particles and a moments pass costs by the
+// nodes.  Whole steps by nodes / by tiles, us, D3Q19 FP32 (D3Q15 and FP16 cross
+// within 50 particles of it): 25k nodes 600 particles 54.0 / 54.6, 800
+// 56.6 / 54.8; 151k nodes 600 59.7 / 60.4, 800 62.7 / 60.9; 885k nodes 1024
+// 83.9 / 91.0.  Hence the limit, which grows with the lattice.
 // (In 2D, where the tiles read the populations themselves, it gains nothing:
 // 200 particles 6.3 against 6.8 us, 10,000 19.9 against 7.9 us.)
-constexpr int INTERP_NODES_MAX = 1024;
+bool particles_interp_by_nodes(int D, int np, long long N) {
+    return D == 3 && np <= std::min<long long>(1024, 640 + N / 2048);
+}
 
 __device__ __forceinline__ float pick_weight(const float* w, int k) {
     const float lo = (k & 1) ? w[1] : w[0], hi = (k & 1) ? w[3] : w[2];
@@ -4240,8 +4249,6 @@ static void interp_tile(PBuf& b, int np, const Grid& g, const PCfg& c, Src src, 
         else interp_tile_launch<D, Src, false, 1>(b, np, g, c, src, s);
     }
 }
-
-bool particles_interp_by_nodes(int D, int np) { return D == 3 && np <= INTERP_NODES_MAX; }
 
 template <int Q, class S>
 static void interp_nodes_launch(PBuf& b, int np, const Grid& g, const PCfg& c, const void* f, S st, hipStream_t s) {

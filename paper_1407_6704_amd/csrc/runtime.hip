@@ -31,7 +31,7 @@ long long scan_blocks(long long n);
 bool particles_sort(int D, PBuf& b, int np, const PCfg& c, bool unordered, const PBuf* tape, hipStream_t s);
 void particles_interp(int D, PBuf& b, int np, const Grid& g, const PCfg& c, const float4* mom, hipStream_t s);
 void particles_unpermute_spin(int D, PBuf& b, int np, float* out, hipStream_t s);
-bool particles_interp_by_nodes(int D, int np);
+bool particles_interp_by_nodes(int D, int np, long long N);
 void particles_interp_nodes(int Q, PBuf& b, int np, const Grid& g, const PCfg& c, const void* f, int fp16, int sl2,
                             hipStream_t s);
 void particles_interp_from_populations(PBuf& b, int np, const Grid& g, const PCfg& c, const void* f, int fp16,
@@ -977,7 +977,7 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     q(mark(c, row, 0));
     if (c->np > 0) sort_particles(c, tape);
     q(mark(c, row, 1));
-    const bool nodes = particles_interp_by_nodes(c->D, c->np);
+    const bool nodes = particles_interp_by_nodes(c->D, c->np, c->N);
     if (c->np > 0 && !fused && !nodes) {
         RowMask m{c->pb.start, {c->pc.n[0], c->pc.n[1], c->pc.n[2]}, {c->pc.nb[0], c->pc.nb[1], c->pc.nb[2]},
                   c->pc.L};
