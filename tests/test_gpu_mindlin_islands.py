@@ -86,3 +86,38 @@ def test_mindlin_islands_match_oracle(P, orc, lat, copies, contact):
     ew = np.linalg.norm(w - ref) / np.linalg.norm(ref)
     print(f"  {np_} particles dX={ex:.2e} dU={ev:.2e} dW={ew:.2e}", flush=True)
     assert ex <= 1e-5 and ev <= 1e-5 and ew <= 1e-5
+
+
+@pytest.mark.parametrize("contact", ["hertz_mindlin", "hertz_mindlin_microslip"])
+def test_member_with_many_candidates(P, orc, contact):
+    """Hubs of twelve equal spheres around one (the corners of an icosahedron), which all touch it and are in reach of
+    each other."""
+    print(f"many candidates {contact}", flush=True)
+    rng = np.random.default_rng(12)
+    n, t = (24, 14, 12), 0.5 * (1 + 5 ** 0.5)
+    e = np.array([p for s in (1, -1) for u in (t, -t) for p in ((0, s, u), (s, u, 0), (u, 0, s))]) / np.sqrt(1 + t * t)
+    hub = 0.4998 * np.concatenate([np.zeros((1, 3)), e])
+    X = np.concatenate([np.array([5.1, 5.2, 5.3]) + hub, np.array([15.4, 7.3, 6.2]) + hub]).T
+    X = X.astype(np.float32).astype(np.float64)
+    np_ = X.shape[1]
+    U = (2e-4 * rng.standard_normal((3, np_))).astype(np.float32).astype(np.float64)
+    W = (1e-3 * rng.standard_normal((3, np_))).astype(np.float32).astype(np.float64)
+    d, rp = np.full(np_, 0.5), np.full(np_, 2.5)
+    cfg = P.make_config(lattice=19, n=n, tau=0.8, gravity=(0, 0, -1e-5), n_sub=200, contact=contact, young=1e3)
+    sim = P.Sim(cfg, np_)
+    sim.set_particles(X, U, d, rp)
+    sim.set_rotation(W)
+    oc = G.oracle_cfg(orc, cfg)
+    f = G.to_oracle_f(orc, 19, sim.read_populations())
+    Xo, Uo, Wo, hist = X.copy(), U.copy(), W.copy(), None
+    for _ in range(2):
+        out = orc.step_hm(oc, f, Xo, Uo, Wo, d, rp, hist)
+        f, Xo, Uo, Wo, hist = out["f"], out["X"], out["U"], out["W"], out["hist"]
+    sim.step(2)
+    sim.synchronize()
+    got, w = sim.read_particles(), sim.read_rotation()
+    ex = np.abs(got["x"] - Xo).max() / np.abs(Xo - X).max()
+    ev = np.linalg.norm(got["v"] - Uo) / np.linalg.norm(Uo)
+    ew = np.linalg.norm(w - Wo) / np.linalg.norm(Wo)
+    print(f"  dX={ex:.2e} dU={ev:.2e} dW={ew:.2e}", flush=True)
+    assert ex <= 1e-5 and ev <= 1e-5 and ew <= 1e-5
