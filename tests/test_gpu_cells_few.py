@@ -49,3 +49,46 @@ def test_cells_of_few_particles(P, lat, n, np_, bin_log2):
         assert np.array_equal(ids, order) and np.array_equal(keys, key[order])
         assert np.array_equal(start, np.searchsorted(key[order], np.arange(np.prod(nb) + 1)))
     sim.synchronize()
+
+
+@pytest.mark.parametrize("lat,np_", [(9, 512), (19, 300), (9, 513)])
+def test_spins_and_fixed_points_are_carried(P, orc, lat, np_):
+    from tests import gpu_helpers as G
+
+    print(f"spins and fixed points {lat} {np_}", flush=True)
+    D = 2 if lat == 9 else 3
+    side = int(np.ceil(np_ ** (1.0 / D)))
+    n = (side + 4, side + 5, 1) if D == 2 else (side + 4, side + 5, side + 6)
+    rng = np.random.default_rng(np_ + D)
+    cells = np.stack(np.meshgrid(*[np.arange(side)] * D, indexing="ij")).reshape(D, -1)
+    cells = cells[:, rng.permutation(cells.shape[1])[:np_]]            # ids in no spatial order
+    X = (cells + 2.3 + 0.2 * rng.random((D, np_))).astype(np.float32).astype(np.float64)
+    U = (1e-4 * rng.standard_normal((D, np_))).astype(np.float32).astype(np.float64)
+    d, rp = rng.uniform(0.3, 0.6, np_).astype(np.float32).astype(np.float64), np.full(np_, 2.5)
+    nw = 3 if D == 3 else 1
+    W = np.zeros((3, np_))
+    W[3 - nw:] = (1e-4 * rng.standard_normal((nw, np_))).astype(np.float32)
+    fixed = np.zeros(np_, np.int32)
+    fixed[rng.permutation(np_)[:np_ // 8]] = 1
+    area = np.where(fixed == 1, np.float32(0.3), 0.0)
+    U[:, fixed == 1] = 0.0
+    cfg = P.make_config(lattice=lat, n=n, tau=0.8, gravity=(0, -1e-5, 0), n_sub=50, contact="hertz_mindlin", young=1e3,
+                        bodies=1)
+    sim = P.Sim(cfg, np_)
+    sim.set_particles(X, U, d, rp)
+    sim.set_rotation(W[3 - nw:])
+    sim.set_bodies(np.where(fixed == 1, 0, -1), area=area)
+    oc = G.oracle_cfg(orc, cfg)
+    f, Xo, Uo = G.to_oracle_f(orc, lat, sim.read_populations()), X, U
+    for step in range(2):
+        out = orc.step_full(oc, f, Xo, Uo, d, rp, W=W, hist=None, fixed=fixed, area=area)
+        f, Xo, Uo = out["f"], out["X"], out["U"]
+    sim.step(2)
+    sim.synchronize()
+    got = sim.read_particles()
+    ex = np.abs(got["x"] - Xo).max() / np.abs(Xo - X).max()
+    ev = np.linalg.norm(got["v"] - Uo) / np.linalg.norm(Uo)
+    print(f"  dX={ex:.2e} dU={ev:.2e}", flush=True)
+    assert ex <= 1e-5 and ev <= 1e-5
+    assert np.array_equal(got["x"][:, fixed == 1], X[:, fixed == 1])
+    assert np.array_equal(sim.read_rotation(), W[3 - nw:])             # no contact: spins unchanged
