@@ -1166,14 +1166,16 @@ __global__ __launch_bounds__(256, 8) void k_classify(PState A, PState Bn, int np
 // step, or would close their gap within it at their present speeds, and an
 // island of one in the same position to a wall.  Such an island is likely to
 // be in contact for most of the step and so to take every sub-step, one
-// after the other.  They are ranked apart (rank | TOUCH_BIT) and laid out
-// thinly, ahead of the packed waves (touch_plan).  Only the layout depends on
-// this test: an island's result does not depend on its wave.
-constexpr uint32_t TOUCH_BIT = 0x80000000u;
-constexpr uint32_t CLS_PAIR = WAVE + 2, CLS_WALL = WAVE + 3;     // rank classes of the touching islands
-// What k_collect leaves in irank for the class of the islands: the particle
-// touches its first candidate, a wall.
-constexpr uint32_t TOUCHES_PAIR = 1u, TOUCHES_WALL = 2u;
+// after the other.  They are ranked apart (rank | TOUCH_BIT, and LAST_BIT for
+// pairs whose contact lasts) and laid out ahead of the packed waves
+// (touch_per).  Only the layout depends on these tests: an island's result does
+// not depend on its wave.
+constexpr uint32_t TOUCH_BIT = 0x80000000u, LAST_BIT = 0x40000000u;
+// rank classes of the touching islands: pairs in lasting contact, other pairs, single ones at a wall
+constexpr uint32_t CLS_LAST = WAVE + 2, CLS_PAIR = WAVE + 3, CLS_WALL = WAVE + 4, CLASSES = WAVE + 5;
+// What is left in irank for the class of the islands: the particle touches
+// its first candidate, that contact lasts, it touches a wall.
+constexpr uint32_t TOUCHES_PAIR = 1u, TOUCHES_WALL = 2u, TOUCH_LASTS = 4u;
 template <int D>
 __device__ __forceinline__ float speed_of(const PState& A, uint32_t s) {
     float us = 0.f;
@@ -1183,7 +1185,7 @@ __device__ __forceinline__ float speed_of(const PState& A, uint32_t s) {
 }
 template <int D>
 __device__ __forceinline__ bool touching_wall(uint32_t s, const PState& A, const PCfg& c) {
-    if (c.contact != PIBM_CONTACT_LSD) return false;           // packed in any case (touch_plan)
+    if (c.contact != PIBM_CONTACT_LSD) return false;           // packed in any case (touch_per)
     const float us = speed_of<D>(A, s);
     bool near = false;
 #pragma unroll
@@ -1203,6 +1205,25 @@ __device__ __forceinline__ bool touching_pair(uint32_t s, uint32_t t, const PSta
     }
     const float reach = 0.5f * (A.d[s] + A.d[t]) + speed_of<D>(A, s) + speed_of<D>(A, t);
     return r2 < reach * reach;
+}
+// Whether the contact of s and its candidate t (constants cd) lasts, rather
+// than bounces: with the spring-dashpot, overlap at the start of the step and a
+// normal speed that would change it by less than a twentieth of itself (in
+// units of the contact's period).  Lasting contacts are at 0.001 to 0.02 of
+// it, bouncing ones above 0.06.  The Hertz laws' contacts are soft and last.
+template <int D>
+__device__ __forceinline__ bool contact_lasts(uint32_t s, uint32_t t, const CandData& cd, float ms, const PState& A,
+                                              const PCfg& c) {
+    if (c.contact != PIBM_CONTACT_LSD) return true;
+    const float mt = particle_mass(D, A.d[t], A.rp[t]);
+    const float overlap = 0.5f * cd.K0 / cd.rc;
+    float rv = 0.f, r2 = 0.f;
+#pragma unroll
+    for (int ax = 0; ax < D; ax++) {
+        rv += cd.r0[ax] * (A.u[ax][s] - A.u[ax][t]);
+        r2 += cd.r0[ax] * cd.r0[ax];
+    }
+    return cd.K0 > 0.f && rv * rv * (ms * mt) < 0.0025f * c.kn * overlap * overlap * r2 * (ms + mt);
 }
 // Candidate constants for the sub-steps of particle s and its candidate t (all
 // but the partner's place), candidate entry `entry`.  K0 = r_c^2 - |r0|^2 is formed in
@@ -1292,8 +1313,12 @@ __device__ __forceinline__ uint32_t cand_prep(uint32_t s, uint32_t off, int n, c
     uint32_t touch = touching_wall<D>(s, A, c) ? TOUCHES_WALL : 0u;
     if (n > 0) {
         const float ms = particle_mass(D, A.d[s], A.rp[s]);
-        if (touching_pair<D>(s, cand[off], A)) touch |= TOUCHES_PAIR;
-        for (int k = 0; k < n; k++) cdata[off + k] = cand_entry<D>(s, cand[off + k], off + k, ms, A, c, md);
+        const bool near = touching_pair<D>(s, cand[off], A);
+        for (int k = 0; k < n; k++) {
+            const CandData cd = cand_entry<D>(s, cand[off + k], off + k, ms, A, c, md);
+            cdata[off + k] = cd;
+            if (k == 0 && near) touch |= TOUCHES_PAIR | (contact_lasts<D>(s, cand[off], cd, ms, A, c) ? TOUCH_LASTS : 0u);
+        }
     }
     return touch;
 }
@@ -1449,38 +1474,45 @@ __device__ __forceinline__ void wave_plan(const uint32_t* cls, uint32_t* wb) {
     }
 }
 
-// Layout of the touching islands: `per` of them to a workgroup of the
-// sub-step kernel, in `groups` workgroups.  The sub-steps of one such island
-// are a serial chain that a wave runs no faster for holding fewer islands.
-// But islands that bounce (the spring-dashpot's restitution) hold each other
-// up in a wave, as their checks and jumps fall on different trips: they are
-// laid out as thinly as one workgroup per compute unit allows.  100 touching
-// pairs in 203 x 187 x 211 (3109 sub-steps): the sub-step kernel takes 0.55-0.7
-// ms a step, 1.0 ms in 64 workgroups, 1.2-1.5 ms with eight pairs to a
-// workgroup.  The Hertz laws' contacts are soft and last; they run the same
-// sub-steps in any layout, and few busy compute units are clocked higher than
-// many: 20 pairs in 40 x 61 x 93 0.49 ms packed, 0.55 ms in 10 or 20 workgroups.
-struct TouchPlan {
-    uint32_t per, groups;
+// The touching islands of a step and their layout: touch_per() of a class to
+// a workgroup of the sub-step kernel.  The sub-steps of one such island are a
+// serial chain that a wave runs no faster for holding fewer islands.  But
+// islands that bounce (the spring-dashpot's restitution) hold each other up in
+// a wave, as their checks and jumps fall on different trips: they are laid out
+// as thinly as one workgroup per compute unit allows: 100 pairs made to bounce
+// in 203 x 187 x 211 (3109 sub-steps), the DEM phase 640 us, 950 with four and
+// 1500 with eight to a workgroup.  Contacts that last run the same sub-steps in
+// any layout, and faster in few workgroups: the late phase of 256^3 (2M spheres,
+// steps 1900 to 2000, some 67 lasting pairs and 35 others), the DEM phase 744 us
+// with every pair thin, 676 to 697 with eight lasting ones to a workgroup; 500k
+// disks in 2048^2 (steps 500 to 600, 14 and 43) 181 and 176 us; 20 pairs of
+// Hertz spheres in 40 x 61 x 93 490 us packed, 550 in 10 or 20 workgroups.
+struct Touching {
+    uint32_t lasting, pairs, walls;
+    // lanemember holds the lasting pairs and the others (two entries each),
+    // the single ones, then, from lanes() on, the packed waves of 64
+    __device__ __forceinline__ uint32_t lanes() const {
+        return (2 * (lasting + pairs) + walls + WAVE - 1) / WAVE * WAVE;
+    }
 };
-__device__ __forceinline__ TouchPlan touch_plan(uint32_t islands, uint32_t size, const PCfg& c) {
-    TouchPlan p;
-    const uint32_t most = 16u / size;
-    p.per = c.contact == PIBM_CONTACT_LSD ? min(max((islands + NUM_CU - 1) / NUM_CU, 1u), most) : most;
-    p.groups = (islands + p.per - 1) / p.per;
-    return p;
+__device__ __forceinline__ Touching touching_of(const uint32_t* counters) {
+    return Touching{counters[CNT_TOUCH], counters[CNT_TOUCH + 1], counters[CNT_TOUCH + 2]};
 }
-// lanemember holds the touching pairs (two entries each), the touching
-// islands of one, then, from this offset, the packed waves of 64.
-__device__ __forceinline__ uint32_t touch_lanes(uint32_t pairs, uint32_t walls) {
-    return (2 * pairs + walls + WAVE - 1) / WAVE * WAVE;
+constexpr uint32_t LASTING_PER = 8;
+__device__ __forceinline__ uint32_t touch_per(uint32_t islands, uint32_t size) {
+    return min(max((islands + NUM_CU - 1) / NUM_CU, 1u), 16u / size);
 }
+__device__ __forceinline__ uint32_t groups_of(uint32_t islands, uint32_t per) { return (islands + per - 1) / per; }
 
-// Class of an island from its size and what its root touches.
+// Class of an island from its size and what its root touches, and its rank's
+// marks.
 __device__ __forceinline__ uint32_t island_class(uint32_t size, uint32_t touch) {
     if (size == 1 && (touch & TOUCHES_WALL)) return CLS_WALL;
-    if (size == 2 && (touch & TOUCHES_PAIR)) return CLS_PAIR;
+    if (size == 2 && (touch & TOUCHES_PAIR)) return (touch & TOUCH_LASTS) ? CLS_LAST : CLS_PAIR;
     return size <= WAVE ? size : WAVE + 1;
+}
+__device__ __forceinline__ uint32_t class_marks(uint32_t cls) {
+    return cls == CLS_LAST ? TOUCH_BIT | LAST_BIT : (cls > CLS_LAST ? TOUCH_BIT : 0u);
 }
 
 // islands by size class: 1..64 packed into waves, 65 = larger than a wave
@@ -1489,11 +1521,11 @@ __device__ __forceinline__ uint32_t island_class(uint32_t size, uint32_t touch) 
 __global__ __launch_bounds__(256) void k_island_class(const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ isize, uint32_t* __restrict__ irank,
                                                       uint32_t* __restrict__ bigroot, uint32_t* counters) {
-    __shared__ uint32_t lc[WAVE + 4], gbase[WAVE + 4];     // the last two: touching pairs, touching a wall
+    __shared__ uint32_t lc[CLASSES], gbase[CLASSES];
     const uint32_t t = threadIdx.x;
     const uint32_t na = counters[CNT_ACTIVE];
     for (uint32_t c0 = blockIdx.x * 256; c0 < na; c0 += gridDim.x * 256) {
-        if (t < WAVE + 4) lc[t] = 0;
+        if (t < CLASSES) lc[t] = 0;
         __syncthreads();
         const uint32_t a = c0 + t;
         uint32_t cls = 0, lr = 0;
@@ -1504,12 +1536,12 @@ __global__ __launch_bounds__(256) void k_island_class(const uint32_t* __restrict
         }
         __syncthreads();
         if (t < WAVE + 2 && lc[t] > 0) gbase[t] = atomicAdd(&counters[CNT_CLASS + t], lc[t]);
-        if (t >= CLS_PAIR && t <= CLS_WALL && lc[t] > 0)
-            gbase[t] = atomicAdd(&counters[t == CLS_PAIR ? CNT_PAIRC : CNT_WALLC], lc[t]);
+        if (t >= CLS_LAST && t < CLASSES && lc[t] > 0)
+            gbase[t] = atomicAdd(&counters[CNT_TOUCH + t - CLS_LAST], lc[t]);
         __syncthreads();
         if (root) {
             const uint32_t r = gbase[cls] + lr;
-            irank[a] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
+            irank[a] = r | class_marks(cls);
             if (cls == WAVE + 1) bigroot[r] = a;
         }
         __syncthreads();
@@ -1518,20 +1550,21 @@ __global__ __launch_bounds__(256) void k_island_class(const uint32_t* __restrict
 
 // Member `pos` of an island of size sz and rank `rank` in its class: its place
 // in its wave's or workgroup's lanes (an island larger than a wave: itself).
-__device__ __forceinline__ uint32_t island_place(uint32_t a, uint32_t pos, uint32_t sz, uint32_t rank, const PCfg& c,
+__device__ __forceinline__ uint32_t island_place(uint32_t a, uint32_t pos, uint32_t sz, uint32_t rank,
                                                  int* __restrict__ lanemember, const uint32_t* __restrict__ bigoff,
                                                  uint32_t* __restrict__ bigmember, const uint32_t* wavebase,
-                                                 uint32_t pairs, uint32_t walls) {
+                                                 const Touching& tc) {
     if (sz <= WAVE && (rank & TOUCH_BIT)) {
-        const uint32_t ir = rank & ~TOUCH_BIT;
-        lanemember[sz == 2 ? 2 * ir + pos : 2 * pairs + ir] = (int)a;
-        return (ir % touch_plan(sz == 2 ? pairs : walls, sz, c).per) * sz + pos;
+        const uint32_t ir = rank & ~(TOUCH_BIT | LAST_BIT);
+        const bool last = (rank & LAST_BIT) != 0;
+        lanemember[sz == 1 ? 2 * (tc.lasting + tc.pairs) + ir : 2 * (last ? ir : tc.lasting + ir) + pos] = (int)a;
+        return (ir % (last ? LASTING_PER : touch_per(sz == 2 ? tc.pairs : tc.walls, sz))) * sz + pos;
     }
     if (sz <= WAVE) {
         const uint32_t per = WAVE / sz;
         const uint32_t w = wavebase[sz] + rank / per;
         const uint32_t lane = (rank % per) * sz + pos;
-        lanemember[touch_lanes(pairs, walls) + (long long)w * WAVE + lane] = (int)a;
+        lanemember[tc.lanes() + (long long)w * WAVE + lane] = (int)a;
         return lane;
     }
     bigmember[bigoff[rank] + pos] = a;
@@ -1540,22 +1573,22 @@ __device__ __forceinline__ uint32_t island_place(uint32_t a, uint32_t pos, uint3
 
 // Lane (small islands, packed by size into waves) or slot (large islands)
 // of active particle a; wavebase[s] = first wave of size class s.
-__device__ __forceinline__ void island_place_one(uint32_t a, const PCfg& c, const uint32_t* __restrict__ parent,
+__device__ __forceinline__ void island_place_one(uint32_t a, const uint32_t* __restrict__ parent,
                                                  const uint32_t* __restrict__ isize,
                                                  const uint32_t* __restrict__ irank, uint32_t* __restrict__ fill,
                                                  int* __restrict__ lanemember, uint32_t* __restrict__ loc,
                                                  const uint32_t* __restrict__ bigoff,
                                                  uint32_t* __restrict__ bigmember, const uint32_t* wavebase,
-                                                 uint32_t pairs, uint32_t walls) {
+                                                 const Touching& tc) {
     const uint32_t r = parent[a];
     const uint32_t pos = atomicAdd(&fill[r], 1u);
-    loc[a] = island_place(a, pos, isize[r], irank[r], c, lanemember, bigoff, bigmember, wavebase, pairs, walls);
+    loc[a] = island_place(a, pos, isize[r], irank[r], lanemember, bigoff, bigmember, wavebase, tc);
 }
 
 // Every block first forms the wave plan and the large-island offsets itself
 // (a few hundred loads; it saves a one-block launch); block 0 stores the
 // plan for the sub-step kernels, and every block writes the same offsets.
-__global__ __launch_bounds__(256) void k_island_place(PCfg c, const uint32_t* __restrict__ parent,
+__global__ __launch_bounds__(256) void k_island_place(const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ isize,
                                                       const uint32_t* __restrict__ irank, uint32_t* __restrict__ fill,
                                                       int* __restrict__ lanemember, uint32_t* __restrict__ loc,
@@ -1566,7 +1599,7 @@ __global__ __launch_bounds__(256) void k_island_place(PCfg c, const uint32_t* __
     __shared__ uint32_t wb[WAVE + 1];
     __shared__ uint32_t scan4[4];
     __shared__ uint32_t cls[WAVE + 1];
-    const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
+    const Touching tc = touching_of(counters);
     if (threadIdx.x <= WAVE) cls[threadIdx.x] = counters[CNT_CLASS + threadIdx.x];
     __syncthreads();
     wave_plan(cls, wb);
@@ -1588,7 +1621,7 @@ __global__ __launch_bounds__(256) void k_island_place(PCfg c, const uint32_t* __
     }
     const uint32_t na = counters[CNT_ACTIVE];
     for (uint32_t a = blockIdx.x * 256 + threadIdx.x; a < na; a += gridDim.x * 256)
-        island_place_one(a, c, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, pairs, walls);
+        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wb, tc);
 }
 
 // The partners' places in the candidates' constants.
@@ -1624,18 +1657,18 @@ __global__ __launch_bounds__(256) void k_cand_place(const uint32_t* __restrict__
 // depend on lane placement).
 constexpr int SETUP_THREADS = 1024;
 __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
-    PCfg c, const uint32_t* __restrict__ alist, const uint32_t* __restrict__ ccount,
+    const uint32_t* __restrict__ alist, const uint32_t* __restrict__ ccount,
     const unsigned long long* __restrict__ prefix, const uint32_t* __restrict__ cand,
     const uint32_t* __restrict__ aidx, uint32_t* parent, uint32_t* isize, uint32_t* irank, uint32_t* fill,
     int* lanemember, uint32_t* loc, uint32_t* bigroot, uint32_t* bigoff, uint32_t* bigmember, CandData* cdata,
     uint32_t* counters) {
-    __shared__ uint32_t ccls[WAVE + 4];     // the last two: touching pairs, touching a wall
+    __shared__ uint32_t ccls[CLASSES];
     __shared__ uint32_t wbase[WAVE + 1];
     __shared__ uint32_t lpar[SETUP_THREADS], lsize[SETUP_THREADS], lrank[SETUP_THREADS], lfill[SETUP_THREADS],
         lloc[SETUP_THREADS], lbig[SETUP_THREADS / WAVE], lbigoff[SETUP_THREADS / WAVE];
     const uint32_t t = threadIdx.x;
     const uint32_t na = counters[CNT_ACTIVE];
-    if (t < WAVE + 4) ccls[t] = 0;
+    if (t < CLASSES) ccls[t] = 0;
     if (na <= SETUP_THREADS) {
         // one active particle per thread, islands in LDS
         const bool on = t < na;
@@ -1670,11 +1703,12 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         if (on && root == t) {
             const uint32_t cls = island_class(lsize[t], touch);
             const uint32_t r = atomicAdd(&ccls[cls], 1u);
-            lrank[t] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
+            lrank[t] = r | class_marks(cls);
             if (cls == WAVE + 1) lbig[r] = t;
         }
         __syncthreads();
-        const uint32_t pairs = ccls[CLS_PAIR], walls = ccls[CLS_WALL], nbig = ccls[WAVE + 1];
+        const Touching tc{ccls[CLS_LAST], ccls[CLS_PAIR], ccls[CLS_WALL]};
+        const uint32_t nbig = ccls[WAVE + 1];
         wave_plan(ccls, wbase);
         if (t == SETUP_THREADS - 1) {
             uint32_t o = 0;
@@ -1684,8 +1718,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
                 bigroot[k] = lbig[k];
                 o += lsize[lbig[k]];
             }
-            counters[CNT_PAIRC] = pairs;
-            counters[CNT_WALLC] = walls;
+            for (uint32_t k = 0; k < 3; k++) counters[CNT_TOUCH + k] = ccls[CLS_LAST + k];
             counters[CNT_CLASS + WAVE + 1] = nbig;
             counters[CNT_BIG] = nbig;
         }
@@ -1697,7 +1730,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         if (t == 0) counters[CNT_WAVES] = wbase[0];
         if (on) {
             const uint32_t pos = atomicAdd(&lfill[root], 1u), sz = lsize[root], rank = lrank[root];
-            lloc[t] = island_place(t, pos, sz, rank, c, lanemember, lbigoff, bigmember, wbase, pairs, walls);
+            lloc[t] = island_place(t, pos, sz, rank, lanemember, lbigoff, bigmember, wbase, tc);
             parent[t] = root;
             isize[t] = sz;
         }
@@ -1718,11 +1751,11 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         if (parent[a] != a) continue;
         const uint32_t cls = island_class(isize[a], irank[a]);
         uint32_t r = atomicAdd(&ccls[cls], 1u);
-        irank[a] = cls >= CLS_PAIR ? (r | TOUCH_BIT) : r;
+        irank[a] = r | class_marks(cls);
         if (cls == WAVE + 1) bigroot[r] = a;
     }
     __syncthreads();
-    const uint32_t pairs = ccls[CLS_PAIR], walls = ccls[CLS_WALL];
+    const Touching tc{ccls[CLS_LAST], ccls[CLS_PAIR], ccls[CLS_WALL]};
     wave_plan(ccls, wbase);
     __syncthreads();
     if (t < WAVE) {
@@ -1730,8 +1763,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
         counters[CNT_CLASS + t + 1] = ccls[t + 1];
     }
     if (t == 0) {
-        counters[CNT_PAIRC] = pairs;
-        counters[CNT_WALLC] = walls;
+        for (uint32_t k = 0; k < 3; k++) counters[CNT_TOUCH + k] = ccls[CLS_LAST + k];
         counters[CNT_WAVES] = wbase[0];
         const uint32_t nbig = ccls[WAVE + 1];
         counters[CNT_CLASS + WAVE + 1] = nbig;
@@ -1744,7 +1776,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_island_setup(
     }
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
-        island_place_one(a, c, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, pairs, walls);
+        island_place_one(a, parent, isize, irank, fill, lanemember, loc, bigoff, bigmember, wbase, tc);
     __syncthreads();
     for (uint32_t a = t; a < na; a += SETUP_THREADS)
         cand_place_one(a, alist, ccount, prefix, cand, aidx, loc, cdata);
@@ -3259,27 +3291,27 @@ __global__ __launch_bounds__(64) void k_island_quads(PState A, PState Bn, int np
                                                      uint32_t* __restrict__ flags,
                                                      const uint32_t* __restrict__ counters, MdBuf md) {
     const uint32_t nw = counters[CNT_WAVES];
-    const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
-    const TouchPlan tp = touch_plan(pairs, 2, c);
+    const Touching tc = touching_of(counters);                       // (every touching pair is a lasting one here)
+    const uint32_t tl = groups_of(tc.lasting, LASTING_PER);
     const int lane = threadIdx.x;
     const uint32_t wb_lane = counters[CNT_WAVEBASE + 1 + lane];
     const uint32_t nw2 = min(nw, counters[CNT_WAVEBASE + 3]);        // waves of islands of one and two
-    for (uint32_t v = blockIdx.x; v < tp.groups + (nw - nw2) * MD_PARTS; v += gridDim.x) {
+    for (uint32_t v = blockIdx.x; v < tl + (nw - nw2) * MD_PARTS; v += gridDim.x) {
         int sz = 2, lane0 = 0, nl;
         const int* member;
-        if (v < tp.groups) {
-            const uint32_t i0 = v * tp.per;
-            nl = 2 * (int)min(tp.per, pairs - i0);
+        if (v < tl) {
+            const uint32_t i0 = v * LASTING_PER;
+            nl = 2 * (int)min(LASTING_PER, tc.lasting - i0);
             member = lanemember + 2 * i0;
         } else {
-            const uint32_t w = nw2 + (v - tp.groups) / MD_PARTS, part = (v - tp.groups) % MD_PARTS;
+            const uint32_t w = nw2 + (v - tl) / MD_PARTS, part = (v - tl) % MD_PARTS;
             const unsigned long long le = __ballot(wb_lane <= w);
             sz = 64 - __clzll(le);
             if (sz > 16) continue;
             const uint32_t per = WAVE / sz;
             const uint32_t idx = w - counters[CNT_WAVEBASE + sz];
             nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
-            member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
+            member = lanemember + tc.lanes() + (long long)w * WAVE;
             const int take = md_take(sz);
             lane0 = (int)part * take;
             nl = min(nl - lane0, take);
@@ -3333,8 +3365,9 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     __shared__ CandData scd[WAVE * CAND_LDS];
     __shared__ float4 smd[MD ? WAVE * CAND_LDS * MD_LDS : 1];
     const uint32_t nw = counters[CNT_WAVES];
-    const uint32_t pairs = counters[CNT_PAIRC], walls = counters[CNT_WALLC];
-    const TouchPlan tp = touch_plan(pairs, 2, c), tw = touch_plan(walls, 1, c);
+    const Touching tc = touching_of(counters);
+    const uint32_t pper = touch_per(tc.pairs, 2), wper = touch_per(tc.walls, 1);
+    const uint32_t tl = groups_of(tc.lasting, LASTING_PER), tp = tl + groups_of(tc.pairs, pper);
     const int lane = threadIdx.x;
     // first wave of size class lane + 1 (non-decreasing in the class)
     const uint32_t wb_lane = counters[CNT_WAVEBASE + 1 + lane];
@@ -3349,7 +3382,7 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
     constexpr uint32_t QUARTERS = MD ? 1u : 4u;
     // islands of three to eight: parts of eight members (the split form NC = 2)
     const uint32_t nw2 = min(nw, counters[CNT_WAVEBASE + 3]);
-    const uint32_t nt = tp.groups + tw.groups;
+    const uint32_t nt = tp + groups_of(tc.walls, wper);
     for (uint32_t v = blockIdx.x; v < nt + nw2 * QUARTERS + (nw - nw2) * MD_PARTS; v += gridDim.x) {
         // islands of size sz at lanes [lane0, lane0 + nl) of the entries from `member`
         int sz, lane0 = 0, nl;
@@ -3357,10 +3390,13 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
         bool split = !MD, rows = false;
         const bool quads = MD && !c.microslip;
         if (v < nt) {
-            sz = v < tp.groups ? 2 : 1;
-            const uint32_t i0 = sz == 2 ? v * tp.per : (v - tp.groups) * tw.per;
-            nl = sz * (int)(sz == 2 ? min(tp.per, pairs - i0) : min(tw.per, walls - i0));
-            member = lanemember + (sz == 2 ? 2 * i0 : 2 * pairs + i0);
+            // this class's islands per workgroup, all of them, and its first entry
+            const uint32_t per = v < tl ? LASTING_PER : (v < tp ? pper : wper);
+            const uint32_t all = v < tl ? tc.lasting : (v < tp ? tc.pairs : tc.walls);
+            const uint32_t i0 = (v - (v < tl ? 0u : (v < tp ? tl : tp))) * per;
+            sz = v < tp ? 2 : 1;
+            nl = sz * (int)min(per, all - i0);
+            member = lanemember + 2 * (v < tl ? 0u : (v < tp ? tc.lasting : tc.lasting + tc.pairs)) + sz * i0;
         } else {
             // the wave's size class is the largest whose first wave is <= w;
             // its islands fill lanes [0, islands_here * size)
@@ -3375,7 +3411,7 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
             const uint32_t per = WAVE / sz;
             const uint32_t idx = w - counters[CNT_WAVEBASE + sz];
             nl = (int)min(per, counters[CNT_CLASS + sz] - idx * per) * sz;
-            member = lanemember + touch_lanes(pairs, walls) + (long long)w * WAVE;
+            member = lanemember + tc.lanes() + (long long)w * WAVE;
             split = split && sz <= 2;
             rows = !MD && sz >= 3 && sz <= 8;
             const bool part_of = split || rows || (quads && sz >= 3 && sz <= 16);
@@ -3436,7 +3472,7 @@ __global__ __launch_bounds__(64) void k_island_small(PState A, PState Bn, int np
         }
         // the general loop: the whole wave, or this workgroup's lanes of it
         bool valid = lane >= lane0 && lane < lane0 + nl;
-        if (MD && quads && (v < tp.groups || sz >= 3)) {
+        if (MD && quads && (v < tl || sz >= 3)) {
             // but for the islands that k_island_quads works
             const MdForms forms = md_forms<D>(sz, lane0, nl, member, A, c, alist, ccount, prefix, cdata);
             valid = valid && forms.of(lane - lane0) == MD_GENERAL;
@@ -4327,7 +4363,7 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
     if (one_group) collect(raw ? &k_collect<D, true, true> : &k_collect<D, false, true>);
     else collect(raw ? &k_collect<D, true, false> : &k_collect<D, false, false>);
     if (one_group) {
-        hipLaunchKernelGGL(k_island_setup, dim3(1), dim3(SETUP_THREADS), 0, s, c, b.alist, b.ccount, b.prefix,
+        hipLaunchKernelGGL(k_island_setup, dim3(1), dim3(SETUP_THREADS), 0, s, b.alist, b.ccount, b.prefix,
                            b.cand, b.aidx, b.parent, b.isize, b.irank, b.fill, b.lanemember, b.loc, b.bigroot,
                            b.bigoff, b.bigmember, b.cdata, b.counters);
     } else {
@@ -4336,7 +4372,7 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
         hipLaunchKernelGGL(k_uf_flatten, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.counters);
         hipLaunchKernelGGL(k_island_class, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.irank, b.bigroot,
                            b.counters);
-        hipLaunchKernelGGL(k_island_place, dim3(grid_act), dim3(256), 0, s, c, b.parent, b.isize, b.irank, b.fill,
+        hipLaunchKernelGGL(k_island_place, dim3(grid_act), dim3(256), 0, s, b.parent, b.isize, b.irank, b.fill,
                            b.lanemember, b.loc, b.bigoff, b.bigmember, b.bigroot, b.counters);
         hipLaunchKernelGGL(k_cand_place, dim3(grid_act), dim3(256), 0, s, b.alist, b.ccount, b.prefix, b.cand,
                            b.aidx, b.loc, b.cdata, b.counters);

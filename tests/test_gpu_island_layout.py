@@ -96,3 +96,36 @@ def test_touching_islands_match_oracle(P, orc, lat, contact, setup):
         w = sim.read_rotation()
         ref = Wo if D == 3 else Wo[2:3]
         assert np.linalg.norm(w - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("lat", [9, 19])
+@pytest.mark.parametrize("lasting,closing,walls", [(1, 0, 0), (8, 1, 1), (9, 257, 3), (20, 7, 0)])
+def test_lasting_and_closing_pairs_match_oracle(P, orc, lat, lasting, closing, walls):
+    """Spring-dashpot pairs that overlap and move together (laid out eight to
+    a workgroup) beside pairs that close in (one to a workgroup, two above
+    256) and particles at a wall; the same bits by both island set-ups."""
+    print(f"lasting and closing pairs {lat} {lasting} {closing} {walls}", flush=True)
+    D = 2 if lat == 9 else 3
+    n, X, U, d = _touching(D, lasting + closing, max(walls, 1), 0)
+    if walls == 0:
+        X, U, d = X[:, :-1], U[:, :-1], d[:-1]
+    U[:, 1:2 * lasting:2] = U[:, 0:2 * lasting:2]
+    rp = np.full(X.shape[1], 2.5)
+    g = [0.0, 0.0, 0.0]
+    g[D - 1] = -1e-5
+    got = []
+    for setup in (1, 2):
+        cfg = P.make_config(lattice=lat, n=n, tau=0.8, gravity=g, n_sub=100, contact="lsd", island_setup=setup)
+        sim = P.Sim(cfg, X.shape[1])
+        sim.set_particles(X, U, d, rp)
+        f = G.to_oracle_f(orc, lat, sim.read_populations())
+        sim.step(1)
+        sim.synchronize()
+        got.append(sim.read_particles())
+    out = orc.step(G.oracle_cfg(orc, cfg), f, X, U, d, rp)
+    ex = np.abs(got[0]["x"] - out["X"]).max() / np.abs(out["X"] - X).max()
+    ev = np.linalg.norm(got[0]["v"] - out["U"]) / np.linalg.norm(out["U"])
+    print(f"  {X.shape[1]} particles dX={ex:.2e} dU={ev:.2e}", flush=True)
+    assert ex <= 1e-5 and ev <= 1e-5
+    for k in ("x", "v", "f_hydro", "f_contact"):
+        assert np.array_equal(got[0][k], got[1][k]), k
