@@ -53,6 +53,64 @@ __device__ __forceinline__ void block_sum256(float* red, int t) {
     }
 }
 
+// One workgroup's share of the lists: LIST_BINS bins' starts, and its part of
+// the diameters and densities.
+constexpr int LIST_BINS = 2048;
+__device__ __forceinline__ void rebuild_lists(const TapeLists& l) {
+    __shared__ uint32_t hist[LIST_BINS];
+    __shared__ uint32_t sh[4];
+    const int t = threadIdx.x;
+    for (long long i = (long long)blockIdx.x * 256 + t; i < l.np; i += (long long)l.blocks * 256) {
+        const int id = l.id[i];
+        l.d[i] = l.d_id[id];
+        l.rp[i] = l.rp_id[id];
+    }
+    constexpr int PER = LIST_BINS / 256;
+#pragma unroll
+    for (int k = 0; k < PER; k++) hist[k * 256 + t] = 0u;
+    // the particles before the share's first bin: 256 probes at a time
+    const uint32_t first = blockIdx.x * (uint32_t)LIST_BINS;
+    int lo = 0, hi = l.np;
+    while (hi - lo > 256) {
+        const int step = (hi - lo + 256) / 257;
+        const long long p = lo + (long long)(t + 1) * step - 1;
+        lo += __syncthreads_count(p < hi && l.keys[p] < first) * step;
+        hi = min(hi, lo + step);
+    }
+    lo += __syncthreads_count(lo + t < hi && l.keys[lo + t] < first);
+    // those in its bins
+    for (int i = lo;; i += 256) {
+        const uint32_t bin = i + t < l.np ? l.keys[i + t] - first : (uint32_t)LIST_BINS;
+        const bool in = bin < (uint32_t)LIST_BINS;
+        if (in) atomicAdd(&hist[bin], 1u);
+        if (__syncthreads_count(in) < 256) break;
+    }
+    uint32_t v[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        v[k] = hist[t * PER + k];
+        sum += v[k];
+    }
+    uint32_t run = sum;
+#pragma unroll
+    for (int off = 1; off < WAVE; off <<= 1) {
+        const uint32_t up = __shfl_up(run, off, WAVE);
+        if ((t & 63) >= off) run += up;
+    }
+    if ((t & 63) == 63) sh[t >> 6] = run;
+    __syncthreads();
+    run += (uint32_t)lo - sum;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        if (k < (t >> 6)) run += sh[k];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const long long bin = (long long)first + t * PER + k;
+        if (bin <= l.nbins) l.start[bin] = run;
+        run += v[k];
+    }
+}
+
 // Reverse of the collision at every node.  In:  abar = adjoint of the
 // populations after streaming; f_t and the force field F_t of the forward
 // step.  Out: the moments of f_t (for the interpolation adjoint), F-bar, the
@@ -60,17 +118,26 @@ __device__ __forceinline__ void block_sum256(float* red, int t) {
 // sum of d/dtau per block.
 //   f*_q = f_q - (f_q - feq_q(rho, u)) / tau + (1 - 1/(2 tau)) S_q(u, F),
 //   u = (j + F/2) / rho;  d f*_q / d tau = (f_q - feq_q) / tau^2 + S_q / (2 tau^2)
+// The first lists.blocks workgroups rebuild the step's cell list meanwhile, for
+// k_adj_particles and the spreading of its adjoints.  (On the tape the bin
+// starts were a twelfth of a step of 10,000 disks in 512^2, 1.05 of 13.0 MB;
+// their copy took 1.5 us of the sort, rebuilding them 1.8 us here, 10.6 -> 12.4.)
 template <int Q, class S>
 __global__ __launch_bounds__(256) void k_adj_collide(const float* __restrict__ abar,
                                                      const typename S::T* __restrict__ ft,
                                                      const float* __restrict__ Ft, int hasF, float ffx, float ffy,
                                                      float ffz, Grid g, float tau, S st, float4* __restrict__ mom,
                                                      float* __restrict__ Fbar, float4* __restrict__ Mc,
-                                                     float* __restrict__ tpart) {
+                                                     float* __restrict__ tpart, TapeLists lists) {
     using L = Lattice<Q>;
+    if (blockIdx.x < lists.blocks) {
+        rebuild_lists(lists);
+        return;
+    }
     __shared__ float red[256];
+    const unsigned block = blockIdx.x - lists.blocks;
     const long long N = g.N;
-    const long long r = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long r = (long long)block * 256 + threadIdx.x;
     float tsum = 0.f;
     if (r < N) {
         const int nx = g.n[0], ny = g.n[1];
@@ -137,7 +204,7 @@ __global__ __launch_bounds__(256) void k_adj_collide(const float* __restrict__ a
     }
     red[threadIdx.x] = tsum;
     block_sum256(red, threadIdx.x);
-    if (threadIdx.x == 0) tpart[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) tpart[block] = red[0];
 }
 
 // (ahi, alo) += (bhi, blo), double-float.
@@ -538,26 +605,19 @@ __global__ __launch_bounds__(256) void k_save_const(PState A, int np, float* __r
     rp[id] = A.rp[s];
 }
 
-// One step's particle state and cell list as the sort left them, for the
-// reverse step: words [xh D][xl D][u D][d][rp][id][key] x np, then the
-// nbins + 1 bin starts.
-__global__ __launch_bounds__(256) void k_save_tape(PState A, const uint32_t* __restrict__ keys,
-                                                   const uint32_t* __restrict__ start, int np, int D, long long nb1,
+// One step's particles as the sort left them, for the reverse step: words
+// [xh D][xl D][u D][id][key] x np.
+__global__ __launch_bounds__(256) void k_save_tape(PState A, const uint32_t* __restrict__ keys, int np, int D,
                                                    uint32_t* __restrict__ out) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < np) {
-        for (int a = 0; a < D; a++) {
-            out[(long long)a * np + i] = __float_as_uint(A.xh[a][i]);
-            out[(long long)(D + a) * np + i] = __float_as_uint(A.xl[a][i]);
-            out[(long long)(2 * D + a) * np + i] = __float_as_uint(A.u[a][i]);
-        }
-        out[(long long)(3 * D) * np + i] = __float_as_uint(A.d[i]);
-        out[(long long)(3 * D + 1) * np + i] = __float_as_uint(A.rp[i]);
-        out[(long long)(3 * D + 2) * np + i] = (uint32_t)A.id[i];
-        out[(long long)(3 * D + 3) * np + i] = keys[i];
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= np) return;
+    for (int a = 0; a < D; a++) {
+        out[(long long)a * np + i] = __float_as_uint(A.xh[a][i]);
+        out[(long long)(D + a) * np + i] = __float_as_uint(A.xl[a][i]);
+        out[(long long)(2 * D + a) * np + i] = __float_as_uint(A.u[a][i]);
     }
-    uint32_t* so = out + (long long)(3 * D + 4) * np;
-    for (long long k = 4 * i; k < min(4 * i + 4, nb1); k++) so[k] = start[k];
+    out[(long long)(3 * D) * np + i] = (uint32_t)A.id[i];
+    out[(long long)(3 * D + 1) * np + i] = keys[i];
 }
 
 // Id-order state -> PState A in id order (the next sort orders it).
@@ -606,17 +666,14 @@ void adj_save_state(int D, const PBuf& b, int np, float* out, hipStream_t s) {
     hipLaunchKernelGGL(k_save_state, dim3(blocks256(np)), dim3(256), 0, s, b.A, np, D, out);
 }
 
-long long adj_tape_words(int D, int np, long long nbins) {
-    return ((3LL * D + 4) * np + nbins + 1 + 63) / 64 * 64;
+long long adj_tape_words(int D, int np) { return ((3LL * D + 2) * np + 63) / 64 * 64; }
+
+void adj_save_tape(int D, const PBuf& b, int np, uint32_t* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_save_tape, dim3(blocks256(np)), dim3(256), 0, s, b.A, b.keys_sorted, np, D, out);
 }
 
-void adj_save_tape(int D, const PBuf& b, int np, long long nbins, uint32_t* out, hipStream_t s) {
-    const long long n = std::max<long long>(np, (nbins + 4) / 4);
-    hipLaunchKernelGGL(k_save_tape, dim3(blocks256(n)), dim3(256), 0, s, b.A, b.keys_sorted, b.start, np, D, nbins + 1,
-                       out);
-}
-
-// The buffers b with the particle state and cell list of a saved step.
+// The buffers b with the positions, velocities, ids and keys of a saved step
+// (the rest of its cell list is rebuilt in b's own arrays: adj_tape_lists).
 PBuf adj_tape_view(int D, const PBuf& b, int np, uint32_t* in) {
     PBuf v = b;
     for (int a = 0; a < D; a++) {
@@ -624,12 +681,14 @@ PBuf adj_tape_view(int D, const PBuf& b, int np, uint32_t* in) {
         v.A.xl[a] = (float*)in + (long long)(D + a) * np;
         v.A.u[a] = (float*)in + (long long)(2 * D + a) * np;
     }
-    v.A.d = (float*)in + 3LL * D * np;
-    v.A.rp = (float*)in + (3LL * D + 1) * np;
-    v.A.id = (int*)in + (3LL * D + 2) * np;
-    v.keys_sorted = in + (3LL * D + 3) * np;
-    v.start = in + (3LL * D + 4) * np;
+    v.A.id = (int*)in + 3LL * D * np;
+    v.keys_sorted = in + (3LL * D + 1) * np;
     return v;
+}
+
+TapeLists adj_tape_lists(const PBuf& v, int np, long long nbins, const float* d_id, const float* rp_id) {
+    return TapeLists{v.keys_sorted, v.A.id, d_id, rp_id, v.start, v.A.d, v.A.rp, np, nbins,
+                     (unsigned)(nbins / LIST_BINS + 1)};
 }
 
 void adj_save_const(const PBuf& b, int np, float* d, float* rp, hipStream_t s) {
@@ -650,24 +709,25 @@ int adj_particle_blocks(int D, int np) { return (int)blocks256((long long)np * a
 template <int Q, class S>
 static void collide_launch(const float* abar, const void* ft, const float* Ft, int hasF, const float* ff,
                            const Grid& g, float tau, S st, float4* mom, float* Fbar, float4* Mc, float* tpart,
-                           hipStream_t s) {
-    hipLaunchKernelGGL((k_adj_collide<Q, S>), dim3(blocks256(g.N)), dim3(256), 0, s, abar,
-                       (const typename S::T*)ft, Ft, hasF, ff[0], ff[1], ff[2], g, tau, st, mom, Fbar, Mc, tpart);
+                           const TapeLists& lists, hipStream_t s) {
+    hipLaunchKernelGGL((k_adj_collide<Q, S>), dim3(blocks256(g.N) + lists.blocks), dim3(256), 0, s, abar,
+                       (const typename S::T*)ft, Ft, hasF, ff[0], ff[1], ff[2], g, tau, st, mom, Fbar, Mc, tpart,
+                       lists);
 }
 
 void adj_collide(int Q, int fp16, int sl2, const float* abar, const void* ft, const float* Ft, int hasF,
                  const float* ff, const Grid& g, float tau, float4* mom, float* Fbar, float4* Mc, float* tpart,
-                 hipStream_t s) {
+                 const TapeLists& lists, hipStream_t s) {
     const float sc = std::ldexp(1.0f, sl2), isc = std::ldexp(1.0f, -sl2);
     if (Q == 19) {
-        if (fp16) collide_launch<19>(abar, ft, Ft, hasF, ff, g, tau, StoreF16{sc, isc}, mom, Fbar, Mc, tpart, s);
-        else collide_launch<19>(abar, ft, Ft, hasF, ff, g, tau, StoreF32{1.f, 1.f}, mom, Fbar, Mc, tpart, s);
+        if (fp16) collide_launch<19>(abar, ft, Ft, hasF, ff, g, tau, StoreF16{sc, isc}, mom, Fbar, Mc, tpart, lists, s);
+        else collide_launch<19>(abar, ft, Ft, hasF, ff, g, tau, StoreF32{1.f, 1.f}, mom, Fbar, Mc, tpart, lists, s);
     } else if (Q == 15) {
-        if (fp16) collide_launch<15>(abar, ft, Ft, hasF, ff, g, tau, StoreF16{sc, isc}, mom, Fbar, Mc, tpart, s);
-        else collide_launch<15>(abar, ft, Ft, hasF, ff, g, tau, StoreF32{1.f, 1.f}, mom, Fbar, Mc, tpart, s);
+        if (fp16) collide_launch<15>(abar, ft, Ft, hasF, ff, g, tau, StoreF16{sc, isc}, mom, Fbar, Mc, tpart, lists, s);
+        else collide_launch<15>(abar, ft, Ft, hasF, ff, g, tau, StoreF32{1.f, 1.f}, mom, Fbar, Mc, tpart, lists, s);
     } else {
-        if (fp16) collide_launch<9>(abar, ft, Ft, hasF, ff, g, tau, StoreF16{sc, isc}, mom, Fbar, Mc, tpart, s);
-        else collide_launch<9>(abar, ft, Ft, hasF, ff, g, tau, StoreF32{1.f, 1.f}, mom, Fbar, Mc, tpart, s);
+        if (fp16) collide_launch<9>(abar, ft, Ft, hasF, ff, g, tau, StoreF16{sc, isc}, mom, Fbar, Mc, tpart, lists, s);
+        else collide_launch<9>(abar, ft, Ft, hasF, ff, g, tau, StoreF32{1.f, 1.f}, mom, Fbar, Mc, tpart, lists, s);
     }
 }
 

@@ -297,25 +297,15 @@ __global__ void k_scatter(const uint32_t* __restrict__ keys, const uint32_t* __r
 }
 
 // Final slot = bin start + rank of the particle's id among its bin.  TAPE: the
-// sorted state, keys and bin starts also to a rollout's tape (a launch of its
-// own took 4.2 us of a step of 10,000 disks in 512^2 after 4.7 us here; now 6.8).
+// sorted state and keys also to a rollout's tape (a launch of its own took 4.2 us
+// of a step of 10,000 disks in 512^2 after 4.7 us here; now 5.2).
 template <int D, bool TAPE>
 __global__ __launch_bounds__(256) void k_reorder(PState A, PState B, const uint32_t* __restrict__ keys,
                                                  const uint32_t* __restrict__ start,
                                                  const int* __restrict__ tmpid,
                                                  uint32_t* __restrict__ keys_sorted, float4* __restrict__ pos4,
-                                                 int np, PState tape, uint32_t* __restrict__ tape_keys,
-                                                 uint32_t* __restrict__ tape_start, long long nb1) {
+                                                 int np, PState tape, uint32_t* __restrict__ tape_keys) {
     int s = xcd_block() * 256 + threadIdx.x;
-    if (TAPE) {
-        const long long k0 = 4LL * s;
-        uint32_t v[4];
-#pragma unroll
-        for (int k = 0; k < 4; k++) v[k] = k0 + k < nb1 ? start[k0 + k] : 0u;
-#pragma unroll
-        for (int k = 0; k < 4; k++)
-            if (k0 + k < nb1) tape_start[k0 + k] = v[k];
-    }
     if (s >= np) return;
     uint32_t k = keys[s];
     uint32_t b0 = start[k], b1 = start[k + 1];
@@ -344,8 +334,6 @@ __global__ __launch_bounds__(256) void k_reorder(PState A, PState B, const uint3
             tape.xl[a][o] = A.xl[a][s];
             tape.u[a][o] = A.u[a][s];
         }
-        tape.d[o] = A.d[s];
-        tape.rp[o] = A.rp[s];
         tape.id[o] = myid;
         tape_keys[o] = k;
     }
@@ -4247,12 +4235,11 @@ static bool sort_impl(PBuf& b, int np, const PCfg& c, bool unordered, const PBuf
         return false;
     }
     if (tape) {
-        const long long threads = std::max<long long>(np, (c.nbins + 4) / 4);
-        hipLaunchKernelGGL((k_reorder<D, true>), dim3(nb256(threads)), dim3(256), 0, s, b.A, b.B, b.keys, b.start,
-                           b.tmpid, b.keys_sorted, b.pos4, np, tape->A, tape->keys_sorted, tape->start, c.nbins + 1);
+        hipLaunchKernelGGL((k_reorder<D, true>), dim3(nb256(np)), dim3(256), 0, s, b.A, b.B, b.keys, b.start, b.tmpid,
+                           b.keys_sorted, b.pos4, np, tape->A, tape->keys_sorted);
     } else {
         hipLaunchKernelGGL((k_reorder<D, false>), dim3(nb256(np)), dim3(256), 0, s, b.A, b.B, b.keys, b.start, b.tmpid,
-                           b.keys_sorted, b.pos4, np, PState{}, nullptr, nullptr, 0LL);
+                           b.keys_sorted, b.pos4, np, PState{}, nullptr);
     }
     std::swap(b.A, b.B);
     return tape != nullptr;

@@ -403,6 +403,20 @@ template <int D> struct SRec {
     static constexpr int COEF = 4 * D + 1;
 };
 
+// What the reverse step rebuilds of a taped step's cell list, rather than hold
+// it for every step: the bin starts from the sorted keys, diameters and
+// densities in sorted order from those in id order.
+struct TapeLists {
+    const uint32_t* keys;
+    const int* id;
+    const float *d_id, *rp_id;
+    uint32_t* start;
+    float *d, *rp;
+    int np;
+    long long nbins;
+    unsigned blocks;         // workgroups that do it (0: nothing to rebuild)
+};
+
 // Device buffers of the particle side (carved from the workspace).
 struct PBuf {
     PState A, B, Bn;             // current, reorder target, next (after DEM)

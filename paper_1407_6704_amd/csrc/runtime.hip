@@ -57,13 +57,14 @@ int adj_collide_blocks(long long N);
 int adj_particle_blocks(int D, int np);
 void adj_collide(int Q, int fp16, int sl2, const float* abar, const void* ft, const float* Ft, int hasF,
                  const float* ff, const Grid& g, float tau, float4* mom, float* Fbar, float4* Mc, float* tpart,
-                 hipStream_t s);
+                 const TapeLists& lists, hipStream_t s);
 void adj_assemble(int Q, const float* abar, const float4* Mc, const float* Sf, int hasS, const Grid& g, float tau,
                   float* abar_out, const float* tpart, int ntb, const float* gpart, int ngb, float* acc,
                   hipStream_t s);
-long long adj_tape_words(int D, int np, long long nbins);
-void adj_save_tape(int D, const PBuf& b, int np, long long nbins, uint32_t* out, hipStream_t s);
+long long adj_tape_words(int D, int np);
+void adj_save_tape(int D, const PBuf& b, int np, uint32_t* out, hipStream_t s);
 PBuf adj_tape_view(int D, const PBuf& b, int np, uint32_t* in);
+TapeLists adj_tape_lists(const PBuf& v, int np, long long nbins, const float* d_id, const float* rp_id);
 void adj_particles(int D, PBuf& b, int np, const Grid& g, const PCfg& c, int two_way, const float4* mom,
                    const float* Fbar, const float* xbh, const float* xbl, const float* ub, float* xbh_o,
                    float* xbl_o, float* ub_o, float* coefS, float* gpart, hipStream_t s);
@@ -80,7 +81,7 @@ struct Rollout {
     float *d_id = nullptr, *rp_id = nullptr;
     char* tape_f = nullptr;       // populations at the start of each step of one segment
     float* tape_F = nullptr;      // force field of each step of one segment
-    uint32_t* tape_p = nullptr;   // sorted particle state and cell list of each step of one segment
+    uint32_t* tape_p = nullptr;   // sorted particles of each step of one segment
     long long tape_words = 0;     // words per step
     float* abar[2] = {nullptr, nullptr};
     float* Fbar = nullptr;
@@ -426,7 +427,7 @@ size_t carve_rollout(const pibm_ctx& c, int steps, int K, char* base, Rollout& R
     const long long len = std::max(1, std::min(K, steps));
     R.tape_f = cv.take<char>(len * fbytes);
     R.tape_F = cv.take<float>(len * D * N);
-    R.tape_words = adj_tape_words(c.D, c.np, c.pc.nbins);
+    R.tape_words = adj_tape_words(c.D, c.np);
     R.tape_p = cv.take<uint32_t>(len * R.tape_words);
     for (int k = 0; k < 2; k++) R.abar[k] = cv.take<float>((size_t)c.Q * N);
     R.Fbar = cv.take<float>(D * N);
@@ -482,12 +483,12 @@ void ensure_force(pibm_ctx* c) {
     c->F_stale = false;
 }
 
-// tape (nullable): where the sorted particles and the cell list are saved.
+// tape (nullable): where the sorted particles are saved.
 void sort_particles(pibm_ctx* c, uint32_t* tape = nullptr) {
     PBuf view;
     if (tape) view = adj_tape_view(c->D, c->pb, c->np, tape);
     const bool saved = particles_sort(c->D, c->pb, c->np, c->pc, c->unordered, tape ? &view : nullptr, c->stream);
-    if (tape && !saved) adj_save_tape(c->D, c->pb, c->np, c->pc.nbins, tape, c->stream);
+    if (tape && !saved) adj_save_tape(c->D, c->pb, c->np, tape, c->stream);
     c->unordered = false;
 }
 
@@ -960,7 +961,7 @@ constexpr uint32_t ONE_GROUP_MAX = 1024;   // one pass per phase: faster than ni
 // one dual cell and FP32 storage is fused into the collision (with FP16
 // storage the collision is short enough that the fused tile order costs
 // more than the force field's traffic saves).
-// tape (nullable): where the sorted particles and the cell list are saved.
+// tape (nullable): where the sorted particles are saved.
 hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int row, bool want_F,
                        uint32_t* tape = nullptr) {
     HipSeq q;
@@ -1147,11 +1148,13 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
         }
         // reverse it
         for (int k = len - 1; k >= 0; k--) {
-            // the step's own sorted particles and cell list, as the tape holds
-            // them (rebuilding them took six launches a step)
+            // the step's own sorted particles, as the tape holds them, and its
+            // cell list, rebuilt from them beside the collision (sorting them
+            // anew took six launches a step)
             PBuf pb = adj_tape_view(D, c->pb, np, R.tape_p + k * R.tape_words);
+            const TapeLists lists = adj_tape_lists(pb, np, c->pc.nbins, R.d_id, R.rp_id);
             adj_collide(Q, c->fp16, c->sl2, R.abar[cur], R.tape_f + k * fbytes, R.tape_F + (size_t)k * D * N, spread,
-                        ff, c->grid, tau, c->mom, R.Fbar, R.Mc, R.tpart, s);
+                        ff, c->grid, tau, c->mom, R.Fbar, R.Mc, R.tpart, lists, s);
             adj_particles(D, pb, np, c->grid, c->pc, spread, c->mom, R.Fbar, R.xbh[cur], R.xbl[cur], R.ub[cur],
                           R.xbh[1 - cur], R.xbl[1 - cur], R.ub[1 - cur], R.coefS, R.gpart, s);
             particles_spread_adjoint(D, pb, np, c->pc, c->grid, R.coefS, R.Sf, s);
@@ -1204,7 +1207,7 @@ pibm_status pibm_adjoint_stage(pibm_ctx* c, int32_t stage, const float* in0, con
                              (float)c->cfg.fluid_force[2]};
         adj_fill(R.acc, 8, 0.f, s);
         adj_collide(Q, c->fp16, c->sl2, in0, c->fA, c->F, np > 0 && spread, ff, c->grid, tau, c->mom, out1, R.Mc,
-                    R.tpart, s);
+                    R.tpart, TapeLists{}, s);
         adj_assemble(Q, in0, R.Mc, nullptr, 0, c->grid, tau, out0, R.tpart, adj_collide_blocks(N), nullptr, 0, R.acc, s);
         nsc = 1;
         break;

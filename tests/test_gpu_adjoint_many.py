@@ -70,3 +70,17 @@ def test_reverse_pass_through_records(P, np_):
     for r in runs[1:]:
         assert r["dtau"] == runs[0]["dtau"] and r["dgravity"] == runs[0]["dgravity"]
         assert np.array_equal(r["dv0"], runs[0]["dv0"]) and np.array_equal(r["dx0"], runs[0]["dx0"])
+
+
+@pytest.mark.parametrize("lattice,n,np_,storage", [(9, (512, 512, 1), 10_000, "fp32"), (19, (61, 67, 72), 3000, "fp16")])
+def test_a_taped_step_holds_particles_not_bins(P, lattice, n, np_, storage):
+    """What a rollout's buffer grows by with each taped step: the populations, the force field and, per particle,
+    positions (two parts), velocity, id and bin; nothing per bin."""
+    D = 2 if lattice == 9 else 3
+    sim = P.Sim(P.make_config(lattice=lattice, n=n, contact="soft", n_sub=1, storage=storage), np_)
+    grown = [sim.lib.pibm_rollout_bytes(sim.ctx, t, t) for t in (200, 100)]
+    per_step = (grown[0] - grown[1]) / 100
+    N = n[0] * n[1] * n[2]
+    held = N * (lattice * (2 if storage == "fp16" else 4) + 4 * D) + 4 * (3 * D + 2) * np_
+    print(f"a taped step {lattice} {n}: {per_step / 1e6:.3f} MB", flush=True)
+    assert per_step <= held + 256          # a step's share of the alignment
