@@ -2970,7 +2970,7 @@ __device__ __forceinline__ float quad_dot(float a, float b) {
 // du - (R W + R' W') x n.
 //
 // ROWS: islands of three to eight particles, each with at most two candidates:
-// a quad per contact, those of a member eight lanes apart (md_row_lane) with a
+// a quad per contact, those of a member eight lanes apart (split_row_lane) with a
 // copy of its state each and their contacts' forces added; the partner's state
 // by a lane shuffle, 0.39 us a sub-step.  `lane0`: the packed lane of the first
 // member, isz: the island's size.
@@ -3264,9 +3264,12 @@ __device__ __forceinline__ MdForms md_forms(int sz, int lane0, int nl, const int
 // other pairs jump over most of theirs; 32 of them in a wave, one lane per
 // particle, cost less: 256^3 with 2M particles, 14,000 of them active, this and
 // k_island_small 26 + 19 us with every pair here, 13 + 15 us so.)
-// A kernel of its own: in one with the general loop their registers spilled,
-// 64^3 with 40 touching pairs 6.2 instead of 5.4 ms.  With a third particle in
-// reach of one pair: 31.2 ms in the general loop, 11.7 by md_multi, 7.7 now.
+// A kernel of its own, also where few islands qualify: as the first workgroups of
+// k_island_small it would be done beside it (256^3 just released, the DEM phase
+// 0.273 instead of 0.285 ms of a step of 1.52), but their registers meet those of
+// the general loop, and 64^3 with 40 touching pairs takes 6.25 instead of 5.99 ms.
+// With a third particle in reach of one pair: 31.2 ms in the general loop, 11.7
+// by md_multi, 7.1 now.
 template <int D>
 __global__ __launch_bounds__(64) void k_island_quads(PState A, PState Bn, int np, PCfg c,
                                                      const int* __restrict__ lanemember,
@@ -4364,7 +4367,8 @@ static void dem_impl(PBuf& b, int np, const PCfg& c, bool one_group, hipStream_t
         hipLaunchKernelGGL(k_cand_place, dim3(grid_act), dim3(256), 0, s, b.alist, b.ccount, b.prefix, b.cand,
                            b.aidx, b.loc, b.cdata, b.counters);
     }
-    // (a workgroup per packed wave, four per wave of islands of one or two without Mindlin)
+    // (workgroups take turns; k_island_small has, without Mindlin, four shares per packed wave of islands of one or
+    // two and up to MD_PARTS per wave of larger ones)
     const dim3 gsmall(std::max<unsigned>(grid_act * 4, 256u));
     const dim3 gsplit(4 * gsmall.x);
     if (c.contact >= PIBM_CONTACT_HERTZ_MINDLIN) {
