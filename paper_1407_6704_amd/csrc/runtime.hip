@@ -1167,6 +1167,10 @@ pibm_status pibm_backward(pibm_ctx* c, const float* dJ_dx_T, const float* dJ_dv_
     if (dJ_dv0) q(hipMemcpyAsync(dJ_dv0, R.ub[cur], 4 * DN, hipMemcpyDeviceToDevice, s));
     float acc[8];
     q(hipMemcpyAsync(acc, R.acc, sizeof(acc), hipMemcpyDeviceToHost, s));
+    // the keys that belong to the bins that the last reverse step rebuilt
+    if (R.steps > 0)
+        q(hipMemcpyAsync(c->pb.keys_sorted, adj_tape_view(D, c->pb, np, R.tape_p).keys_sorted, 4 * (size_t)np,
+                         hipMemcpyDeviceToDevice, s));
     // leave the context in the final state of the rollout
     q(hipMemcpyAsync(c->fA, R.ck_f[R.nck - 1], fbytes, hipMemcpyDeviceToDevice, s));
     adj_load_state(D, c->pb, np, R.ck_p[R.nck - 1], R.d_id, R.rp_id, s);

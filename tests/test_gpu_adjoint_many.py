@@ -84,3 +84,18 @@ def test_a_taped_step_holds_particles_not_bins(P, lattice, n, np_, storage):
     held = N * (lattice * (2 if storage == "fp16" else 4) + 4 * D) + 4 * (3 * D + 2) * np_
     print(f"a taped step {lattice} {n}: {per_step / 1e6:.3f} MB", flush=True)
     assert per_step <= held + 256          # a step's share of the alignment
+
+
+@pytest.mark.parametrize("np_,K", [(40, 3), (600, 3), (600, 7)])
+def test_cell_list_after_the_reverse_pass(P, np_, K):
+    """The keys and bins that are left after a backward pass are those of the first step, the last one reversed."""
+    print(f"cell list after the reverse pass {np_} {K}", flush=True)
+    n = (90, 101, 1)
+    X, U, d, rp = _dilute(9, n, np_, 5)
+    sim = _gpu_grads(P, 9, n, X, U, d, rp, 0.7, 1e-3, 7, K)["sim"]
+    keys, _, start = sim.read_cell_list()
+    plain = P.Sim(P.make_config(lattice=9, n=n, tau=0.7, gravity=(0, -1e-3, 0), contact="soft", k_soft=2e-3, n_sub=1), np_)
+    plain.set_particles(X, U, d, rp)
+    plain.step(1)
+    ref = plain.read_cell_list()
+    assert np.array_equal(keys, ref[0]) and np.array_equal(start, ref[2])
