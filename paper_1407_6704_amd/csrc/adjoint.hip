@@ -348,10 +348,6 @@ __device__ __forceinline__ void soft_mag(float ks, float s, float rc, float& f, 
 // adjoints (rho_i-bar, j_i-bar) with their weights for spreading, and one
 // partial sum of d/dgvec per block.
 constexpr int adj_lanes(int D) { return D == 3 ? 16 : 4; }      // lanes per particle: rows of its stencil
-__device__ __forceinline__ float pick(const float* w, int k) {
-    const float lo = (k & 1) ? w[1] : w[0], hi = (k & 1) ? w[3] : w[2];
-    return (k & 2) ? hi : lo;
-}
 template <int LP>
 __device__ __forceinline__ void lane_sum(float& v) {
 #pragma unroll
@@ -398,8 +394,8 @@ __global__ __launch_bounds__(256) void k_adj_particles(PState A, int np, Grid g,
         {
             const int ky = lane & 3, kz = D == 3 ? lane >> 2 : 0;
             const int y = base[1] + ky, z = (D == 3) ? base[2] + kz : 0;
-            const float py = pick(phi[1], ky), dpy = pick(dphi[1], ky);
-            const float pz = D == 3 ? pick(phi[2], kz) : 1.f, dpz = D == 3 ? pick(dphi[2], kz) : 0.f;
+            const float py = pick_weight(phi[1], ky), dpy = pick_weight(dphi[1], ky);
+            const float pz = D == 3 ? pick_weight(phi[2], kz) : 1.f, dpz = D == 3 ? pick_weight(dphi[2], kz) : 0.f;
             const bool row = y >= 0 && y < g.n[1] && z >= 0 && z < g.n[2];
             float4 mm[4];
             float fb[4][3];

@@ -840,10 +840,6 @@ bool particles_interp_by_nodes(int D, int np, long long N) {
     return D == 3 && np <= std::min<long long>(1024, 640 + N / 2048);
 }
 
-__device__ __forceinline__ float pick_weight(const float* w, int k) {
-    const float lo = (k & 1) ? w[1] : w[0], hi = (k & 1) ? w[3] : w[2];
-    return (k & 2) ? hi : lo;
-}
 template <class Src, bool LAG>
 __global__ __launch_bounds__(256) void k_interp_nodes(PState A, int np, Grid g, Src src, float* __restrict__ drho_i,
                                                       float* __restrict__ j_i, short4* __restrict__ wbase,

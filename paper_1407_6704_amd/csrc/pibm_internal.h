@@ -262,7 +262,7 @@ enum {
 
 constexpr int WAVE = 64;
 constexpr unsigned NUM_XCD = 8;
-constexpr unsigned NUM_CU = 256;
+constexpr unsigned NUM_CU = 256;     // of an MI355X (only the layout of the touching islands asks)
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  Map dispatch index b (on XCD b % 8) to a logical block so that every
@@ -330,6 +330,12 @@ __device__ __forceinline__ void drag_power(float hc, int m, float& qm, float& om
 __device__ __forceinline__ float rcp_fast(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float sqrt_fast(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ float rsq_fast(float x) { return __builtin_amdgcn_rsqf(x); }
+
+// w[k] of four values in registers.
+__device__ __forceinline__ float pick_weight(const float* w, int k) {
+    const float lo = (k & 1) ? w[1] : w[0], hi = (k & 1) ? w[3] : w[2];
+    return (k & 2) ? hi : lo;
+}
 
 // Particle mass: sphere (3D) or disk of unit depth (2D).
 __device__ __forceinline__ float particle_mass(int D, float d, float rp) {

@@ -953,14 +953,13 @@ pibm_status pibm_read_cell_list(pibm_ctx* c, uint32_t* keys, int32_t* ids, int32
 namespace {
 constexpr uint32_t ONE_GROUP_MAX = 1024;   // one pass per phase: faster than nine launches
 
-// One coupled step from populations fin to fout, with the force field in F.
-// Returns the first failure of the enqueued event records and copies (kernel
-// launch errors are read by the caller with hipGetLastError).
-// One coupled step from fin into fout.  want_F: the force field must be
-// written to F (a rollout records it); otherwise 3D spreading with bins of
-// one dual cell and FP32 storage is fused into the collision (with FP16
-// storage the collision is short enough that the fused tile order costs
-// more than the force field's traffic saves).
+// One coupled step from fin into fout, with the force field in F.  want_F: it
+// must be written there (a rollout records it); otherwise 3D spreading with
+// bins of one dual cell and FP32 storage is fused into the collision (with
+// FP16 storage the collision is short enough that the fused tile order costs
+// more than the force field's traffic saves).  Returns the first failure of
+// the enqueued event records and copies (kernel launch errors are read by the
+// caller with hipGetLastError).
 // tape (nullable): where the sorted particles are saved.
 hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int row, bool want_F,
                        uint32_t* tape = nullptr) {
@@ -969,10 +968,10 @@ hipError_t launch_step(pibm_ctx* c, const void* fin, void* fout, float* F, int r
     const float ff[3] = {(float)c->cfg.fluid_force[0], (float)c->cfg.fluid_force[1], (float)c->cfg.fluid_force[2]};
     const bool spread = c->np > 0 && c->cfg.two_way;
     const bool fuse_sc = spread && !want_F && c->D == 3 && c->pc.L == 0 && !c->fp16;
-    // Few particles in 3D take the moments of their support nodes straight from
-    // the populations.  Otherwise D2Q9 interpolation takes the moments straight from the populations of
-    // the tiles that hold particles; 3D (15 or 19 planes, a larger halo) and
-    // the coarse-bin path read them from a moments pass, which the cell list
+    // few particles in 3D take the moments of their support nodes straight
+    // from the populations; D2Q9 interpolation those of the tiles that hold
+    // particles; the rest of 3D (15 or 19 planes, a larger halo) and the
+    // coarse-bin path read them from a moments pass, which the cell list
     // restricts to the node rows that the particles' stencils reach
     const bool fused = c->D == 2 && c->pc.L <= 1;
     q(mark(c, row, 0));
