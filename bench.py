@@ -45,16 +45,16 @@ PROFILE_SAMPLES = 10     # timed steps that record the phase events (evenly spac
 # and the shared device header) hashes to `kernel_sha`: a changed kernel
 # reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    ("collide", "c1"): {"fetch_bytes": 184657106, "write_bytes": 153742632, "kernel_sha": "74c47c78842cd7f4"},
-    ("collide", "c3"): {"fetch_bytes": 838978130, "write_bytes": 645541636, "kernel_sha": "74c47c78842cd7f4"},
-    ("interp", "c1"): {"fetch_bytes": 147793950, "write_bytes": 35927872, "kernel_sha": "13550b2c69f29678"},
-    ("interp", "c2"): {"fetch_bytes": 268623185, "write_bytes": 180321752, "kernel_sha": "13550b2c69f29678"},
-    ("interp", "c3"): {"fetch_bytes": 268623185, "write_bytes": 180662947, "kernel_sha": "13550b2c69f29678"},
-    ("moments", "c2"): {"fetch_bytes": 884715750, "write_bytes": 180287632, "kernel_sha": "3729ded843aba06f"},
-    ("moments", "c3"): {"fetch_bytes": 365832693, "write_bytes": 136273430, "kernel_sha": "3729ded843aba06f"},
-    ("spread", "c1"): {"fetch_bytes": 44522500, "write_bytes": 33539504, "kernel_sha": "f927fd0435b43768"},
-    ("spread", "c3"): {"fetch_bytes": 212372739, "write_bytes": 201271147, "kernel_sha": "f927fd0435b43768"},
-    ("spread_collide", "c2"): {"fetch_bytes": 1488861922, "write_bytes": 1296542399, "kernel_sha": "a6643ec0a5e65b86"},
+    ("collide", "c1"): {"fetch_bytes": 184638500, "write_bytes": 153812181, "kernel_sha": "98361e087ec91b5a"},
+    ("collide", "c3"): {"fetch_bytes": 838987201, "write_bytes": 645909845, "kernel_sha": "98361e087ec91b5a"},
+    ("interp", "c1"): {"fetch_bytes": 141231738, "write_bytes": 35991275, "kernel_sha": "9297d352d16df8c4"},
+    ("interp", "c2"): {"fetch_bytes": 269322717, "write_bytes": 192433813, "kernel_sha": "9297d352d16df8c4"},
+    ("interp", "c3"): {"fetch_bytes": 269355953, "write_bytes": 192396000, "kernel_sha": "9297d352d16df8c4"},
+    ("moments", "c2"): {"fetch_bytes": 689591506, "write_bytes": 136314880, "kernel_sha": "fe07c879d6123bfe"},
+    ("moments", "c3"): {"fetch_bytes": 365859749, "write_bytes": 136314880, "kernel_sha": "fe07c879d6123bfe"},
+    ("spread", "c1"): {"fetch_bytes": 44519862, "write_bytes": 33554432, "kernel_sha": "a781ae1f0554245d"},
+    ("spread", "c3"): {"fetch_bytes": 212390013, "write_bytes": 201355541, "kernel_sha": "a781ae1f0554245d"},
+    ("spread_collide", "c2"): {"fetch_bytes": 1488859353, "write_bytes": 1296653643, "kernel_sha": "2371aeeb9ad91ac4"},
 }
 # the source of each measured kernel: its __global__ function and the device
 # routines of its own file that carry its arithmetic (pibm_internal.h, which
