@@ -308,7 +308,7 @@ __device__ __forceinline__ void axis_weights_grad(float xh, float xl, int n, int
     const float fr = dual_frac(xh, xl, c);
     float sv, cv;
     sincospif(0.5f * fr, &sv, &cv);
-    base = c - 1;
+    base = bounded_cell(c, n) - 1;
     float w[4] = {0.25f * (1.0f - sv), 0.25f * (1.0f + cv), 0.25f * (1.0f + sv), 0.25f * (1.0f - cv)};
     const float k = 0.125f * PI_F;
     float dw[4] = {-k * cv, -k * sv, k * cv, k * sv};
@@ -319,7 +319,7 @@ __device__ __forceinline__ void axis_weights_grad(float xh, float xl, int n, int
         S += w[i];
         dS += dw[i];
     }
-    const float inv = S > 0.f ? 1.0f / S : 0.f;
+    const float inv = S > 0.f && base == c - 1 ? 1.0f / S : 0.f;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         phi[i] = w[i] * inv;

@@ -31,9 +31,7 @@ namespace pibm {
 
 
 __device__ __forceinline__ int bin_of(const PCfg& c, float xh, float xl, int a) {
-    int ci = dual_cell(xh, xl);
-    int b = (ci + 1) >> c.L;
-    return min(max(b, 0), c.nb[a] - 1);
+    return (bounded_cell(dual_cell(xh, xl), c.n[a]) + 1) >> c.L;
 }
 
 // ---------------------------------------------------------------------------
@@ -511,7 +509,7 @@ __global__ __launch_bounds__(256) void k_unpack_records(const float4* __restrict
 // ---------------------------------------------------------------------------
 // interpolation (Eqs. lbm11-lbm12 weights, moments gathered): phi_k = delta(X - (i + 1/2)) of the four
 // nodes i = floor(X - 1/2) - 1 + k, zero outside the domain, divided by
-// their sum.  With fr = X - 1/2 - floor(X - 1/2) the four cosines are
+// their sum (all zero for a particle that has left the box).  With fr = X - 1/2 - floor(X - 1/2) the four cosines are
 // -sin, cos, sin, -cos of (pi fr / 2).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void axis_weights(float xh, float xl, int n, int& base, float* phi) {
@@ -519,14 +517,14 @@ __device__ __forceinline__ void axis_weights(float xh, float xl, int n, int& bas
     float fr = dual_frac(xh, xl, c);
     float sv, cv;
     sincospif(0.5f * fr, &sv, &cv);
-    base = c - 1;
+    base = bounded_cell(c, n) - 1;
     float w0 = 0.25f * (1.0f - sv), w1 = 0.25f * (1.0f + cv), w2 = 0.25f * (1.0f + sv), w3 = 0.25f * (1.0f - cv);
     if (base < 0 || base >= n) w0 = 0.f;
     if (base + 1 < 0 || base + 1 >= n) w1 = 0.f;
     if (base + 2 < 0 || base + 2 >= n) w2 = 0.f;
     if (base + 3 < 0 || base + 3 >= n) w3 = 0.f;
     float sum = w0 + w1 + w2 + w3;
-    float inv = sum > 0.f ? 1.0f / sum : 0.f;
+    float inv = sum > 0.f && base == c - 1 ? 1.0f / sum : 0.f;
     phi[0] = w0 * inv; phi[1] = w1 * inv; phi[2] = w2 * inv; phi[3] = w3 * inv;
 }
 
@@ -538,7 +536,7 @@ __device__ __forceinline__ void axis_weights(float xh, float xl, int n, int& bas
 __device__ __forceinline__ void axis_lagrange(float xh, float xl, int n, float* lag) {
     const int c = dual_cell(xh, xl);
     const float t = dual_frac(xh, xl, c) + 1.0f;
-    const int base = c - 1;
+    const int base = bounded_cell(c, n) - 1;
     bool in[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) in[k] = base + k >= 0 && base + k < n;

@@ -214,10 +214,12 @@ __host__ __device__ __forceinline__ void df_add(float& hi, float& lo, float d) {
 
 // Dual cell floor(X - 1/2) of X = hi + lo, exactly (hi - 1/2 is exact for
 // hi >= 1/4 and cannot reach an integer below; lo only matters when
-// hi - 1/2 is an integer).
+// hi - 1/2 is an integer).  A particle that has left the box may be anywhere,
+// also at infinity or NaN: the cell is then one far outside, from which the
+// few nodes of a stencil are counted without overflow.
 __device__ __forceinline__ int dual_cell(float hi, float lo) {
     float t = hi - 0.5f;
-    float c = floorf(t);
+    float c = fminf(fmaxf(floorf(t), -1e9f), 1e9f);
     int ci = (int)c;
     if (t == c && lo < 0.0f) ci -= 1;
     return ci;
@@ -227,6 +229,13 @@ __device__ __forceinline__ float dual_frac(float hi, float lo, int c) {
     float f = ((hi - 0.5f) - (float)c) + lo;
     return fminf(fmaxf(f, 0.0f), 0.99999994f);
 }
+
+// The dual cell that stands for cell c in the cell list and as the place of the
+// weights: c itself, -1 .. n - 1 for every position in the box.  For a particle
+// that has left it (flagged) bin and weights agree on the nearest cell, so that
+// a node's distance from the first node stays among the four weights (unbounded
+// it was read far outside LDS and the records: a GPU fault).
+__device__ __forceinline__ int bounded_cell(int c, int n) { return min(max(c, -1), n - 1); }
 
 // Particle state, structure of arrays in sorted (bin, id) order.
 struct PState {
