@@ -3811,6 +3811,22 @@ __device__ __forceinline__ void spread_tile(const Grid& g, const PCfg& c, const 
             }
         }
         __syncthreads();
+    } else {
+        // too many to stage: in the particles' place, per row and node column
+        // the first and the end slot as whole words (pk holds 16 bits of each,
+        // and there may be more particles around the tile than that)
+        static_assert(2 * NR * TX <= MAXP * PW, "the slots fit the particles' place");
+        if (t < NR) {
+            const int cy = cy0 + t % HY, cz = cz0 + t / HY;
+            const bool ok = cy >= 0 && cy < c.nb[1] && cz >= 0 && cz < c.nb[2] && lo <= hi;
+            const uint32_t* row = start + (ok ? ((long long)cz * c.nb[1] + cy) * c.nb[0] : 0);
+#pragma unroll 1
+            for (int lx = 0; lx < TX; lx++) {
+                sp[2 * (t * TX + lx)] = __uint_as_float(ok ? row[min(max(cx0 + lx, lo), hi + 1)] : 0u);
+                sp[2 * (t * TX + lx) + 1] = __uint_as_float(ok ? row[min(max(cx0 + lx + 4, lo), hi + 1)] : 0u);
+            }
+        }
+        __syncthreads();
     }
     for (int node = t; node < TX * TY * TZ; node += 256) {
         const int lx = node % TX, ly = (node / TX) % TY, lz = node / (TX * TY);
@@ -3869,11 +3885,9 @@ __device__ __forceinline__ void spread_tile(const Grid& g, const PCfg& c, const 
 #pragma unroll 1
             for (int i = 0; i < NRW; i++) {
                 const int ky = i & 3, kz = i >> 2;
-                const int r = row_of(i);
-                const uint32_t pr = pk[r * TX + lx];
-                for (uint32_t k = pr & 0xffffu; k < (pr >> 16); k++) {
-                    // particle k of halo row r sits at sorted slot rowg0[r] + (k - rowbase[r])
-                    const uint32_t gsl = rowg0[r] + (k - rowbase[r]);
+                const float* w = sp + 2 * (row_of(i) * TX + lx);
+                const uint32_t s1 = __float_as_uint(w[1]);
+                for (uint32_t gsl = __float_as_uint(w[0]); gsl < s1; gsl++) {
                     const float* q = srec + (long long)gsl * RS::STRIDE;
                     const float W = q[x - __float_as_int(q[RS::BASE])] * q[4 + ky] *
                                     (D == 3 ? q[8 % (4 * D) + kz] : 1.f);

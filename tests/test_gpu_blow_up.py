@@ -2,7 +2,8 @@
 box by far, more of them in the corner tiles than are staged in LDS, on steps
 that were queued behind the one that lost them (the library reports E_UNSTABLE
 or E_SKIN at the next synchronising call and goes on with new particles and
-fluid).
+fluid); and more particles around a tile than 16 bits count, against the FP64
+oracle.
 
 Bounds: those of the free-particle tests (1e-5 for fields, velocities and
 displacements).
@@ -84,3 +85,33 @@ def test_overlapping_particles_blow_up(P, orc, lat, n):
     p = np.stack([k % side, (k // side) % side, k // side ** 2])[:D]
     X = np.stack([1.0 + p[a] * (n[a] - 2.0) / side for a in range(D)]).astype(np.float32).astype(np.float64)
     _works_as_before(P, orc, sim, lat, X, rng)
+
+
+@pytest.mark.parametrize("lat", [9, 19])
+def test_more_particles_around_a_tile_than_16_bits_count(P, orc, lat):
+    print(f"crowded tile {lat}", flush=True)
+    D, np_ = (2 if lat == 9 else 3), (70_000 if lat == 9 else 120_000)
+    n = (40, 24, 1) if D == 2 else (36, 10, 9)
+    rng = np.random.default_rng(4)
+    X = np.stack([rng.uniform(0.3 if a else 2.0, n[a] - 0.3 if a else 30.0, np_) for a in range(D)])
+    X[1] = rng.uniform(2.0, 9.0, np_)
+    if D == 3:
+        X[2] = rng.uniform(2.0, 7.0, np_)
+    X = X.astype(np.float32).astype(np.float64)
+    U = (1e-4 * rng.standard_normal((D, np_))).astype(np.float32).astype(np.float64)
+    d, rp = np.full(np_, np.float32(0.02)).astype(np.float64), np.full(np_, 2.0)
+    g = [0.0, 0.0, 0.0]
+    g[D - 1] = -1e-5
+    cfg = P.make_config(lattice=lat, n=n, tau=0.8, gravity=g, n_sub=2000, contact="none")
+    sim = P.Sim(cfg, np_)
+    sim.set_particles(X, U, d, rp)
+    f0 = G.to_oracle_f(orc, lat, sim.read_populations())
+    out = orc.step(G.oracle_cfg(orc, cfg), f0, X.copy(), U.copy(), d, rp)
+    sim.step(1)
+    sim.synchronize()
+    got = sim.read_particles()
+    eu, er, _ = G.field_errors(orc, lat, sim.read_populations(), out["f"], sim.N)
+    ex = np.abs(got["x"] - out["X"]).max() / np.abs(out["X"] - X).max()
+    ev = np.linalg.norm(got["v"] - out["U"]) / np.linalg.norm(out["U"])
+    print(f"  eps_u={eu:.2e} eps_rho={er:.2e} dX={ex:.2e} dU={ev:.2e}", flush=True)
+    assert eu <= 1e-5 and er <= 1e-6 and ex <= 1e-5 and ev <= 1e-5
