@@ -45,16 +45,16 @@ PROFILE_SAMPLES = 10     # timed steps that record the phase events (evenly spac
 # and the shared device header) hashes to `kernel_sha`: a changed kernel
 # reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    ("collide", "c1"): {"fetch_bytes": 184638500, "write_bytes": 153812181, "kernel_sha": "98361e087ec91b5a"},
-    ("collide", "c3"): {"fetch_bytes": 838987201, "write_bytes": 645909845, "kernel_sha": "98361e087ec91b5a"},
-    ("interp", "c1"): {"fetch_bytes": 141231738, "write_bytes": 35991275, "kernel_sha": "9297d352d16df8c4"},
-    ("interp", "c2"): {"fetch_bytes": 269322717, "write_bytes": 192433813, "kernel_sha": "9297d352d16df8c4"},
-    ("interp", "c3"): {"fetch_bytes": 269355953, "write_bytes": 192396000, "kernel_sha": "9297d352d16df8c4"},
-    ("moments", "c2"): {"fetch_bytes": 689591506, "write_bytes": 136314880, "kernel_sha": "fe07c879d6123bfe"},
-    ("moments", "c3"): {"fetch_bytes": 365859749, "write_bytes": 136314880, "kernel_sha": "fe07c879d6123bfe"},
-    ("spread", "c1"): {"fetch_bytes": 44519862, "write_bytes": 33554432, "kernel_sha": "a781ae1f0554245d"},
-    ("spread", "c3"): {"fetch_bytes": 212390013, "write_bytes": 201355541, "kernel_sha": "a781ae1f0554245d"},
-    ("spread_collide", "c2"): {"fetch_bytes": 1488859353, "write_bytes": 1296653643, "kernel_sha": "2371aeeb9ad91ac4"},
+    ("collide", "c1"): {"fetch_bytes": 184638522, "write_bytes": 153807744, "kernel_sha": "c7603d51a0160581"},
+    ("collide", "c3"): {"fetch_bytes": 838987301, "write_bytes": 645910251, "kernel_sha": "c7603d51a0160581"},
+    ("interp", "c1"): {"fetch_bytes": 141614635, "write_bytes": 35979072, "kernel_sha": "d20e253490c45f7f"},
+    ("interp", "c2"): {"fetch_bytes": 269326802, "write_bytes": 192501984, "kernel_sha": "d20e253490c45f7f"},
+    ("interp", "c3"): {"fetch_bytes": 269386790, "write_bytes": 192525483, "kernel_sha": "d20e253490c45f7f"},
+    ("moments", "c2"): {"fetch_bytes": 689591589, "write_bytes": 136314880, "kernel_sha": "0dc54acafe66cf5e"},
+    ("moments", "c3"): {"fetch_bytes": 365859793, "write_bytes": 136314880, "kernel_sha": "0dc54acafe66cf5e"},
+    ("spread", "c1"): {"fetch_bytes": 44520891, "write_bytes": 33554432, "kernel_sha": "0c72096d3f9c106e"},
+    ("spread", "c3"): {"fetch_bytes": 212398955, "write_bytes": 201355819, "kernel_sha": "0c72096d3f9c106e"},
+    ("spread_collide", "c2"): {"fetch_bytes": 1488832054, "write_bytes": 1298628224, "kernel_sha": "8eaf11edae903043"},
 }
 # the source of each measured kernel: its __global__ function and the device
 # routines of its own file that carry its arithmetic (pibm_internal.h, which
